@@ -101,14 +101,15 @@ fock_status fock_plan_destroy(fockmi_plan plan);
  * nphi >= 1: an empty target set is FOCK_ERR_ARG, as are a NULL or misaligned
  * pointer, a cell index out of range and an output that overlaps an input;
  * nothing is launched then.
- * With phi == u_occ on a 32^3 cell of at least 3 k-points (FOCK_FP32_COMP,
- * no down-sampling) the pair kernel computes each pair of k-points once and
- * adds its conjugate term to the other target through per-XCD mirror copies:
- * the plan then holds 8 * nk * nb * N_r * 32 bytes of them (29 GB for
- * 216 k-points and 16 bands). The result is bitwise repeatable and agrees
- * with the form that runs every pair to rounding; that form runs instead
- * when the copies exceed the plan's workspace cap or the free device memory,
- * or with FOCKMI_SPLIT_SYM=0 at plan creation.
+ * With phi == u_occ on a 32^3 cell (FOCK_FP32_COMP, no down-sampling) each pair of
+ * fields is transformed once and its conjugate term added to the other row: the plan
+ * then holds a batch of pair fields (8 GiB, less when the device or the plan's workspace
+ * cap cannot hold it) and mirror sums of 24 bytes per grid point and 64 targets of a row
+ * of blocks. The result is bitwise repeatable and agrees with the form that runs every
+ * pair to rounding; that form runs instead when 64 fields' pairs exceed the plan's
+ * workspace cap, or with FOCKMI_SPLIT_SYM=0 at plan creation. A plan created with
+ * FOCKMI_SPLIT_WAIT_TICKS set runs 32^3 cells in the split form (each target on two CUs),
+ * whose wait limit that variable is.
  * Stream-ordered; returns without synchronising. */
 fock_status fock_apply(fockmi_plan plan, int cell, const void* u_occ, const void* phi, int nphi,
                        void* vphi, void* stream);
@@ -124,8 +125,8 @@ fock_status fock_apply(fockmi_plan plan, int cell, const void* u_occ, const void
  * 0 <= k0, nk_out >= 1, k0 + nk_out <= nk and nphi >= 1 (FOCK_ERR_ARG otherwise). Each target's sum is the
  * one fock_apply computes; the plain FP64 path and the grid forms of the fused
  * kernel give the same bits, the 32^3 lockstep form may group its FP64
- * additions differently, and fock_apply's pair-symmetric 32^3 form (phi ==
- * u_occ) adds each target's terms in another order (a k-range runs every
+ * additions differently, and fock_apply's symmetric 32^3 sum (phi == u_occ)
+ * adds each target's terms in another order (a k-range runs every
  * pair of its targets). Stream-ordered. */
 fock_status fock_apply_krange(fockmi_plan plan, int cell, const void* u_occ, int k0, int nk_out, const void* phi,
                               int nphi, void* vphi, void* stream);

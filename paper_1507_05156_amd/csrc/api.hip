@@ -209,9 +209,13 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   bool sym = has_split && split_sym && !c.ds && ps.ntk == c.nk && ps.nsk == c.nk &&
                    ps.qidx == (const int*)c.qidx.ptr && X == P && P == M && nx == ns && c.nk >= 3 &&
                    (!workspace_cap || mirror_bytes <= workspace_cap);
+  // the two-stage pair form, with the pair symmetry when u is targets and sources over the whole mesh
+  const bool pairs_tri = split_sym && !c.ds && ps.ntk == c.nk && ps.nsk == c.nk &&
+                         ps.qidx == (const int*)c.qidx.ptr && X == P && P == M && nx == ns &&
+                         pairs_tri_fits(nitems, nr, nr * sizeof(c64));
   auto usable = [&](int v) {
     if (n != 32) return v >= 0 && v < fused_variants(n);
-    return v == 0 || (v == 1 && has_ls) || (v == 2 && has_split);
+    return v == 0 || (v == 1 && has_ls) || (v == 2 && has_split) || v == 3;
   };
   auto fallback_variant = [&](int v) { return usable(v) ? v : (n == 32 && has_ls ? 1 : 0); };
   // the lockstep form's k' split: the part count (dividing the source k-points,
@@ -253,6 +257,7 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   // buffers of one variant (grown on demand, kept by the plan)
   auto prepare = [&](int v) -> fock_status {
     fock_status st2;
+    if (v == 3) return FOCK_OK;  // run_pairs sizes its own buffers
     const int h = v == 1 ? ksplit : 1;
     if ((st2 = comp.ensure((size_t)h * nitems * nr * sizeof(c64), workspace_cap, "compensation buffer")) != FOCK_OK)
       return st2;
@@ -316,7 +321,20 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
     return FOCK_OK;
   };
   // one application in variant v
+  fock_status pairs_status = FOCK_OK;
   auto launch = [&](int v) -> hipError_t {
+    if (v == 3) {
+      Mirror<float> mr;
+      if (pairs_tri) {
+        mr.F = Xs;
+        mr.dst = out;
+        mr.scale = scale;
+        mr.accumulate = true;
+        mr.tri = true;
+      }
+      pairs_status = run_pairs<float>(c, ps, Xs, nx, Ps, Ms, ns, out, scale, accumulate, (const float*)c.Kt.ptr, mr, st);
+      return hipSuccess;
+    }
     if (v != 2) return launch_fused_apply(n, a, st, v, &ls);
     SplitArgs sa{};
     sa.f = a;
@@ -350,7 +368,7 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
     if (profiling) e2 = launch_count_abort((long long*)fallbacks.ptr, (const int*)sstatus.ptr, st);
     return e2;
   };
-  int variant = fallback_variant(fused_default_variant(n));
+  int variant = fallback_variant(n == 32 && split_form ? 2 : fused_default_variant(n));
   hipError_t e;
   const std::string key = key_for(c, ps, nx, "fused");
   TuneEntry te;
@@ -372,6 +390,7 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
         a.xcd_map = (n != 32 || v == 0) ? x : 1;
         (void)hipEventRecord(e0, st);
         if ((e = launch(v)) != hipSuccess) return hip_fail(e, "fused pair kernel");
+        if (pairs_status != FOCK_OK) return pairs_status;
         (void)hipEventRecord(e1, st);
         if ((e = hipEventSynchronize(e1)) != hipSuccess) return hip_fail(e, "tuning sync");
         float ms = 0.f;
@@ -396,6 +415,7 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   if ((s = prepare(variant)) != FOCK_OK) return s;
   if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
   if ((e = launch(variant)) != hipSuccess) return hip_fail(e, "fused pair kernel");
+  if (pairs_status != FOCK_OK) return pairs_status;
   if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
   return FOCK_OK;
 }
@@ -537,7 +557,10 @@ fock_status fock_plan_create(const fock_cell_desc* cells, int ncells, fock_prec 
     (void)p->tune.load(p->tune_path);
   }
   if (const char* g = std::getenv("FOCKMI_GRAPH")) p->use_graph = std::atoi(g) != 0;
-  if (const char* g = std::getenv("FOCKMI_SPLIT_WAIT_TICKS")) p->split_wait_ticks = std::atol(g);
+  if (const char* g = std::getenv("FOCKMI_SPLIT_WAIT_TICKS")) {
+    p->split_wait_ticks = std::atol(g);
+    p->split_form = 1;  // a plan that sets the split form's wait limit runs the split form
+  }
   if (const char* g = std::getenv("FOCKMI_SPLIT_SYM")) p->split_sym = std::atoi(g);
   if (const char* g = std::getenv("FOCKMI_SPLIT_STAGGER_SHIFT")) p->split_stagger_shift = std::min(std::max(std::atoi(g), 0), 30);
   {

@@ -1,0 +1,497 @@
+// Two-stage pair form: W of every pair of a block through a batch buffer, then the sums.
+//
+//   stage 1 (pair_w_kernel)  one pair per workgroup pass: rho = conj(P_j) X_i, forward 3D
+//                            FFT, kernel multiply, inverse FFT, W_ji stored to the batch;
+//   stage 2 (wsum_kernel)    out_i += sum_j M_j W_ji, and for a two-sided block also
+//                            mir_j += sum_i F_i conj(W_ji), both from one read of W.
+//
+// Stage 2 with both sides is what the two-stage form is for. The pair (j, i) with targets
+// and sources exchanged has the density conj(rho) and the table of -q on the reflected
+// grid, K_{-q}(-G) = K_q(G) (Nyquist planes are averaged over both signs), so its W is
+// conj(W_ji): with u as targets and sources one transform serves two rows of the result,
+// and no sum crosses workgroups while a pair is transformed.
+//
+// Bound: stage 1 at 32^3 by its transforms and their transposes (17 us of the 30 us a CU
+// takes per pair; the rest is the operands' loads and the drain of the W stores, which one
+// field per CU cannot overlap), stage 2 by the one read of W. 32^3 / 216 k / 16 bands, FP32:
+// 1,732 ms per application with every pair of k-points pushed between CU pairs (split32.hip),
+// 1,270 ms in this form with plain W accesses, 1,142 ms with non-temporal ones, 1,088 ms with
+// the next pair's first operands loaded before the stores. One of eight k-point shards of it
+// (one-sided sums): 284.6 -> 247 ms.
+#include "pairs.hpp"
+
+#include "fused_common.hpp"
+
+namespace fockmi {
+
+namespace {
+
+__device__ __forceinline__ cx<float> ld_cx(rsrc_t r, unsigned vo, unsigned so, float) { return ld_c64(r, vo, so); }
+__device__ __forceinline__ cx<double> ld_cx(rsrc_t r, unsigned vo, unsigned so, double) { return ld_c128(r, vo, so); }
+__device__ __forceinline__ float ld_re(rsrc_t r, unsigned vo, unsigned so, float) { return ld_f32(r, vo, so); }
+__device__ __forceinline__ double ld_re(rsrc_t r, unsigned vo, unsigned so, double) { return ld_f64(r, vo, so); }
+
+// rounds of a transpose through LDS and the LDS elements they need
+template <int N, int NPH>
+constexpr int pw_lds_elems() {
+  constexpr int H = N / NPH;
+  return NPH == 1 ? N * N * (N + 1) : (N * N * H > H * N * (N + 1) ? N * N * H : H * N * (N + 1));
+}
+
+template <int N, typename T>
+constexpr int pw_nph() {
+  return ((long)N * N * (N + 1) * (long)sizeof(cx<T>) > 160L * 1024) ? 2 : 1;
+}
+// elements whose loads are in flight together: operands of the pair product, kernel values
+template <int N, typename T>
+constexpr int pw_grp_px() { return sizeof(T) == 8 ? 4 : (N == 32 ? 12 : (N == 16 ? 8 : 4)); }
+// elements of the next pair's operands loaded before the current pair's W is stored (at 32^3
+// what the registers hold beside the line: 6; 1 ahead 1,114 ms, 6 ahead 1,088 ms)
+template <int N, typename T>
+constexpr int pw_ahead() { return sizeof(T) == 8 ? (N == 24 ? 1 : 4) : (N == 32 ? 6 : 8); }
+template <int N, typename T>
+constexpr int pw_grp_k() { return sizeof(T) == 8 ? 4 : (N <= 24 ? N : 8); }
+
+// a uniform load through the scalar cache: a vector load here would wait for the W stores
+// in flight, like every load that is waited for behind them
+__device__ __forceinline__ int ld_uniform(const int* p) {
+  return *(const __attribute__((address_space(4))) int*)(uintptr_t)p;
+}
+
+// W is written once and read once, much later: the non-temporal hint keeps it from pushing
+// the operands out of L2 (an XCD's 32 CUs write 8 MiB of W per pair round, twice its L2)
+template <typename T>
+__device__ __forceinline__ void st_w(cx<T>* p, cx<T> v) {
+  typedef T v2 __attribute__((ext_vector_type(2)));
+  __builtin_nontemporal_store((v2){v.re, v.im}, (v2*)p);
+}
+template <typename T>
+__device__ __forceinline__ cx<T> ld_w(const cx<T>* p) {
+  typedef T v2 __attribute__((ext_vector_type(2)));
+  const v2 v = __builtin_nontemporal_load((const v2*)p);
+  return {v.x, v.y};
+}
+
+template <int N, typename T, int WPE>
+__global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE))) pair_w_kernel(PairArgs<T> a) {
+  constexpr int NPH = pw_nph<N, T>();
+  constexpr int E = (int)sizeof(cx<T>);
+  constexpr int NTI = N * N;
+  constexpr int NR = N * N * N;
+  constexpr int H = N / NPH;
+  constexpr int TPG = NTI / NPH;
+  constexpr int NBK = N / NPH;
+  constexpr bool XY_WAVES = TPG % 64 == 0;
+  constexpr bool YZ_WAVES = XY_WAVES && (NBK * H) % 64 == 0;
+  __shared__ cx<T> lds[pw_lds_elems<N, NPH>()];
+  static_assert(sizeof(lds) <= 160 * 1024, "LDS of the pair kernel");
+
+  const int t = threadIdx.x;
+  const int grp = (NPH == 1) ? 0 : (XY_WAVES ? __builtin_amdgcn_readfirstlane(t / TPG) : t / TPG);
+  const int tl = t % TPG;
+  const int hl = tl % H;
+  const int clo = hl + H * grp;  // m3 in the x and y phases, l2 in the z phase
+  const int chi = tl / H;        // m2 in the x phase, l1 in the y and z phases
+  const int gyz = (NPH == 1) ? 0 : (YZ_WAVES ? __builtin_amdgcn_readfirstlane(chi / NBK) : chi / NBK);
+  const int lrow = chi % NBK;
+
+  // LDS byte offsets of this thread's elements in the transposes (see fused.hip)
+  constexpr bool INPLACE = NPH == 1;
+  constexpr unsigned SX = INPLACE ? (unsigned)(N * (N + 1) * E) : (unsigned)(N * H * E);
+  constexpr unsigned SY = INPLACE ? (unsigned)((N + 1) * E) : (unsigned)(H * E);
+  constexpr int L1S = (int)((65535u / SX) + 1) < N ? (int)((65535u / SX) + 1) : N;
+  const unsigned lx0 = INPLACE ? (unsigned)((chi * (N + 1) + hl) * E) : (unsigned)((chi * H + hl) * E);
+  const unsigned ly0 = INPLACE ? (unsigned)((chi * N * (N + 1) + hl) * E) : (unsigned)((chi * N * H + hl) * E);
+  const unsigned lyz0 = (unsigned)((lrow * N * (N + 1) + clo) * E);
+  const unsigned lz0 = (unsigned)((lrow * N + clo) * (N + 1) * E);
+  const unsigned voff = (unsigned)((chi * N + clo) * E);
+  const unsigned voff_t = (unsigned)(t * (int)sizeof(T));
+  constexpr unsigned FB = (unsigned)NR * E;
+
+  // The pairs of a block in order: target tiles, for each tile its sources, for each source
+  // the tile's targets. XCD x (workgroups b = x mod 8) runs a contiguous eighth of them, so
+  // that the tile's targets, the current sources and the kernel table meet in its L2.
+  const long n = a.npairs;
+  const int x = blockIdx.x & 7;
+  const long q1 = n * (x + 1) / 8, step = gridDim.x >> 3;
+  long q = n * x / 8 + (blockIdx.x >> 3);
+  if (q >= q1) return;
+  int tile = 0;
+  long tile_q0 = 0, tile_q1 = 0;  // pairs of the current tile
+  int tw = 0;                     // its targets
+  int ti = 0, j = 0;              // target and source of the current pair within the block
+  auto enter = [&](int tt) {
+    tile = tt;
+    tw = a.nt - tt * kPairTile < kPairTile ? a.nt - tt * kPairTile : kPairTile;
+    const int njt = a.tri ? (a.nj < (tt + 1) * kPairTile ? a.nj : (tt + 1) * kPairTile) : a.nj;
+    tile_q1 = tile_q0 + (long)tw * njt;
+  };
+  auto locate = [&](long qq) {
+    while (qq >= tile_q1) {
+      tile_q0 = tile_q1;
+      enter(tile + 1);
+    }
+    const int rem = (int)(qq - tile_q0);
+    j = __builtin_amdgcn_readfirstlane(rem / tw);
+    ti = __builtin_amdgcn_readfirstlane(tile * kPairTile + rem % tw);
+  };
+  auto res_x = [&] { return make_rsrc(a.X + (long)(a.t0 + ti) * NR, FB); };
+  auto res_p = [&] { return make_rsrc(a.P + (long)(a.j0 + j) * NR, FB); };
+  // The first PF operands of a pair are loaded before the previous pair's W is stored: a
+  // wait for a load also waits for every store issued before it.
+  constexpr int PF = pw_ahead<N, T>();
+  cx<T> fp[PF], fx[PF];
+  auto fetch = [&] {
+    const rsrc_t rX = res_x(), rP = res_p();
+    static_for<PF>([&](auto e) {
+      const unsigned so = (unsigned)(decltype(e)::value * NTI * E);
+      fp[e] = ld_cx(rP, voff, so, T{});
+      fx[e] = ld_cx(rX, voff, so, T{});
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  enter(0);
+  locate(q);
+  fetch();
+  for (;;) {
+    const int gt = a.t0 + ti, gj = a.j0 + j;
+    const int qi = ld_uniform(a.qidx + (long)(gt / a.nx) * a.nsk + gj / a.ns);
+    const rsrc_t rX = res_x(), rP = res_p();
+    const rsrc_t rK = make_rsrc(a.Kt + (long)qi * NR, NR * (unsigned)sizeof(T));
+    cx<T> v[N];
+    constexpr int G = pw_grp_px<N, T>(), NG = (N - PF + G - 1) / G;
+    static_for<NG>([&](auto cc) {
+      constexpr int C0 = PF + decltype(cc)::value * G, CN = (N - C0 < G) ? N - C0 : G;
+      cx<T> p[CN], xx[CN];
+      static_for<CN>([&](auto e) {
+        const unsigned so = (unsigned)((C0 + decltype(e)::value) * NTI * E);
+        p[e] = ld_cx(rP, voff, so, T{});
+        xx[e] = ld_cx(rX, voff, so, T{});
+      });
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (decltype(cc)::value == 0) static_for<PF>([&](auto e) { v[decltype(e)::value] = cmulc(fp[e], fx[e]); });
+      static_for<CN>([&](auto e) { v[C0 + decltype(e)::value] = cmulc(p[e], xx[e]); });
+    });
+    fft<N, -1>(v);
+    // x -> y
+#pragma unroll
+    for (int g = 0; g < NPH; ++g) {
+      if (grp == g) {
+        const unsigned b0 = opaque(lx0), b1 = opaque(lx0 + L1S * SX);
+        static_for<N>([&](auto l1) {
+          constexpr int L = decltype(l1)::value;
+          if constexpr (L < L1S) lds_at<L * SX>(lds, b0) = v[L];
+          else lds_at<(L - L1S) * SX>(lds, b1) = v[L];
+        });
+      }
+      __syncthreads();
+      if (grp == g) {
+        const unsigned b = opaque(ly0);
+        static_for<N>([&](auto m2) { v[m2] = lds_at<decltype(m2)::value * SY>(lds, b); });
+      }
+      if constexpr (!INPLACE) __syncthreads();
+    }
+    fft<N, -1>(v);
+    // y -> z
+#pragma unroll
+    for (int g = 0; g < NPH; ++g) {
+      if (gyz == g) {
+        const unsigned b = opaque(lyz0);
+        static_for<N>([&](auto l2) { lds_at<decltype(l2)::value * (N + 1) * E>(lds, b) = v[l2]; });
+      }
+      __syncthreads();
+      if (gyz == g) {
+        const unsigned b = opaque(lz0);
+        static_for<N>([&](auto m3) { v[m3] = lds_at<decltype(m3)::value * E>(lds, b); });
+      }
+      if constexpr (!INPLACE) __syncthreads();
+    }
+    fft<N, -1>(v);
+    static_for<(N + pw_grp_k<N, T>() - 1) / pw_grp_k<N, T>()>([&](auto cc) {
+      constexpr int G = pw_grp_k<N, T>(), C0 = decltype(cc)::value * G, CN = (N - C0 < G) ? N - C0 : G;
+      T kv[CN];
+      static_for<CN>([&](auto e) { kv[e] = ld_re(rK, voff_t, (unsigned)((C0 + decltype(e)::value) * NTI * (int)sizeof(T)), T{}); });
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<CN>([&](auto e) { v[C0 + decltype(e)::value] = cscale(v[C0 + decltype(e)::value], kv[e]); });
+    });
+    fft<N, +1>(v);
+    // z -> y
+#pragma unroll
+    for (int g = 0; g < NPH; ++g) {
+      if (gyz == g) {
+        const unsigned b = opaque(lz0);
+        static_for<N>([&](auto m3) { lds_at<decltype(m3)::value * E>(lds, b) = v[m3]; });
+      }
+      __syncthreads();
+      if (gyz == g) {
+        const unsigned b = opaque(lyz0);
+        static_for<N>([&](auto l2) { v[l2] = lds_at<decltype(l2)::value * (N + 1) * E>(lds, b); });
+      }
+      if constexpr (!INPLACE) __syncthreads();
+    }
+    fft<N, +1>(v);
+    // y -> x
+#pragma unroll
+    for (int g = 0; g < NPH; ++g) {
+      if (grp == g) {
+        const unsigned b = opaque(ly0);
+        static_for<N>([&](auto m2) { lds_at<decltype(m2)::value * SY>(lds, b) = v[m2]; });
+      }
+      __syncthreads();
+      if (grp == g) {
+        const unsigned b0 = opaque(lx0), b1 = opaque(lx0 + L1S * SX);
+        static_for<N>([&](auto l1) {
+          constexpr int L = decltype(l1)::value;
+          if constexpr (L < L1S) v[L] = lds_at<L * SX>(lds, b0);
+          else v[L] = lds_at<(L - L1S) * SX>(lds, b1);
+        });
+      }
+      if constexpr (!INPLACE) __syncthreads();
+    }
+    fft<N, +1>(v);
+    char* w = (char*)(a.W + ((long)j * a.nt + ti) * NR);
+    q += step;
+    const bool more = q < q1;
+    if (more) {
+      locate(q);
+      fetch();
+    }
+    static_for<N>([&](auto m1) { st_w((cx<T>*)(w + decltype(m1)::value * (NTI * E) + voff), v[m1]); });
+    if (!more) return;
+  }
+}
+
+// s + c += x with the rounding error carried in c (no contraction: see fused.hip)
+__device__ __forceinline__ void fold(double& s, double& c, double x) {
+#pragma clang fp contract(off)
+  const double t = s + x;
+  if (fabs(s) >= fabs(x)) c += (s - t) + x;
+  else c += (x - t) + s;
+  s = t;
+}
+
+// conj(w) * f added to acc
+template <typename T>
+__device__ __forceinline__ cx<T> cmac_conj(cx<T> acc, cx<T> w, cx<T> f) {
+  return {fmadd(w.im, f.im, fmadd(w.re, f.re, acc.re)), fmadd(-w.im, f.re, fmadd(w.re, f.im, acc.im))};
+}
+
+// Stage 2. One wave holds kPairTile targets on 64 grid points and streams the sources; the
+// NW waves of a workgroup hold NW tiles on the same points, so the mirror sums of NW * 8
+// targets meet in LDS and go to memory once per source.
+template <typename T, int NW, bool TWO>
+__global__ void __launch_bounds__(64 * NW) wsum_kernel(WsumArgs<T> a) {
+  constexpr int TI = kPairTile;
+  constexpr bool F32 = sizeof(T) == 4;
+  __shared__ cx<T> part[TWO ? NW * NW * 64 : 1];  // [source of the batch][wave][lane]
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r = blockIdx.x * 64 + lane;
+  const int tile = blockIdx.y * NW + w;
+  const int left = a.nt - tile * TI;
+  const int n = left < 0 ? 0 : (left < TI ? left : TI);
+  const long nr = a.nr;
+  const long tg0 = (long)(a.t0 + tile * TI);  // first target of this wave
+
+  cx<T> f[TWO ? TI : 1];
+  cx<T> acc[TI];
+  c128 s[F32 ? TI : 1];
+  cx<float> c[F32 ? TI : 1];
+  static_for<TI>([&](auto i) {
+    constexpr int I = decltype(i)::value;
+    acc[I] = cx<T>{0, 0};
+    if constexpr (TWO) f[I] = I < n ? a.F[(tg0 + I) * nr + r] : cx<T>{0, 0};
+    if constexpr (F32) {
+      s[I] = (I < n && (!a.first || a.accumulate)) ? a.out[(tg0 + I) * nr + r] : c128{0.0, 0.0};
+      c[I] = (I < n && !a.first) ? a.comp[(tg0 + I) * nr + r] : cx<float>{0.0f, 0.0f};
+    } else {
+      if (I < n && !a.first) acc[I] = a.run[(tg0 + I) * nr + r];
+    }
+  });
+  int jb = a.jb0;  // band of the current source within its k-point
+  const cx<T>* wp = a.W + (long)tile * TI * nr + r;
+  for (int j0 = 0; j0 < a.nj; j0 += NW) {
+    const int j1 = j0 + NW < a.nj ? j0 + NW : a.nj;
+    for (int j = j0; j < j1; ++j) {
+      const int jt = j / TI;
+      const bool on = n > 0 && (!a.tri || tile >= jt);
+      const bool mir = TWO && on && (!a.tri || tile > jt);
+      cx<T> ms{0, 0};
+      if (on) {
+        const cx<T>* wj = wp + (long)j * a.nt * nr;
+        const cx<T> m = a.M[(long)(a.j0 + j) * nr + r];
+        cx<T> wv[TI];
+        static_for<TI>([&](auto i) {
+          constexpr int I = decltype(i)::value;
+          wv[I] = I < n ? ld_w(wj + I * nr) : cx<T>{0, 0};
+        });
+        static_for<TI>([&](auto i) { acc[decltype(i)::value] = cmac(acc[decltype(i)::value], m, wv[decltype(i)::value]); });
+        if constexpr (TWO) {
+          if (mir) static_for<TI>([&](auto i) { ms = cmac_conj(ms, wv[decltype(i)::value], f[decltype(i)::value]); });
+        }
+      }
+      if constexpr (TWO) part[((j - j0) * NW + w) * 64 + lane] = ms;
+      ++jb;
+      if constexpr (F32) {
+        // the FP32 sum covers at most 16 sources of one k-point, then goes into the
+        // compensated FP64 sum
+        const bool endk = jb == a.ns;
+        if (endk || (jb & 15) == 0 || j == a.nj - 1) {
+          static_for<TI>([&](auto i) {
+            constexpr int I = decltype(i)::value;
+            double cr = c[I].re, ci = c[I].im;
+            fold(s[I].re, cr, a.scale * (double)acc[I].re);
+            fold(s[I].im, ci, a.scale * (double)acc[I].im);
+            c[I] = cx<float>{(float)cr, (float)ci};
+            acc[I] = cx<T>{0, 0};
+          });
+        }
+      }
+      if (jb == a.ns) jb = 0;
+    }
+    if constexpr (TWO) {
+      __syncthreads();
+      if (j0 + w < j1) {
+        // the groups of NW tiles keep mirror sums of their own
+        const long o = ((long)blockIdx.y * a.nsrc + a.j0 + j0 + w) * nr + r;
+        double re = 0.0, im = 0.0;
+        static_for<NW>([&](auto k) {
+          const cx<T> v = part[(w * NW + decltype(k)::value) * 64 + lane];
+          re += (double)v.re;
+          im += (double)v.im;
+        });
+        c128 ms = a.mfirst ? c128{0.0, 0.0} : a.mir[o];
+        if constexpr (F32) {
+          const cx<float> mc = a.mfirst ? cx<float>{0.0f, 0.0f} : a.mcomp[o];
+          double cr = mc.re, ci = mc.im;
+          fold(ms.re, cr, re);
+          fold(ms.im, ci, im);
+          a.mcomp[o] = cx<float>{(float)cr, (float)ci};
+        } else {
+          ms.re += re;
+          ms.im += im;
+        }
+        a.mir[o] = ms;
+      }
+      __syncthreads();
+    }
+  }
+  static_for<TI>([&](auto i) {
+    constexpr int I = decltype(i)::value;
+    if (I < n) {
+      const long o = (tg0 + I) * nr + r;
+      if constexpr (F32) {
+        a.out[o] = a.last ? c128{s[I].re + (double)c[I].re, s[I].im + (double)c[I].im} : s[I];
+        if (!a.last) a.comp[o] = c[I];
+      } else if (a.last) {
+        c128 v = cscale(acc[I], a.scale);
+        if (a.accumulate) v = a.out[o] + v;
+        a.out[o] = v;
+      } else {
+        a.run[o] = acc[I];
+      }
+    }
+  });
+}
+
+// dst[j] = (accumulate ? dst[j] : 0) + scale * sum over the groups g of mir[g][j] + mcomp[g][j],
+// groups in order. Of a symmetric sum in rows of `rows` fields, the fields of the last row
+// have the groups of that row only.
+template <bool F32>
+__global__ void __launch_bounds__(256) mirror_add_kernel(c128* __restrict__ dst, const c128* __restrict__ mir,
+                                                         const cx<float>* __restrict__ mcomp, double scale,
+                                                         int accumulate, int nsrc, int nr, int rows, int tri) {
+  const long count = (long)nsrc * nr;
+  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < count; i += (long)gridDim.x * 256) {
+    int in_row = rows;
+    if (tri) {
+      const int row0 = (int)(i / nr) / rows * rows;
+      in_row = nsrc - row0 < rows ? nsrc - row0 : rows;
+    }
+    const int ng = (in_row + kPairGroup - 1) / kPairGroup;
+    c128 d = accumulate ? dst[i] : c128{0.0, 0.0};
+    for (int g = 0; g < ng; ++g) {
+      c128 m = mir[g * count + i];
+      if constexpr (F32) {
+        m.re += (double)mcomp[g * count + i].re;
+        m.im += (double)mcomp[g * count + i].im;
+      }
+      d.re += scale * m.re;
+      d.im += scale * m.im;
+    }
+    dst[i] = d;
+  }
+}
+
+template <int N, typename T, int WPE>
+hipError_t launch_pw(const PairArgs<T>& a, int slots, hipStream_t st) {
+  const long per = (a.npairs + 7) / 8;
+  const int g = (int)(per < slots / 8 ? per : slots / 8);
+  hipLaunchKernelGGL((pair_w_kernel<N, T, WPE>), dim3(8 * g), dim3(N * N), 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+template <>
+int pair_w_slots<float>(int n, int num_cus) {
+  const int c = (num_cus / 8) * 8;
+  return n == 16 ? 4 * c : (n == 20 ? 2 * c : c);
+}
+template <>
+int pair_w_slots<double>(int n, int num_cus) {
+  const int c = (num_cus / 8) * 8;
+  return n == 16 ? 2 * c : c;
+}
+
+template <>
+hipError_t launch_pair_w<float>(int n, const PairArgs<float>& a, int num_cus, hipStream_t st) {
+  const int slots = pair_w_slots<float>(n, num_cus);
+  switch (n) {
+    case 16: return launch_pw<16, float, 4>(a, slots, st);
+    case 20: return launch_pw<20, float, 4>(a, slots, st);
+    case 24: return launch_pw<24, float, 3>(a, slots, st);
+    case 32: return launch_pw<32, float, 4>(a, slots, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+template <>
+hipError_t launch_pair_w<double>(int n, const PairArgs<double>& a, int num_cus, hipStream_t st) {
+  const int slots = pair_w_slots<double>(n, num_cus);
+  switch (n) {
+    case 16: return launch_pw<16, double, 2>(a, slots, st);
+    case 20: return launch_pw<20, double, 2>(a, slots, st);
+    case 24: return launch_pw<24, double, 3>(a, slots, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+template <typename T>
+hipError_t launch_wsum(const WsumArgs<T>& a, hipStream_t st) {
+  constexpr int NW = kPairGroup / kPairTile;
+  const int tiles = (a.nt + kPairTile - 1) / kPairTile;
+  if (a.nr % 64 != 0) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(a.nr / 64), (unsigned)((tiles + NW - 1) / NW));
+  if (a.mir)
+    hipLaunchKernelGGL((wsum_kernel<T, NW, true>), grid, dim3(64 * NW), 0, st, a);
+  else
+    hipLaunchKernelGGL((wsum_kernel<T, NW, false>), grid, dim3(64 * NW), 0, st, a);
+  return hipGetLastError();
+}
+template hipError_t launch_wsum<float>(const WsumArgs<float>&, hipStream_t);
+template hipError_t launch_wsum<double>(const WsumArgs<double>&, hipStream_t);
+
+hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double scale, int accumulate, int nsrc,
+                             int nr, int rows, int tri, hipStream_t st) {
+  long g = ((long)nsrc * nr + 255) / 256;
+  if (g > 65536) g = 65536;
+  if (mcomp)
+    hipLaunchKernelGGL(mirror_add_kernel<true>, dim3((unsigned)g), dim3(256), 0, st, dst, mir, mcomp, scale, accumulate,
+                       nsrc, nr, rows, tri);
+  else
+    hipLaunchKernelGGL(mirror_add_kernel<false>, dim3((unsigned)g), dim3(256), 0, st, dst, mir, mcomp, scale,
+                       accumulate, nsrc, nr, rows, tri);
+  return hipGetLastError();
+}
+
+}  // namespace fockmi

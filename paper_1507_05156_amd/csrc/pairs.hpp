@@ -1,0 +1,68 @@
+// Launchers of the two-stage pair form (pairs.hip).
+#pragma once
+
+#include "kernels.hpp"
+
+namespace fockmi {
+
+constexpr int kPairTile = 8;   // targets of one tile: the targets one wave of stage 2 holds
+constexpr int kPairGroup = 64;  // targets of one workgroup of stage 2: those whose mirror sums meet there
+
+// A block of pairs: nt targets from t0 on (index kt * nx + s) against nj sources from j0 on
+// (index ks * ns + band). With tri, targets and sources are the same fields (t0 == j0,
+// nt == nj) and only the pairs whose target tile is not below the source tile are run.
+// W of pair (t, j) is field j * nt + t of the batch.
+template <typename T>
+struct PairArgs {
+  const cx<T>* X;   // targets [ntk][nx][nr]
+  const cx<T>* P;   // sources [nsk][ns][nr], conjugated in the density
+  const T* Kt;      // [nq][nr] kernel tables in the z-phase order, 1/N_r folded
+  const int* qidx;  // [ntk][nsk]
+  cx<T>* W;
+  int t0, nt, j0, nj, nx, ns, nsk, tri;
+  long npairs;      // pairs the block runs
+};
+inline long pair_count(int nt, int nj, bool tri) {
+  if (!tri) return (long)nt * nj;
+  long n = 0;
+  for (int t = 0; t < nt; t += kPairTile) {
+    const int w = nt - t < kPairTile ? nt - t : kPairTile, m = t + kPairTile < nj ? t + kPairTile : nj;
+    n += (long)w * m;
+  }
+  return n;
+}
+// workgroups that run at once on num_cus CUs
+template <typename T>
+int pair_w_slots(int n, int num_cus);
+// n: cubic grid length, {16, 20, 24, 32} in FP32, {16, 20, 24} in FP64
+template <typename T>
+hipError_t launch_pair_w(int n, const PairArgs<T>& a, int num_cus, hipStream_t st);
+
+// The sums over one block. out: the targets' sums; mir (NULL: one-sided): the sources' sums
+// of F_t conj(W), unscaled, over the pairs of different tiles when tri.
+template <typename T>
+struct WsumArgs {
+  const cx<T>* W;
+  const cx<T>* M;   // [sources][nr]
+  const cx<T>* F;   // [targets][nr]
+  c128* out;        // [targets][nr]
+  cx<float>* comp;  // FP32: compensation of out between the blocks of one target
+  c128* run;        // FP64: the unscaled sum between the blocks of one target
+  c128* mir;        // [groups of the row][nsrc][nr]
+  cx<float>* mcomp; // FP32: compensation of mir
+  int t0, nt, j0, nj, ns, tri;
+  int nsrc;         // all sources
+  int jb0;          // band index of source j0 within its k-point
+  int nr;
+  int first, last;  // first / last block of these targets
+  int mfirst;       // first block of these sources' mirror sums
+  int accumulate;   // add to the existing out
+  double scale;
+};
+template <typename T>
+hipError_t launch_wsum(const WsumArgs<T>& a, hipStream_t st);
+// dst = (accumulate ? dst : 0) + scale * sum over the groups of (mir + mcomp); mcomp may be NULL
+hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double scale, int accumulate, int nsrc,
+                             int nr, int rows, int tri, hipStream_t st);
+
+}  // namespace fockmi

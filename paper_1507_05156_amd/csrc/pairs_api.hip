@@ -1,0 +1,136 @@
+// Host side of the two-stage pair form (pairs.hip): blocks of pairs, buffers, launches.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "../../include/fockmi.h"
+#include "pairs.hpp"
+#include "plan.hpp"
+
+using namespace fockmi;
+
+namespace fockmi {
+
+extern thread_local std::string g_last_error;
+
+// Targets of one row of blocks. Stage 2 runs nr/64 waves per target tile, and a grid of
+// about 8,192 waves fills the 256 CUs twice over; two-sided blocks take multiples of 64
+// targets, whose mirror sums meet in one workgroup. At 32^3 that is 128 targets; with the
+// 8 GiB batch a block then runs 16,384 to 32,768 pairs, so that its last round costs under 2%
+// (32^3 / 216 k / 16 bands: 1,159 ms with batches of 512 MiB, 1,110 with 4 GiB, 1,088 with 8).
+static int row_targets(int nt, int nr, size_t field_bytes, size_t budget, bool tri) {
+  long want = std::max<long>(64, ((1L << 22) / nr + 63) / 64 * 64);
+  if (tri) {
+    while (want > 64 && (size_t)want * want * field_bytes > budget) want -= 64;
+  } else {
+    // at least 16 sources (one FP32 partial sum) per block
+    while (want > kPairTile && (size_t)want * 16 * field_bytes > budget) want -= want > 64 ? 64 : kPairTile;
+  }
+  return (int)std::min<long>(want, nt);
+}
+
+bool Plan::pairs_tri_fits(int nt, int nr, size_t field_bytes) const {
+  const size_t b = std::min<size_t>(nt, 64);
+  return !workspace_cap || (b * b * field_bytes <= workspace_cap && (size_t)nt * nr * sizeof(c128) <= workspace_cap);
+}
+
+template <typename T>
+fock_status Plan::run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P, const cx<T>* M,
+                            int ns, c128* out, double scale, bool accumulate, const T* Kt, const Mirror<T>& mr,
+                            hipStream_t st) {
+  constexpr bool F32 = sizeof(T) == 4;
+  const int nr = c.nr, nt = ps.ntk * nx, nj = ps.nsk * ns;
+  const size_t fb = (size_t)nr * sizeof(cx<T>);
+  const bool two = mr.dst != nullptr;
+  size_t budget = workspace_cap ? std::min(workspace_cap, pair_batch) : pair_batch;
+  fock_status s;
+  hipError_t e;
+  int rows = 0;
+  long njmax = 0;
+  for (;;) {
+    rows = row_targets(nt, nr, fb, budget, mr.tri);
+    njmax = std::max<long>(std::min<long>((long)(budget / ((size_t)rows * fb)), nj), mr.tri ? rows : 1);
+    if (!F32 || two) njmax = std::max<long>(njmax, 1);
+    else njmax = std::max<long>(njmax, std::min(16, ns));
+    s = pbatch.ensure((size_t)rows * njmax * fb, workspace_cap, "pair batch");
+    if (s == FOCK_OK) break;
+    if (budget <= (size_t(64) << 20)) return s;
+    budget /= 2;
+  }
+  if ((s = prun.ensure((size_t)rows * nr * (F32 ? sizeof(c64) : sizeof(c128)), workspace_cap, "pair sums")) != FOCK_OK)
+    return s;
+  const int groups = (rows + kPairGroup - 1) / kPairGroup;
+  if (two) {
+    if ((s = pmir.ensure((size_t)groups * nj * nr * sizeof(c128), workspace_cap, "mirror sums")) != FOCK_OK) return s;
+    if (F32 && (s = pmcomp.ensure((size_t)groups * nj * nr * sizeof(c64), workspace_cap, "mirror compensation")) != FOCK_OK)
+      return s;
+  }
+  PairArgs<T> pa{};
+  pa.X = X;
+  pa.P = P;
+  pa.Kt = Kt;
+  pa.qidx = ps.qidx;
+  pa.W = (cx<T>*)pbatch.ptr;
+  pa.nx = nx;
+  pa.ns = ns;
+  pa.nsk = ps.nsk;
+  WsumArgs<T> wa{};
+  wa.W = pa.W;
+  wa.M = M;
+  wa.F = mr.F;
+  wa.out = out;
+  wa.mir = two ? (c128*)pmir.ptr : nullptr;
+  wa.mcomp = two && F32 ? (c64*)pmcomp.ptr : nullptr;
+  wa.ns = ns;
+  wa.nsrc = nj;
+  wa.nr = nr;
+  wa.accumulate = accumulate ? 1 : 0;
+  wa.scale = scale;
+  auto block = [&](int t0, int ntb, int j0, int njb, bool tri, bool first, bool last, bool mfirst) -> fock_status {
+    pa.t0 = wa.t0 = t0;
+    pa.nt = wa.nt = ntb;
+    pa.j0 = wa.j0 = j0;
+    pa.nj = wa.nj = njb;
+    pa.tri = wa.tri = tri ? 1 : 0;
+    pa.npairs = pair_count(ntb, njb, tri);
+    wa.jb0 = j0 % ns;
+    wa.first = first ? 1 : 0;
+    wa.last = last ? 1 : 0;
+    wa.mfirst = mfirst ? 1 : 0;
+    // the sums kept between the blocks of a row, indexed by target
+    wa.comp = F32 ? (c64*)prun.ptr - (long)t0 * nr : nullptr;
+    wa.run = F32 ? nullptr : (c128*)prun.ptr - (long)t0 * nr;
+    if ((e = launch_pair_w<T>(c.geom.n1, pa, num_cus, st)) != hipSuccess) return hip_fail(e, "pair kernel");
+    if ((e = launch_wsum<T>(wa, st)) != hipSuccess) return hip_fail(e, "pair sums");
+    return FOCK_OK;
+  };
+  for (int t0 = 0; t0 < nt; t0 += rows) {
+    const int ntb = std::min(rows, nt - t0);
+    const int jend = mr.tri ? t0 : nj;
+    for (int j0 = 0; j0 < jend;) {
+      int j1 = (int)std::min<long>(jend, j0 + njmax);
+      if (F32 && !two && j1 < jend) {
+        // whole FP32 partial sums per block: a target's sum does not depend on the blocks
+        const int b = j1 % ns;
+        j1 -= b % 16;
+        if (j1 <= j0) j1 = j0 + std::min(16, ns - j0 % ns);
+      }
+      const bool first = j0 == 0, last = !mr.tri && j1 == jend;
+      if ((s = block(t0, ntb, j0, j1 - j0, false, first, last, !mr.tri && t0 == 0)) != FOCK_OK) return s;
+      j0 = j1;
+    }
+    if (mr.tri && (s = block(t0, ntb, t0, ntb, true, t0 == 0, true, true)) != FOCK_OK) return s;
+  }
+  if (two && (e = launch_mirror_add(mr.dst, (const c128*)pmir.ptr, wa.mcomp, mr.scale, mr.accumulate ? 1 : 0,
+                                    nj, nr, rows, mr.tri ? 1 : 0, st)) != hipSuccess)
+    return hip_fail(e, "mirror sums");
+  return FOCK_OK;
+}
+
+template fock_status Plan::run_pairs<float>(const Cell&, const PairSet&, const c64*, int, const c64*, const c64*, int,
+                                            c128*, double, bool, const float*, const Mirror<float>&, hipStream_t);
+template fock_status Plan::run_pairs<double>(const Cell&, const PairSet&, const c128*, int, const c128*, const c128*,
+                                             int, c128*, double, bool, const double*, const Mirror<double>&,
+                                             hipStream_t);
+
+}  // namespace fockmi

@@ -94,6 +94,18 @@ struct BatchState {
   void release();
 };
 
+// The mirror side of a two-sided pair sum: dst[j] = (accumulate ? dst[j] : 0) + scale *
+// sum_i F_i conj(W_ji) over the targets i. dst NULL: one-sided. tri: the targets are the
+// sources, every pair of fields is transformed once and the mirror adds the other half.
+template <typename T>
+struct Mirror {
+  const cx<T>* F = nullptr;
+  c128* dst = nullptr;
+  double scale = 0.0;
+  bool accumulate = false;
+  bool tri = false;
+};
+
 // work arrays of the block eigensolver (eig_api.hip)
 struct EigState {
   DevBuf x, hx, w, hw, p, hp, xn, hxn, pn, hpn;  // [nk][nb][N_r] blocks and their images under h
@@ -124,6 +136,11 @@ struct Plan {
   int sym_key[4] = {-1, -1, -1, -1};
   int split_stagger_shift = 1;              // the bands' order of the symmetric form (FOCKMI_SPLIT_STAGGER_SHIFT)
   int split_sym = 1;                        // 0: the split form runs every pair (FOCKMI_SPLIT_SYM=0)
+  // two-stage pair form (pairs_api.hip): the batch of W fields, the sums kept between the
+  // blocks of a row, the mirror sums and their compensation
+  DevBuf pbatch, prun, pmir, pmcomp;
+  size_t pair_batch = size_t(8) << 30;      // bytes of one batch
+  int split_form = 0;                       // 1: a split-form variable is set, 32^3 runs the split form
   std::vector<double> host_norms;
   double* host_pinned = nullptr;            // 4 doubles for reductions
   bool profiling = false;
@@ -157,6 +174,13 @@ struct Plan {
                         c128* out, double scale, bool accumulate, hipStream_t st);
   fock_status run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx, const c128* P, const c128* M,
                           int ns, c128* out, double scale, bool accumulate, hipStream_t st);
+  // the same sum in the two-stage pair form; Kt: tables in the pair kernel's order
+  template <typename T>
+  fock_status run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P, const cx<T>* M,
+                        int ns, c128* out, double scale, bool accumulate, const T* Kt, const Mirror<T>& mr,
+                        hipStream_t st);
+  // whether the batch and mirror sums of a symmetric sum over nt fields fit the workspace cap
+  bool pairs_tri_fits(int nt, int nr, size_t field_bytes) const;
   // the orbitals of the source k-points, contiguous: `arr` itself without
   // down-sampling, else a copy of its S blocks ([nsrc][nper][nr]) in buf
   fock_status sources(Cell& c, const c128* arr, int nper, DevBuf& buf, hipStream_t st, const c128** out);
