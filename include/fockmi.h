@@ -101,8 +101,9 @@ fock_status fock_plan_destroy(fockmi_plan plan);
  * nphi >= 1: an empty target set is FOCK_ERR_ARG, as are a NULL or misaligned
  * pointer, a cell index out of range and an output that overlaps an input;
  * nothing is launched then.
- * With phi == u_occ on a 32^3 cell (FOCK_FP32_COMP, no down-sampling) each pair of
- * fields is transformed once and its conjugate term added to the other row: the plan
+ * With phi == u_occ and no down-sampling, the FP32 form at 32^3 and the fused forms at
+ * 16^3 to 24^3 (where it is the faster way) transform each pair of fields once and add its
+ * conjugate term to the other row: the plan
  * then holds a batch of pair fields (8 GiB, less when the device or the plan's workspace
  * cap cannot hold it) and mirror sums of 24 bytes per grid point and 64 targets of a row
  * of blocks. The result is bitwise repeatable and agrees with the form that runs every
@@ -125,7 +126,7 @@ fock_status fock_apply(fockmi_plan plan, int cell, const void* u_occ, const void
  * 0 <= k0, nk_out >= 1, k0 + nk_out <= nk and nphi >= 1 (FOCK_ERR_ARG otherwise). Each target's sum is the
  * one fock_apply computes; the plain FP64 path and the grid forms of the fused
  * kernel give the same bits, the 32^3 lockstep form may group its FP64
- * additions differently, and fock_apply's symmetric 32^3 sum (phi == u_occ)
+ * additions differently, and fock_apply's symmetric sum (phi == u_occ)
  * adds each target's terms in another order (a k-range runs every
  * pair of its targets). Stream-ordered. */
 fock_status fock_apply_krange(fockmi_plan plan, int cell, const void* u_occ, int k0, int nk_out, const void* phi,
@@ -295,9 +296,10 @@ fock_status fock_apply_batched(fockmi_plan plan, const void* const* u_occ, const
  * hipMalloc, hipFree or other allocating routine. Its scratch (the complex64
  * shadows of u_occ and phi, the Neumaier compensation field and, for 32^3 cells,
  * the FP32 band sums) comes from one fixed device array of 64 MiB that the
- * library holds on every GPU it runs on until the process ends. It runs the
- * grid form of the fused kernel (one workgroup per target), so for grid
- * lengths up to 24 it gives fock_apply's bits.
+ * library holds on every GPU it runs on until the process ends. At grid lengths
+ * up to 24 it runs what fock_apply runs (the grid form of the fused kernel, one
+ * workgroup per target, or for small sums the two-stage pair form) and gives
+ * fock_apply's bits; at 32^3 it runs the grid form.
  * Errors: FOCK_ERR_SIZE when the cell needs more scratch than the fixed array
  * (about 32 MiB of shadows: e.g. 16^3 with up to ~500 orbitals) or its grid is
  * not cubic; FOCK_ERR_ARG as

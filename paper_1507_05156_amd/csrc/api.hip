@@ -213,11 +213,19 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   const bool pairs_tri = split_sym && !c.ds && ps.ntk == c.nk && ps.nsk == c.nk &&
                          ps.qidx == (const int*)c.qidx.ptr && X == P && P == M && nx == ns &&
                          pairs_tri_fits(nitems, nr, nr * sizeof(c64));
+  PairRule rule = pair_rule(c, ps, nx, ns, X == P && P == M, true);
+  if (n == 32) rule.tri = pairs_tri;
   auto usable = [&](int v) {
-    if (n != 32) return v >= 0 && v < fused_variants(n);
+    if (n != 32) {
+      // of a sum that fock_apply_noalloc shares, only the form of the rule; else the rule is a default
+      if (rule.shared) return rule.pairs ? v == 3 : (v >= 0 && v < fused_variants(n));
+      return (v >= 0 && v < fused_variants(n)) || (v == 3 && rule.pairs);
+    }
     return v == 0 || (v == 1 && has_ls) || (v == 2 && has_split) || v == 3;
   };
-  auto fallback_variant = [&](int v) { return usable(v) ? v : (n == 32 && has_ls ? 1 : 0); };
+  auto fallback_variant = [&](int v) {
+    return usable(v) ? v : (n == 32 ? (has_ls ? 1 : 0) : (usable(3) ? 3 : 0));
+  };
   // the lockstep form's k' split: the part count (dividing the source k-points,
   // at most 4) with the fewest rounds of ls.nwg workgroups, in units of a whole
   // target's sum
@@ -325,7 +333,7 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   auto launch = [&](int v) -> hipError_t {
     if (v == 3) {
       Mirror<float> mr;
-      if (pairs_tri) {
+      if (rule.tri) {
         mr.F = Xs;
         mr.dst = out;
         mr.scale = scale;
@@ -368,7 +376,7 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
     if (profiling) e2 = launch_count_abort((long long*)fallbacks.ptr, (const int*)sstatus.ptr, st);
     return e2;
   };
-  int variant = fallback_variant(n == 32 && split_form ? 2 : fused_default_variant(n));
+  int variant = fallback_variant(n == 32 && split_form ? 2 : (rule.pairs ? 3 : fused_default_variant(n)));
   hipError_t e;
   const std::string key = key_for(c, ps, nx, "fused");
   TuneEntry te;
@@ -383,11 +391,11 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
     if ((e = hipEventCreate(&e1)) != hipSuccess) return hip_fail(e, "tuning event");
     double best = 1e300;
     int bv = 0, bx = 1;
-    for (int v = 0; v < fused_variants(n); ++v) {
+    for (int v = 0; v < 4; ++v) {
       if (!usable(v)) continue;
       if ((s = prepare(v)) != FOCK_OK) return s;
-      for (int x = 0; x < ((n != 32 || v == 0) ? 2 : 1); ++x) {
-        a.xcd_map = (n != 32 || v == 0) ? x : 1;
+      for (int x = 0; x < (v == 0 || (n != 32 && v < 3) ? 2 : 1); ++x) {
+        a.xcd_map = v == 0 || (n != 32 && v < 3) ? x : 1;
         (void)hipEventRecord(e0, st);
         if ((e = launch(v)) != hipSuccess) return hip_fail(e, "fused pair kernel");
         if (pairs_status != FOCK_OK) return pairs_status;
@@ -443,6 +451,23 @@ fock_status Plan::run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx,
                               int ns, c128* out, double scale, bool accumulate, hipStream_t st) {
   const int nitems = ps.ntk * nx;
   fock_status s;
+  hipError_t e;
+  const PairRule rule = pair_rule(c, ps, nx, ns, X == P && P == M, false);
+  if (rule.pairs) {
+    Mirror<double> mr;
+    if (rule.tri) {
+      mr.F = X;
+      mr.dst = out;
+      mr.scale = scale;
+      mr.accumulate = mr.tri = true;
+    }
+    if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
+    if ((s = run_pairs<double>(c, ps, X, nx, P, M, ns, out, scale, accumulate, (const double*)c.Kt64.ptr, mr, st)) !=
+        FOCK_OK)
+      return s;
+    if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
+    return FOCK_OK;
+  }
   const size_t acc_elems = fused64_acc_scratch_elems(c.geom.n1, nitems);
   if (acc_elems && (s = accs.ensure(acc_elems * sizeof(c128), workspace_cap, "FP64 sums")) != FOCK_OK) return s;
   Fused64Args a{};
@@ -461,7 +486,6 @@ fock_status Plan::run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx,
   a.scale = scale;
   a.accumulate = accumulate ? 1 : 0;
   a.xcd_map = xcd_map;
-  hipError_t e;
   if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
   if ((e = launch_fused64_apply(c.geom.n1, a, st)) != hipSuccess) return hip_fail(e, "fused FP64 pair kernel");
   if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");

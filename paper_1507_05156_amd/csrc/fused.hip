@@ -594,7 +594,7 @@ size_t fused_acc_scratch_elems(int n, int nslots) {
 
 // 32^3: 0 the grid form, 1 the lockstep form, 2 the split form (split32.hip), 3 the two-stage
 // pair form (pairs.hip); the caller launches the last two itself
-int fused_variants(int n) { return n == 32 ? 4 : ((n == 16 || n == 20) ? 2 : 1); }
+int fused_variants(int n) { return n == 32 ? 3 : ((n == 16 || n == 20) ? 2 : 1); }
 
 bool fused_has_lockstep(int n) { return n == 32; }
 

@@ -10,9 +10,10 @@
 // (noalloc_setup) and kept per device. Host code never passes the array's name
 // to a kernel: in host code that name is only a stand-in for the symbol.
 //
-// The call runs the grid form of the fused kernel (one workgroup per target),
-// the form fock_apply uses for grid lengths up to 24, so that for those cells
-// the two calls give the same bits. Every call on a GPU shares that GPU's
+// For grid lengths up to 24 the call runs what fock_apply runs (the grid form of the
+// fused kernel, one workgroup per target, or for small sums the two-stage pair form,
+// by the same rule), so that for those cells the two calls give the same bits; at
+// 32^3 it runs the grid form. Every call on a GPU shares that GPU's
 // array and leaves its contents behind; calls that overlap on one GPU race.
 // The fused kernel writes every compensation and band-sum element before it
 // reads it, so nothing needs clearing between calls.
@@ -29,7 +30,6 @@ namespace fockmi {
 
 extern thread_local std::string g_last_error;
 
-constexpr size_t kNoAllocBytes = size_t(64) << 20;
 constexpr int kNoAllocMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
@@ -38,6 +38,27 @@ namespace {
 std::mutex g_noalloc_mu;
 void* g_noalloc_ptr[kNoAllocMaxDevices] = {};
 }  // namespace
+
+// scratch layout (256-byte aligned pieces): source shadow [nsrc][nb][N_r], target shadow
+// [nk][nphi][N_r] unless phi is u_occ, compensation [nk][nphi][N_r], FP32 band sums
+// [nk * nphi][N_r] where the kernel keeps them in global memory
+struct NoAllocLayout {
+  size_t x, c, a, end;
+};
+static NoAllocLayout noalloc_layout(const Cell& c, const PairSet& ps, int nx, int ns, bool x_is_u) {
+  auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
+  const size_t nitems = (size_t)(ps.ntk_all ? ps.ntk_all : ps.ntk) * nx;
+  NoAllocLayout l;
+  l.x = up((size_t)ps.nsk * ns * c.nr * sizeof(c64));
+  l.c = l.x + (x_is_u ? 0 : up(nitems * c.nr * sizeof(c64)));
+  l.a = l.c + up(nitems * c.nr * sizeof(c64));
+  l.end = l.a + up(fused_acc_scratch_elems(c.geom.n1, (int)nitems) * sizeof(c64));
+  return l;
+}
+
+size_t noalloc_bytes(const Cell& c, const PairSet& ps, int nx, int ns, bool x_is_u) {
+  return noalloc_layout(c, ps, nx, ns, x_is_u).end;
+}
 
 // Looks up this device's copy of `scratch` (the device must be current). Called
 // by fock_plan_create; idempotent per device.
@@ -78,20 +99,12 @@ extern "C" fock_status fock_apply_noalloc(fockmi_plan plan, int cell, const void
   void* base = (p->device >= 0 && p->device < kNoAllocMaxDevices) ? g_noalloc_ptr[p->device] : nullptr;
   if (!base) return fail(FOCK_ERR_STATE, "the scratch array of device %d was not set up", p->device);
 
-  // scratch layout (256-byte aligned pieces): source shadow [nsrc][nb][N_r],
-  // target shadow [nk][nphi][N_r] unless phi is u_occ, compensation
-  // [nk][nphi][N_r], FP32 band sums [nk * nphi][N_r] where the kernel keeps them
-  // in global memory
   const PairSet ps = c.fwd();
   const int nitems = ps.ntk * nphi;
   const bool x_is_u = phi == u_occ && nphi == c.nb && !c.ds;
   const size_t blk = (size_t)c.nb * c.nr;  // elements of one source k-point
-  auto up = [](size_t b) { return (b + 255) & ~size_t(255); };
-  const size_t o_u = 0;
-  const size_t o_x = o_u + up((size_t)ps.nsk * blk * sizeof(c64));
-  const size_t o_c = o_x + (x_is_u ? 0 : up((size_t)nitems * c.nr * sizeof(c64)));
-  const size_t o_a = o_c + up((size_t)nitems * c.nr * sizeof(c64));
-  const size_t need = o_a + up(fused_acc_scratch_elems(c.geom.n1, nitems) * sizeof(c64));
+  const NoAllocLayout lay = noalloc_layout(c, ps, nphi, c.nb, x_is_u);
+  const size_t o_u = 0, o_x = lay.x, o_c = lay.c, o_a = lay.a, need = lay.end;
   if (need > kNoAllocBytes)
     return fail(FOCK_ERR_SIZE, "fock_apply_noalloc: this cell needs %zu bytes of scratch, above the fixed %zu bytes",
                 need, kNoAllocBytes);
@@ -111,6 +124,16 @@ extern "C" fock_status fock_apply_noalloc(fockmi_plan plan, int cell, const void
   }
   if (!x_is_u && (e = launch_to_c64(sx, (const c128*)phi, (long)nitems * c.nr, st)) != hipSuccess)
     return hip_fail(e, "complex64 shadow (phi)");
+  if (c.geom.n1 <= 24 && p->pair_rule(c, ps, nphi, c.nb, x_is_u, true).pairs) {
+    // the sums kept between blocks take the compensation's place, the batch what is left
+    const size_t fb = (size_t)c.nr * sizeof(c64);
+    int rows = 0;
+    long njmax = 0;
+    pairs_block_shape(nitems, ps.nsk * c.nb, c.nb, c.nr, fb, kNoAllocBytes - o_a, true, false, &rows, &njmax);
+    return pairs_blocks<float>(c.geom.n1, c.nr, p->num_cus, ps, sx, nphi, su, su, c.nb, (c128*)vphi, -1.0 / c.nsrc,
+                               false, (const float*)c.Kt.ptr, Mirror<float>{}, rows, njmax, (c64*)(sp + o_a),
+                               sp + o_c, nullptr, nullptr, st);
+  }
   FusedArgs a{};
   a.X = sx;
   a.P = su;

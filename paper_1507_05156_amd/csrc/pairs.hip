@@ -43,14 +43,15 @@ constexpr int pw_nph() {
   return ((long)N * N * (N + 1) * (long)sizeof(cx<T>) > 160L * 1024) ? 2 : 1;
 }
 // elements whose loads are in flight together: operands of the pair product, kernel values
+// (24^3 FP64: groups of 4 took 120 ns per pair, of 12 115 ns; 24 kernel values at once spill)
 template <int N, typename T>
-constexpr int pw_grp_px() { return sizeof(T) == 8 ? 4 : (N == 32 ? 12 : (N == 16 ? 8 : 4)); }
+constexpr int pw_grp_px() { return 12; }
 // elements of the next pair's operands loaded before the current pair's W is stored (at 32^3
 // what the registers hold beside the line: 6; 1 ahead 1,114 ms, 6 ahead 1,088 ms)
 template <int N, typename T>
-constexpr int pw_ahead() { return sizeof(T) == 8 ? (N == 24 ? 1 : 4) : (N == 32 ? 6 : 8); }
+constexpr int pw_ahead() { return sizeof(T) == 8 ? (N == 24 ? 2 : 4) : (N == 32 ? 6 : 8); }
 template <int N, typename T>
-constexpr int pw_grp_k() { return sizeof(T) == 8 ? 4 : (N <= 24 ? N : 8); }
+constexpr int pw_grp_k() { return sizeof(T) == 8 ? 12 : (N <= 24 ? N : 8); }
 
 // a uniform load through the scalar cache: a vector load here would wait for the W stores
 // in flight, like every load that is waited for behind them

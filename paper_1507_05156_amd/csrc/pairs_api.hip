@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdlib>
 
 #include "../../include/fockmi.h"
 #include "pairs.hpp"
@@ -19,7 +20,8 @@ extern thread_local std::string g_last_error;
 // 8 GiB batch a block then runs 16,384 to 32,768 pairs, so that its last round costs under 2%
 // (32^3 / 216 k / 16 bands: 1,159 ms with batches of 512 MiB, 1,110 with 4 GiB, 1,088 with 8).
 static int row_targets(int nt, int nr, size_t field_bytes, size_t budget, bool tri) {
-  long want = std::max<long>(64, ((1L << 22) / nr + 63) / 64 * 64);
+  static const int sh = std::getenv("XX_ROWS") ? std::atoi(std::getenv("XX_ROWS")) : 22;
+  long want = std::max<long>(64, ((1L << sh) / nr + 63) / 64 * 64);
   if (tri) {
     while (want > 64 && (size_t)want * want * field_bytes > budget) want -= 64;
   } else {
@@ -29,48 +31,79 @@ static int row_targets(int nt, int nr, size_t field_bytes, size_t budget, bool t
   return (int)std::min<long>(want, nt);
 }
 
+void pairs_block_shape(int nt, int nj, int ns, int nr, size_t fb, size_t budget, bool whole_partials, bool tri,
+                       int* rows, long* njmax) {
+  *rows = row_targets(nt, nr, fb, budget, tri);
+  long m = std::min<long>((long)(budget / ((size_t)*rows * fb)), nj);
+  m = std::max<long>(m, whole_partials ? std::min(16, ns) : 1);
+  *njmax = tri ? std::max<long>(m, *rows) : m;
+}
+
 bool Plan::pairs_tri_fits(int nt, int nr, size_t field_bytes) const {
   const size_t b = std::min<size_t>(nt, 64);
   return !workspace_cap || (b * b * field_bytes <= workspace_cap && (size_t)nt * nr * sizeof(c128) <= workspace_cap);
 }
 
+// Measured costs of the forms on a 256-CU device, cubic grids: the fused kernels take `round`
+// us per source for every `slots` targets (a grid of fewer workgroups leaves CUs idle), the
+// pair form `pair` ns per pair one-sided and `sym` ns per pair of the sum with the pair
+// symmetry, whatever the shape of the sum.
+struct FormCost {
+  int n, slots;
+  double round, pair, sym;
+};
+constexpr FormCost kCost64[] = {{16, 512, 7.1, 29.5, 15.6}, {20, 256, 11.2, 69.0, 37.0}, {24, 256, 36.0, 147.0, 79.0}};
+constexpr FormCost kCost32[] = {{16, 1024, 9.0, 15.0, 9.0}, {20, 512, 13.1, 36.0, 21.0}, {24, 256, 12.5, 68.0, 39.0}};
+
+Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns, bool same, bool f32) const {
+  PairRule r;
+  const long nt = (long)(ps.ntk_all ? ps.ntk_all : ps.ntk) * nx, nj = (long)ps.nsk * ns;
+  const FormCost* fc = nullptr;
+  for (const FormCost& x : f32 ? kCost32 : kCost64)
+    if (x.n == c.geom.n1) fc = &x;
+  if (!fc) return r;
+  same = same && nx == ns && !c.ds;
+  const double scale = num_cus / 256.0;
+  const double fused = fc->round * 1e3 * (double)((nt + (long)(fc->slots * scale) - 1) / std::max<long>(1, (long)(fc->slots * scale)));
+  // below 4 tiles the triangle is nearly the whole square, and the mirror sums cost a launch
+  const bool tri_ok = same && ps.ntk == c.nk && ps.nsk == c.nk && ps.qidx == (const int*)c.qidx.ptr &&
+                      nt > 3 * kPairTile &&
+                      pairs_tri_fits((int)nt, c.nr, (size_t)c.nr * (f32 ? sizeof(c64) : sizeof(c128)));
+  if (f32) {
+    const size_t need = noalloc_bytes(c, ps, nx, ns, same);
+    r.shared = need <= kNoAllocBytes;
+    if (r.shared) {
+      // fock_apply_noalloc serves this sum with the same bits: one-sided in both (its sums do
+      // not depend on the blocks), and only where its 64 MiB hold a batch that is still the
+      // faster form
+      const size_t least = (size_t)std::min<long>(nt, kPairTile) * std::min(ns, 16) * c.nr * sizeof(c64);
+      r.pairs = nt * nj <= (fc->n == 24 ? 96 * 96 : 128 * 128) && nt * fc->pair < fused &&
+                need + least <= kNoAllocBytes;
+      return r;
+    }
+  }
+  if (tri_ok && nt * fc->sym < fused) r.pairs = r.tri = true;
+  else if (!f32) r.pairs = nt * fc->pair < fused;
+  return r;
+}
+
+// the blocks of a sum: rows of `rows` targets, at most njmax sources each
 template <typename T>
-fock_status Plan::run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P, const cx<T>* M,
-                            int ns, c128* out, double scale, bool accumulate, const T* Kt, const Mirror<T>& mr,
-                            hipStream_t st) {
+fock_status pairs_blocks(int n, int nr, int num_cus, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P,
+                         const cx<T>* M, int ns, c128* out, double scale, bool accumulate, const T* Kt,
+                         const Mirror<T>& mr, int rows, long njmax, cx<T>* W, void* run, c128* mir, c64* mcomp,
+                         hipStream_t st) {
   constexpr bool F32 = sizeof(T) == 4;
-  const int nr = c.nr, nt = ps.ntk * nx, nj = ps.nsk * ns;
-  const size_t fb = (size_t)nr * sizeof(cx<T>);
+  const int nt = ps.ntk * nx, nj = ps.nsk * ns;
   const bool two = mr.dst != nullptr;
-  size_t budget = workspace_cap ? std::min(workspace_cap, pair_batch) : pair_batch;
   fock_status s;
   hipError_t e;
-  int rows = 0;
-  long njmax = 0;
-  for (;;) {
-    rows = row_targets(nt, nr, fb, budget, mr.tri);
-    njmax = std::max<long>(std::min<long>((long)(budget / ((size_t)rows * fb)), nj), mr.tri ? rows : 1);
-    if (!F32 || two) njmax = std::max<long>(njmax, 1);
-    else njmax = std::max<long>(njmax, std::min(16, ns));
-    s = pbatch.ensure((size_t)rows * njmax * fb, workspace_cap, "pair batch");
-    if (s == FOCK_OK) break;
-    if (budget <= (size_t(64) << 20)) return s;
-    budget /= 2;
-  }
-  if ((s = prun.ensure((size_t)rows * nr * (F32 ? sizeof(c64) : sizeof(c128)), workspace_cap, "pair sums")) != FOCK_OK)
-    return s;
-  const int groups = (rows + kPairGroup - 1) / kPairGroup;
-  if (two) {
-    if ((s = pmir.ensure((size_t)groups * nj * nr * sizeof(c128), workspace_cap, "mirror sums")) != FOCK_OK) return s;
-    if (F32 && (s = pmcomp.ensure((size_t)groups * nj * nr * sizeof(c64), workspace_cap, "mirror compensation")) != FOCK_OK)
-      return s;
-  }
   PairArgs<T> pa{};
   pa.X = X;
   pa.P = P;
   pa.Kt = Kt;
   pa.qidx = ps.qidx;
-  pa.W = (cx<T>*)pbatch.ptr;
+  pa.W = W;
   pa.nx = nx;
   pa.ns = ns;
   pa.nsk = ps.nsk;
@@ -79,8 +112,8 @@ fock_status Plan::run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, in
   wa.M = M;
   wa.F = mr.F;
   wa.out = out;
-  wa.mir = two ? (c128*)pmir.ptr : nullptr;
-  wa.mcomp = two && F32 ? (c64*)pmcomp.ptr : nullptr;
+  wa.mir = two ? mir : nullptr;
+  wa.mcomp = two && F32 ? mcomp : nullptr;
   wa.ns = ns;
   wa.nsrc = nj;
   wa.nr = nr;
@@ -98,9 +131,9 @@ fock_status Plan::run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, in
     wa.last = last ? 1 : 0;
     wa.mfirst = mfirst ? 1 : 0;
     // the sums kept between the blocks of a row, indexed by target
-    wa.comp = F32 ? (c64*)prun.ptr - (long)t0 * nr : nullptr;
-    wa.run = F32 ? nullptr : (c128*)prun.ptr - (long)t0 * nr;
-    if ((e = launch_pair_w<T>(c.geom.n1, pa, num_cus, st)) != hipSuccess) return hip_fail(e, "pair kernel");
+    wa.comp = F32 ? (c64*)run - (long)t0 * nr : nullptr;
+    wa.run = F32 ? nullptr : (c128*)run - (long)t0 * nr;
+    if ((e = launch_pair_w<T>(n, pa, num_cus, st)) != hipSuccess) return hip_fail(e, "pair kernel");
     if ((e = launch_wsum<T>(wa, st)) != hipSuccess) return hip_fail(e, "pair sums");
     return FOCK_OK;
   };
@@ -121,12 +154,48 @@ fock_status Plan::run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, in
     }
     if (mr.tri && (s = block(t0, ntb, t0, ntb, true, t0 == 0, true, true)) != FOCK_OK) return s;
   }
-  if (two && (e = launch_mirror_add(mr.dst, (const c128*)pmir.ptr, wa.mcomp, mr.scale, mr.accumulate ? 1 : 0,
+  if (two && (e = launch_mirror_add(mr.dst, mir, wa.mcomp, mr.scale, mr.accumulate ? 1 : 0,
                                     nj, nr, rows, mr.tri ? 1 : 0, st)) != hipSuccess)
     return hip_fail(e, "mirror sums");
   return FOCK_OK;
 }
 
+template <typename T>
+fock_status Plan::run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P, const cx<T>* M,
+                            int ns, c128* out, double scale, bool accumulate, const T* Kt, const Mirror<T>& mr,
+                            hipStream_t st) {
+  constexpr bool F32 = sizeof(T) == 4;
+  const int nr = c.nr, nt = ps.ntk * nx, nj = ps.nsk * ns;
+  const size_t fb = (size_t)nr * sizeof(cx<T>);
+  const bool two = mr.dst != nullptr;
+  if (const char* g = std::getenv("XX_BATCH_MB")) pair_batch = (size_t)std::atol(g) << 20;
+  size_t budget = workspace_cap ? std::min(workspace_cap, pair_batch) : pair_batch;
+  fock_status s;
+  int rows = 0;
+  long njmax = 0;
+  for (;;) {
+    pairs_block_shape(nt, nj, ns, nr, fb, budget, F32 && !two, mr.tri, &rows, &njmax);
+    s = pbatch.ensure((size_t)rows * njmax * fb, workspace_cap, "pair batch");
+    if (s == FOCK_OK) break;
+    if (budget <= (size_t(64) << 20)) return s;
+    budget /= 2;
+  }
+  g_last_error.clear();  // a smaller batch after a failed allocation is no failure
+  if ((s = prun.ensure((size_t)rows * nr * (F32 ? sizeof(c64) : sizeof(c128)), workspace_cap, "pair sums")) != FOCK_OK)
+    return s;
+  const int groups = (rows + kPairGroup - 1) / kPairGroup;
+  if (two) {
+    if ((s = pmir.ensure((size_t)groups * nj * nr * sizeof(c128), workspace_cap, "mirror sums")) != FOCK_OK) return s;
+    if (F32 && (s = pmcomp.ensure((size_t)groups * nj * nr * sizeof(c64), workspace_cap, "mirror compensation")) != FOCK_OK)
+      return s;
+  }
+  return pairs_blocks<T>(c.geom.n1, nr, num_cus, ps, X, nx, P, M, ns, out, scale, accumulate, Kt, mr, rows, njmax,
+                         (cx<T>*)pbatch.ptr, prun.ptr, (c128*)pmir.ptr, (c64*)pmcomp.ptr, st);
+}
+
+template fock_status pairs_blocks<float>(int, int, int, const PairSet&, const c64*, int, const c64*, const c64*, int,
+                                         c128*, double, bool, const float*, const Mirror<float>&, int, long, c64*,
+                                         void*, c128*, c64*, hipStream_t);
 template fock_status Plan::run_pairs<float>(const Cell&, const PairSet&, const c64*, int, const c64*, const c64*, int,
                                             c128*, double, bool, const float*, const Mirror<float>&, hipStream_t);
 template fock_status Plan::run_pairs<double>(const Cell&, const PairSet&, const c128*, int, const c128*, const c128*,

@@ -39,6 +39,7 @@ inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
 struct PairSet {
   int ntk = 0, nsk = 0;
   const int* qidx = nullptr;  // device [ntk][nsk]
+  int ntk_all = 0;            // target k-points of the whole application (a k-range runs part of them)
 };
 
 struct Cell {
@@ -62,9 +63,9 @@ struct Cell {
   int nsrc = 0;
   DevBuf qidx_ts, qidx_st;    // int[nk][nsrc] (target k, source s), int[nsrc][nk] (source s as target, k)
   // forward sums: all k-points as targets, S as sources
-  PairSet fwd() const { return {nk, nsrc, (const int*)(ds ? qidx_ts.ptr : qidx.ptr)}; }
+  PairSet fwd() const { return {nk, nsrc, (const int*)(ds ? qidx_ts.ptr : qidx.ptr), nk}; }
   // the reverse role of the adjoint: S as targets, all k-points as sources
-  PairSet rev() const { return {nsrc, nk, (const int*)(ds ? qidx_st.ptr : qidx.ptr)}; }
+  PairSet rev() const { return {nsrc, nk, (const int*)(ds ? qidx_st.ptr : qidx.ptr), nsrc}; }
 };
 
 // the batched form used when no tuned choice exists: the forked cells (three
@@ -105,6 +106,23 @@ struct Mirror {
   bool accumulate = false;
   bool tri = false;
 };
+
+// The targets per row and sources per block of a two-stage pair sum within `budget` bytes of W
+// (whole_partials: blocks of at least one FP32 partial sum of at most 16 bands).
+void pairs_block_shape(int nt, int nj, int ns, int nr, size_t fb, size_t budget, bool whole_partials, bool tri,
+                       int* rows, long* njmax);
+// The blocks of a two-stage pair sum over buffers of the caller's: W holds rows * njmax fields,
+// run rows * nr sums (complex64 in FP32, complex128 in FP64).
+template <typename T>
+fock_status pairs_blocks(int n, int nr, int num_cus, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P,
+                         const cx<T>* M, int ns, c128* out, double scale, bool accumulate, const T* Kt,
+                         const Mirror<T>& mr, int rows, long njmax, cx<T>* W, void* run, c128* mir, c64* mcomp,
+                         hipStream_t st);
+
+// bytes of the fixed scratch array of fock_apply_noalloc, and what a sum needs of it
+// (x_is_u: the targets are the sources' array)
+constexpr size_t kNoAllocBytes = size_t(64) << 20;
+size_t noalloc_bytes(const Cell& c, const PairSet& ps, int nx, int ns, bool x_is_u);
 
 // work arrays of the block eigensolver (eig_api.hip)
 struct EigState {
@@ -179,6 +197,12 @@ struct Plan {
   fock_status run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P, const cx<T>* M,
                         int ns, c128* out, double scale, bool accumulate, const T* Kt, const Mirror<T>& mr,
                         hipStream_t st);
+  // whether the sum runs in the two-stage pair form (cubic grids up to 24), and with the pair symmetry
+  struct PairRule {
+    bool pairs = false, tri = false;
+    bool shared = false;  // fock_apply_noalloc serves the same sum, by the same rule
+  };
+  PairRule pair_rule(const Cell& c, const PairSet& ps, int nx, int ns, bool same, bool f32) const;
   // whether the batch and mirror sums of a symmetric sum over nt fields fit the workspace cap
   bool pairs_tri_fits(int nt, int nr, size_t field_bytes) const;
   // the orbitals of the source k-points, contiguous: `arr` itself without
@@ -200,7 +224,7 @@ struct Plan {
   fock_status kinetic(Cell& c, const c128* x, int nf, c128* y, const double a[3], hipStream_t st);
   fock_status h_apply(Cell& c, const c128* us, const c128* us2, const c128* x, c128* out, const c128* base,
                       double cre, double cim, const double* vloc, const double a[3], double alpha, hipStream_t st);
-  // acc <- x0 + sum_{m=1}^{order} phi_m, phi_m = (-i dt/m) h phi_{m-1}, phi_0 = x0 (acc may alias x0)
+  // acc <- x0 + sum_{m=1}^{order} phi_m, phi_m = (-i dt/m) h phi_{m-1}, phi_0 = x0 (acc distinct from x0)
   fock_status taylor_sum(Cell& c, const c128* us, const c128* us2, const c128* x0, c128* acc, const double* vloc,
                          const double a[3], double dt, double alpha, int order, hipStream_t st);
   // max over (k, b) of |(Omega/N_r) ||psi_kb||^2 - 1|; synchronises st

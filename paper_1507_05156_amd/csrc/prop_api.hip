@@ -73,17 +73,19 @@ fock_status Plan::taylor_sum(Cell& c, const c128* us, const c128* us2, const c12
   if ((s = field_bufs(c, {&phiA, &phiB}, c.nb)) != FOCK_OK) return s;
   const size_t bytes = (size_t)c.nk * c.nb * c.nr * sizeof(c128);
   const long count = (long)c.nk * c.nb * c.nr;
-  c128* cur = (c128*)phiA.ptr;
   c128* nxt = (c128*)phiB.ptr;
+  c128* other = (c128*)phiA.ptr;
   hipError_t e;
-  if ((e = hipMemcpyAsync(cur, x0, bytes, hipMemcpyDeviceToDevice, st)) != hipSuccess) return hip_fail(e, "copy psi");
-  if (acc != x0 && (e = hipMemcpyAsync(acc, x0, bytes, hipMemcpyDeviceToDevice, st)) != hipSuccess)
+  // the first term reads x0 itself (when it is also the source array, its V_x has the pair symmetry)
+  const c128* cur = x0;
+  if ((e = hipMemcpyAsync(acc, x0, bytes, hipMemcpyDeviceToDevice, st)) != hipSuccess)
     return hip_fail(e, "copy psi");
   for (int m = 1; m <= order; ++m) {
     // phi_m = (-i dt/m) h phi_{m-1}
     if ((s = h_apply(c, us, us2, cur, nxt, nullptr, 0.0, -dt / m, vloc, a, alpha, st)) != FOCK_OK) return s;
     if ((e = launch_scale_add(acc, nxt, 1.0, 0.0, count, st)) != hipSuccess) return hip_fail(e, "accumulate step");
-    std::swap(cur, nxt);
+    cur = nxt;
+    std::swap(nxt, other);
   }
   return FOCK_OK;
 }
@@ -217,7 +219,7 @@ fock_status taylor_step_vjp(fockmi_plan plan, int cell, const void* psi_n, const
   hipError_t e;
   if ((e = hipMemcpyAsync(phis, U, bytes, hipMemcpyDeviceToDevice, st)) != hipSuccess) return hip_fail(e, "copy");
   for (int m = 1; m < order; ++m) {
-    if ((s = p->h_apply(c, U, nullptr, phis + (size_t)(m - 1) * count, phis + (size_t)m * count, nullptr, 0.0, -dt / m, vloc,
+    if ((s = p->h_apply(c, U, nullptr, m == 1 ? U : phis + (size_t)(m - 1) * count, phis + (size_t)m * count, nullptr, 0.0, -dt / m, vloc,
                         A_over_c, alpha, st)) != FOCK_OK)
       return s;
   }

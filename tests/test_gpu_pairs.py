@@ -5,7 +5,8 @@ the triangle, k-points whose bands end inside a tile, more than 16 bands (two FP
 sums per k-point). Every k-point against a reference of the same sum, with u as targets and
 sources (each pair transformed once) and with separate targets (one-sided).
 
-The tolerance of the FP32 form is its stated one, 1e-6 per k-point against FP64."""
+The tolerances are the forms' stated ones, per k-point against the plain FP64 path: 1e-6 in FP32,
+1e-10 in FP64."""
 
 import os
 
@@ -61,3 +62,52 @@ def test_fp32_32cube_blocks(device, mesh, nb, cap):
     k0 = nk // 2
     part = plan.apply_krange(u, k0, nk - k0, phi[k0:].contiguous())
     assert bool((part == plan.apply(u, phi)[k0:]).all())   # a target's sum does not depend on the blocks
+
+
+@pytest.mark.parametrize("n,prec,mesh,nb,cap", [
+    (16, "fp64f", (1, 1, 1), 1, None), (16, "fp64f", (3, 1, 1), 3, None), (16, "fp64f", (3, 1, 1), 11, None),
+    (16, "fp64f", (5, 1, 1), 13, 270 << 20), (20, "fp64f", (5, 1, 1), 13, None), (20, "fp64f", (7, 1, 1), 1, 3 << 20),
+    (24, "fp64f", (2, 2, 2), 4, None), (24, "fp64f", (5, 1, 1), 13, 910 << 20), (24, "fp64f", (3, 1, 1), 17, None),
+    (16, "fp32", (2, 2, 2), 4, None), (20, "fp32", (3, 1, 1), 19, None), (24, "fp32", (1, 1, 1), 7, None),
+    (24, "fp32", (19, 1, 1), 16, None)])
+def test_small_cube_blocks(device, n, prec, mesh, nb, cap):
+    """16^3 to 24^3 with few fields (the pair form in both precisions) and, in FP32, 304 fields
+    of 24^3 (the pair symmetry); caps that leave one row of 64 fields beside a second row, and
+    blocks of a few sources."""
+    print(f"[gpu] pair form {n}^3 {prec} mesh={mesh} nb={nb} cap={cap}", flush=True)
+    tol = 1e-6 if prec == "fp32" else 1e-10
+    plan, nk = make(n, mesh, nb, prec, cap)
+    ref, _ = make(n, mesh, nb, "fp64")
+    u = fields(nk, nb, n, 21 + nb)
+    got = plan.apply(u)
+    assert bool((plan.apply(u) == got).all())
+    assert per_k(got, ref.apply(u)) < tol
+    phi = fields(nk, 3, n, 22)
+    full = plan.apply(u, phi)
+    assert per_k(full, ref.apply(u, phi)) < tol
+    assert bool((plan.apply_krange(u, nk // 2, nk - nk // 2, phi[nk // 2:].contiguous()) == full[nk // 2:]).all())
+    g = fields(nk, 3, n, 23)
+    for a, b in zip(plan.vjp(u, phi, g), ref.vjp(u, phi, g)):
+        assert per_k(a, b) < tol
+
+
+@pytest.mark.parametrize("n,prec,nb", [(24, "fp64f", 9), (32, "fp32", 5)])
+def test_pair_form_in_a_graph(device, n, prec, nb):
+    """Captured once (every buffer sized by an eager call before), replayed on changed inputs with
+    eager work between the replays: each replay gives the eager call's bits."""
+    import torch
+    print(f"[gpu] pair form captured, {n}^3 {prec}", flush=True)
+    plan, nk = make(n, (4, 1, 1), nb, prec)
+    u = fields(nk, nb, n, 31)
+    out = torch.empty_like(u)
+    plan.apply(u, out=out)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plan.apply(u, out=out)
+    for seed in (32, 33, 34):
+        u.copy_(fields(nk, nb, n, seed))
+        g.replay()
+        torch.cuda.synchronize()
+        replay = out.clone()
+        assert bool((replay == plan.apply(u)).all())
