@@ -50,16 +50,18 @@ typedef enum {
 } fock_status;
 
 typedef enum {
-  FOCK_FP64 = 0,         /* plain FP64 path: one stage per kernel through HBM */
+  FOCK_FP64 = 0,         /* FP64 throughout, in two stages through HBM: the pair fields W of a
+                            block of pairs, then the sums over them. Sums of many targets on
+                            cubic grids up to 24 run as in FOCK_FP64_FUSED */
   FOCK_FP32_COMP = 1,    /* fused pair kernel: complex64 pair FFTs; the sum over the bands j
                             of one k' in FP32 over at most 16 bands at a time, each such
                             partial sum added into an FP64 running sum with Neumaier
                             compensation, so the FP32 error does not grow with N_b.
-                            Cells whose grid is not cubic run the plain stages with
-                            complex64 pair products and FFTs and FP64 sums */
+                            Cells whose grid is not cubic run the two stages of
+                            FOCK_FP64 with complex64 pair products and FFTs and FP64 sums */
   FOCK_FP64_FUSED = 2    /* fused pair kernel in FP64 throughout (complex128 pair FFTs, one FP64
                             sum over all pairs) for cubic grids of length 16, 20 or 24; other
-                            cells of such a plan run the plain FP64 stages */
+                            cells of such a plan run the two stages of FOCK_FP64 */
 } fock_prec;
 
 typedef struct {
@@ -124,7 +126,7 @@ fock_status fock_apply(fockmi_plan plan, int cell, const void* u_occ, const void
  *   vphi  : device [nk_out][nphi][N_r] complex128 output, overwritten; must not overlap
  *           u_occ or phi
  * 0 <= k0, nk_out >= 1, k0 + nk_out <= nk and nphi >= 1 (FOCK_ERR_ARG otherwise). Each target's sum is the
- * one fock_apply computes; the plain FP64 path and the grid forms of the fused
+ * one fock_apply computes; the two-stage form without the symmetric sum and the grid forms of the fused
  * kernel give the same bits, the 32^3 lockstep form may group its FP64
  * additions differently, and fock_apply's symmetric sum (phi == u_occ)
  * adds each target's terms in another order (a k-range runs every
@@ -310,7 +312,7 @@ fock_status fock_apply_noalloc(fockmi_plan plan, int cell, const void* u_occ, co
                                void* vphi, void* stream);
 
 /* Diagnostics for measurement. While enabled, every launch of the fused pair
- * kernel (FOCK_FP32_COMP plans) and every batch of the plain path's pair
+ * kernel (FOCK_FP32_COMP plans) and every two-stage sum of the other plans'
  * pipeline (FOCK_FP64 plans) is bracketed by HIP events recorded on the
  * caller's stream. fock_profile_read synchronises those events and returns
  * the summed elapsed time (ms) and the number of bracketed launches; reset=1

@@ -31,9 +31,9 @@ class Plan:
     cells : list of dicts with keys n (int or 3-tuple), a (3x3 rows), kpts ([nk][3]),
             nb, omega, gs (default 2.0), and optionally src: the k indices of a
             down-sampled source sub-mesh (the pair sum runs over them with weight 1/len(src))
-    prec  : "fp64" (plain staged FP64 path), "fp32" (fused complex64 pair FFTs with
+    prec  : "fp64" (FP64 in two stages through HBM: pair fields, then sums), "fp32" (fused complex64 pair FFTs with
             compensated FP64 accumulation) or "fp64f" (fused kernel in FP64 throughout for
-            cubic grids of length 16, 20, 24; other cells take the plain path)
+            cubic grids of length 16, 20, 24; other cells run as in fp64)
     """
 
     def __init__(self, cells, prec="fp64", tune_cache=None):

@@ -76,28 +76,46 @@ fock_status Plan::check_ready(int cell) const {
 }
 
 // ------------------------------------------------------------------ plumbing
-template <typename T>
-static fock_status plain_pipeline(Plan& pl, Cell& c, const PairSet& ps, const c128* X, int nx, const c128* P,
-                                  const c128* M, int ns, c128* out, double scale, bool accumulate, hipStream_t st,
-                                  size_t cap);
-
-// the plain stages in FP64, or in FP32 for an FP32-form cell on a grid that is not cubic
-static fock_status plain_stages(Plan& pl, Cell& c, const PairSet& ps, const c128* X, int nx, const c128* P,
-                                const c128* M, int ns, c128* out, double scale, bool accumulate, hipStream_t st,
-                                size_t cap) {
-  if (c.f32plain) return plain_pipeline<float>(pl, c, ps, X, nx, P, M, ns, out, scale, accumulate, st, cap);
-  return plain_pipeline<double>(pl, c, ps, X, nx, P, M, ns, out, scale, accumulate, st, cap);
-}
-
 fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, const c128* P, const c128* M, int ns,
                             c128* out, double scale, bool accumulate, hipStream_t st) {
+  const int nr = c.nr, nt = ps.ntk * nx, nj = ps.nsk * ns;
+  const bool cube = c.Kt64.ptr != nullptr;  // the field fits on a CU
+  // many targets: the fused FP64 kernel, which keeps each target's sum on its CU
+  if (cube && !pair_rule(c, ps, nx, ns, X == P && P == M, false).pairs)
+    return run_fused64(c, ps, X, nx, P, M, ns, out, scale, accumulate, st);
+  // The pair symmetry, where u is targets and sources over the whole mesh; not in FP32, whose
+  // k-ranges give the full application's bits.
+  Mirror<double> mr;
+  if (!c.f32plain && !c.ds && X == P && P == M && nx == ns && ps.ntk == c.nk && ps.nsk == c.nk &&
+      ps.qidx == (const int*)c.qidx.ptr && nt > 3 * kPairTile && pairs_tri_fits(nt, nr, nr * sizeof(c128))) {
+    mr.F = X;
+    mr.dst = out;
+    mr.scale = scale;
+    mr.accumulate = mr.tri = true;
+  }
+  auto run = [&](size_t batch) -> fock_status {
+    hipError_t e;
+    fock_status s;
+    if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
+    if (c.f32plain)
+      s = run_pairs<float, double>(
+          nr, nt, nj, ns, plane_stage<float>(c.geom, num_cus, ps, X, nx, P, ns, (const double*)c.Kpl.ptr, st), M, out,
+          scale, accumulate, mr, batch, st);
+    else
+      s = run_pairs<double, double>(
+          nr, nt, nj, ns,
+          cube ? cube_stage<double>(c.geom.n1, num_cus, ps, X, nx, P, ns, (const double*)c.Kt64.ptr, st)
+               : plane_stage<double>(c.geom, num_cus, ps, X, nx, P, ns, (const double*)c.Kpl.ptr, st),
+          M, out, scale, accumulate, mr, batch, st);
+    if (s != FOCK_OK) return s;
+    if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
+    return FOCK_OK;
+  };
   const std::string key = key_for(c, ps, nx, "plain");
   TuneEntry te;
-  if (tune.get(key, &te)) return plain_stages(*this, c, ps, X, nx, P, M, ns, out, scale, accumulate, st,
-                                                (size_t)te.fields["batch_mb"] << 20);
-  if (!tuning || accumulate)
-    return plain_stages(*this, c, ps, X, nx, P, M, ns, out, scale, accumulate, st, batch_cap);
-  // measure the pair-batch size (each candidate writes the same result)
+  if (tune.get(key, &te)) return run((size_t)te.fields["batch_mb"] << 20);
+  if (!tuning || accumulate) return run(pair_batch);
+  // measure the pair-batch size (each candidate writes the same result to rounding)
   hipEvent_t e0, e1;
   hipError_t e;
   if ((e = hipEventCreate(&e0)) != hipSuccess) return hip_fail(e, "tuning event");
@@ -106,7 +124,7 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
   int bmb = 16384;
   for (int mb : {1024, 4096, 16384}) {
     (void)hipEventRecord(e0, st);
-    fock_status s = plain_stages(*this, c, ps, X, nx, P, M, ns, out, scale, false, st, (size_t)mb << 20);
+    fock_status s = run((size_t)mb << 20);
     if (s != FOCK_OK) return s;
     (void)hipEventRecord(e1, st);
     if ((e = hipEventSynchronize(e1)) != hipSuccess) return hip_fail(e, "tuning sync");
@@ -123,47 +141,7 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
   te.fields["ms"] = best;
   tune.put(key, te);
   save_tune();
-  return plain_stages(*this, c, ps, X, nx, P, M, ns, out, scale, false, st, (size_t)bmb << 20);
-}
-
-template <typename T>
-static fock_status plain_pipeline(Plan& pl, Cell& c, const PairSet& ps, const c128* X, int nx, const c128* P,
-                                  const c128* M, int ns, c128* out, double scale, bool accumulate, hipStream_t st,
-                                  size_t cap) {
-  const int nr = c.nr;
-  // a batch holds ntb target k-points x nkb source k-points (the pairs of one
-  // (target, source) k-point pair take per_k bytes): all sources of several targets
-  // when the cap allows, else a block of sources of one target
-  const size_t per_k = (size_t)ns * nx * nr * sizeof(cx<T>);
-  const long fit = (long)std::max<size_t>(1, cap / std::max<size_t>(per_k, 1));
-  const int nkb_max = (int)std::min<long>(fit, ps.nsk);
-  const int ntb_max = (int)std::max<long>(1, std::min<long>(fit / ps.nsk, ps.ntk));
-  if ((long)ntb_max * nkb_max * ns * nx > (long)INT32_MAX)
-    return fail(FOCK_ERR_SIZE, "pair batch of %d x %d k-points too large", ntb_max, nkb_max);
-  fock_status s = pl.batch.ensure((size_t)ntb_max * nkb_max * per_k, pl.workspace_cap, "plain-path batch buffer");
-  if (s != FOCK_OK) return s;
-  cx<T>* buf = (cx<T>*)pl.batch.ptr;
-  hipError_t e;
-  if ((e = pl.prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
-  for (int kt0 = 0; kt0 < ps.ntk; kt0 += ntb_max) {
-    const int ntb = std::min(ntb_max, ps.ntk - kt0);
-    for (int ks0 = 0; ks0 < ps.nsk; ks0 += nkb_max) {
-      const int nkb = std::min(nkb_max, ps.nsk - ks0);
-      const int nf = ntb * nkb * ns * nx;
-      if ((e = launch_pair_product(buf, X, P, kt0, ntb, ks0, nkb, ns, nx, nr, st)) != hipSuccess)
-        return hip_fail(e, "pair product");
-      if ((e = launch_fft3_plain(buf, nf, c.geom, -1, st)) != hipSuccess) return hip_fail(e, "forward FFT");
-      if ((e = launch_kernel_mul(buf, (const double*)c.K64.ptr, ps.qidx, kt0, ntb, ps.nsk, ks0, nkb, ns * nx, nr,
-                                 st)) != hipSuccess)
-        return hip_fail(e, "kernel multiply");
-      if ((e = launch_fft3_plain(buf, nf, c.geom, +1, st)) != hipSuccess) return hip_fail(e, "inverse FFT");
-      if ((e = launch_mac(out, buf, M, kt0, ntb, ks0, nkb, ns, nx, nr, scale, (accumulate || ks0 > 0) ? 1 : 0,
-                          st)) != hipSuccess)
-        return hip_fail(e, "accumulate");
-    }
-  }
-  if ((e = pl.prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
-  return FOCK_OK;
+  return run((size_t)bmb << 20);
 }
 
 fock_status Plan::shadow(DevBuf& buf, const c128* src, size_t count, const char* what, hipStream_t st,
@@ -340,7 +318,9 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
         mr.accumulate = true;
         mr.tri = true;
       }
-      pairs_status = run_pairs<float>(c, ps, Xs, nx, Ps, Ms, ns, out, scale, accumulate, (const float*)c.Kt.ptr, mr, st);
+      pairs_status = run_pairs<float, float>(
+          nr, nitems, ps.nsk * ns, ns, cube_stage<float>(n, num_cus, ps, Xs, nx, Ps, ns, (const float*)c.Kt.ptr, st), Ms,
+          out, scale, accumulate, mr, pair_batch, st);
       return hipSuccess;
     }
     if (v != 2) return launch_fused_apply(n, a, st, v, &ls);
@@ -462,8 +442,10 @@ fock_status Plan::run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx,
       mr.accumulate = mr.tri = true;
     }
     if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
-    if ((s = run_pairs<double>(c, ps, X, nx, P, M, ns, out, scale, accumulate, (const double*)c.Kt64.ptr, mr, st)) !=
-        FOCK_OK)
+    if ((s = run_pairs<double, double>(
+             c.nr, nitems, ps.nsk * ns, ns,
+             cube_stage<double>(c.geom.n1, num_cus, ps, X, nx, P, ns, (const double*)c.Kt64.ptr, st), M, out, scale,
+             accumulate, mr, pair_batch, st)) != FOCK_OK)
       return s;
     if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
     return FOCK_OK;

@@ -130,9 +130,11 @@ extern "C" fock_status fock_apply_noalloc(fockmi_plan plan, int cell, const void
     int rows = 0;
     long njmax = 0;
     pairs_block_shape(nitems, ps.nsk * c.nb, c.nb, c.nr, fb, kNoAllocBytes - o_a, true, false, &rows, &njmax);
-    return pairs_blocks<float>(c.geom.n1, c.nr, p->num_cus, ps, sx, nphi, su, su, c.nb, (c128*)vphi, -1.0 / c.nsrc,
-                               false, (const float*)c.Kt.ptr, Mirror<float>{}, rows, njmax, (c64*)(sp + o_a),
-                               sp + o_c, nullptr, nullptr, st);
+    return pairs_blocks<float, float>(
+        c.nr, nitems, ps.nsk * c.nb, c.nb,
+        cube_stage<float>(c.geom.n1, p->num_cus, ps, sx, nphi, su, c.nb, (const float*)c.Kt.ptr, st), su,
+        Mirror<float>{}, (c128*)vphi, -1.0 / c.nsrc, false, rows, njmax, (c64*)(sp + o_a), sp + o_c, nullptr, nullptr,
+        st);
   }
   FusedArgs a{};
   a.X = sx;

@@ -18,9 +18,7 @@
 // 1,270 ms in this form with plain W accesses, 1,142 ms with non-temporal ones, 1,088 ms with
 // the next pair's first operands loaded before the stores. One of eight k-point shards of it
 // (one-sided sums): 284.6 -> 247 ms.
-#include "pairs.hpp"
-
-#include "fused_common.hpp"
+#include "pairs_dev.hpp"
 
 namespace fockmi {
 
@@ -52,26 +50,6 @@ template <int N, typename T>
 constexpr int pw_ahead() { return sizeof(T) == 8 ? (N == 24 ? 2 : 4) : (N == 32 ? 6 : 8); }
 template <int N, typename T>
 constexpr int pw_grp_k() { return sizeof(T) == 8 ? 12 : (N <= 24 ? N : 8); }
-
-// a uniform load through the scalar cache: a vector load here would wait for the W stores
-// in flight, like every load that is waited for behind them
-__device__ __forceinline__ int ld_uniform(const int* p) {
-  return *(const __attribute__((address_space(4))) int*)(uintptr_t)p;
-}
-
-// W is written once and read once, much later: the non-temporal hint keeps it from pushing
-// the operands out of L2 (an XCD's 32 CUs write 8 MiB of W per pair round, twice its L2)
-template <typename T>
-__device__ __forceinline__ void st_w(cx<T>* p, cx<T> v) {
-  typedef T v2 __attribute__((ext_vector_type(2)));
-  __builtin_nontemporal_store((v2){v.re, v.im}, (v2*)p);
-}
-template <typename T>
-__device__ __forceinline__ cx<T> ld_w(const cx<T>* p) {
-  typedef T v2 __attribute__((ext_vector_type(2)));
-  const v2 v = __builtin_nontemporal_load((const v2*)p);
-  return {v.x, v.y};
-}
 
 template <int N, typename T, int WPE>
 __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE))) pair_w_kernel(PairArgs<T> a) {
@@ -109,35 +87,10 @@ __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE)
   const unsigned voff_t = (unsigned)(t * (int)sizeof(T));
   constexpr unsigned FB = (unsigned)NR * E;
 
-  // The pairs of a block in order: target tiles, for each tile its sources, for each source
-  // the tile's targets. XCD x (workgroups b = x mod 8) runs a contiguous eighth of them, so
-  // that the tile's targets, the current sources and the kernel table meet in its L2.
-  const long n = a.npairs;
-  const int x = blockIdx.x & 7;
-  const long q1 = n * (x + 1) / 8, step = gridDim.x >> 3;
-  long q = n * x / 8 + (blockIdx.x >> 3);
-  if (q >= q1) return;
-  int tile = 0;
-  long tile_q0 = 0, tile_q1 = 0;  // pairs of the current tile
-  int tw = 0;                     // its targets
-  int ti = 0, j = 0;              // target and source of the current pair within the block
-  auto enter = [&](int tt) {
-    tile = tt;
-    tw = a.nt - tt * kPairTile < kPairTile ? a.nt - tt * kPairTile : kPairTile;
-    const int njt = a.tri ? (a.nj < (tt + 1) * kPairTile ? a.nj : (tt + 1) * kPairTile) : a.nj;
-    tile_q1 = tile_q0 + (long)tw * njt;
-  };
-  auto locate = [&](long qq) {
-    while (qq >= tile_q1) {
-      tile_q0 = tile_q1;
-      enter(tile + 1);
-    }
-    const int rem = (int)(qq - tile_q0);
-    j = __builtin_amdgcn_readfirstlane(rem / tw);
-    ti = __builtin_amdgcn_readfirstlane(tile * kPairTile + rem % tw);
-  };
-  auto res_x = [&] { return make_rsrc(a.X + (long)(a.t0 + ti) * NR, FB); };
-  auto res_p = [&] { return make_rsrc(a.P + (long)(a.j0 + j) * NR, FB); };
+  PairWalk walk(a.b);
+  if (!walk.start()) return;
+  auto res_x = [&] { return make_rsrc(a.X + (long)(a.b.t0 + walk.ti) * NR, FB); };
+  auto res_p = [&] { return make_rsrc(a.P + (long)(a.b.j0 + walk.j) * NR, FB); };
   // The first PF operands of a pair are loaded before the previous pair's W is stored: a
   // wait for a load also waits for every store issued before it.
   constexpr int PF = pw_ahead<N, T>();
@@ -151,11 +104,9 @@ __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE)
     });
     __builtin_amdgcn_sched_barrier(0);
   };
-  enter(0);
-  locate(q);
   fetch();
   for (;;) {
-    const int gt = a.t0 + ti, gj = a.j0 + j;
+    const int gt = a.b.t0 + walk.ti, gj = a.b.j0 + walk.j;
     const int qi = ld_uniform(a.qidx + (long)(gt / a.nx) * a.nsk + gj / a.ns);
     const rsrc_t rX = res_x(), rP = res_p();
     const rsrc_t rK = make_rsrc(a.Kt + (long)qi * NR, NR * (unsigned)sizeof(T));
@@ -250,13 +201,9 @@ __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE)
       if constexpr (!INPLACE) __syncthreads();
     }
     fft<N, +1>(v);
-    char* w = (char*)(a.W + ((long)j * a.nt + ti) * NR);
-    q += step;
-    const bool more = q < q1;
-    if (more) {
-      locate(q);
-      fetch();
-    }
+    char* w = (char*)(a.W + ((long)walk.j * a.b.nt + walk.ti) * NR);
+    const bool more = walk.next();
+    if (more) fetch();
     static_for<N>([&](auto m1) { st_w((cx<T>*)(w + decltype(m1)::value * (NTI * E) + voff), v[m1]); });
     if (!more) return;
   }
@@ -280,8 +227,8 @@ __device__ __forceinline__ cx<T> cmac_conj(cx<T> acc, cx<T> w, cx<T> f) {
 // Stage 2. One wave holds kPairTile targets on 64 grid points and streams the sources; the
 // NW waves of a workgroup hold NW tiles on the same points, so the mirror sums of NW * 8
 // targets meet in LDS and go to memory once per source.
-template <typename T, int NW, bool TWO>
-__global__ void __launch_bounds__(64 * NW) wsum_kernel(WsumArgs<T> a) {
+template <typename TW, typename T, int NW, bool TWO>
+__global__ void __launch_bounds__(64 * NW) wsum_kernel(WsumArgs<TW, T> a) {
   constexpr int TI = kPairTile;
   constexpr bool F32 = sizeof(T) == 4;
   __shared__ cx<T> part[TWO ? NW * NW * 64 : 1];  // [source of the batch][wave][lane]
@@ -310,7 +257,7 @@ __global__ void __launch_bounds__(64 * NW) wsum_kernel(WsumArgs<T> a) {
     }
   });
   int jb = a.jb0;  // band of the current source within its k-point
-  const cx<T>* wp = a.W + (long)tile * TI * nr + r;
+  const cx<TW>* wp = a.W + (long)tile * TI * nr + r;
   for (int j0 = 0; j0 < a.nj; j0 += NW) {
     const int j1 = j0 + NW < a.nj ? j0 + NW : a.nj;
     for (int j = j0; j < j1; ++j) {
@@ -319,12 +266,17 @@ __global__ void __launch_bounds__(64 * NW) wsum_kernel(WsumArgs<T> a) {
       const bool mir = TWO && on && (!a.tri || tile > jt);
       cx<T> ms{0, 0};
       if (on) {
-        const cx<T>* wj = wp + (long)j * a.nt * nr;
+        const cx<TW>* wj = wp + (long)j * a.nt * nr;
         const cx<T> m = a.M[(long)(a.j0 + j) * nr + r];
         cx<T> wv[TI];
         static_for<TI>([&](auto i) {
           constexpr int I = decltype(i)::value;
-          wv[I] = I < n ? ld_w(wj + I * nr) : cx<T>{0, 0};
+          if (I < n) {
+            const cx<TW> q = ld_w(wj + I * nr);
+            wv[I] = cx<T>{(T)q.re, (T)q.im};
+          } else {
+            wv[I] = cx<T>{0, 0};
+          }
         });
         static_for<TI>([&](auto i) { acc[decltype(i)::value] = cmac(acc[decltype(i)::value], m, wv[decltype(i)::value]); });
         if constexpr (TWO) {
@@ -426,7 +378,7 @@ __global__ void __launch_bounds__(256) mirror_add_kernel(c128* __restrict__ dst,
 
 template <int N, typename T, int WPE>
 hipError_t launch_pw(const PairArgs<T>& a, int slots, hipStream_t st) {
-  const long per = (a.npairs + 7) / 8;
+  const long per = (a.b.npairs + 7) / 8;
   const int g = (int)(per < slots / 8 ? per : slots / 8);
   hipLaunchKernelGGL((pair_w_kernel<N, T, WPE>), dim3(8 * g), dim3(N * N), 0, st, a);
   return hipGetLastError();
@@ -467,20 +419,21 @@ hipError_t launch_pair_w<double>(int n, const PairArgs<double>& a, int num_cus, 
   }
 }
 
-template <typename T>
-hipError_t launch_wsum(const WsumArgs<T>& a, hipStream_t st) {
+template <typename TW, typename TM>
+hipError_t launch_wsum(const WsumArgs<TW, TM>& a, hipStream_t st) {
   constexpr int NW = kPairGroup / kPairTile;
   const int tiles = (a.nt + kPairTile - 1) / kPairTile;
   if (a.nr % 64 != 0) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(a.nr / 64), (unsigned)((tiles + NW - 1) / NW));
   if (a.mir)
-    hipLaunchKernelGGL((wsum_kernel<T, NW, true>), grid, dim3(64 * NW), 0, st, a);
+    hipLaunchKernelGGL((wsum_kernel<TW, TM, NW, true>), grid, dim3(64 * NW), 0, st, a);
   else
-    hipLaunchKernelGGL((wsum_kernel<T, NW, false>), grid, dim3(64 * NW), 0, st, a);
+    hipLaunchKernelGGL((wsum_kernel<TW, TM, NW, false>), grid, dim3(64 * NW), 0, st, a);
   return hipGetLastError();
 }
-template hipError_t launch_wsum<float>(const WsumArgs<float>&, hipStream_t);
-template hipError_t launch_wsum<double>(const WsumArgs<double>&, hipStream_t);
+template hipError_t launch_wsum<float, float>(const WsumArgs<float, float>&, hipStream_t);
+template hipError_t launch_wsum<double, double>(const WsumArgs<double, double>&, hipStream_t);
+template hipError_t launch_wsum<float, double>(const WsumArgs<float, double>&, hipStream_t);
 
 hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double scale, int accumulate, int nsrc,
                              int nr, int rows, int tri, hipStream_t st) {

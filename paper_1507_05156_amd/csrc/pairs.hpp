@@ -12,6 +12,10 @@ constexpr int kPairGroup = 64;  // targets of one workgroup of stage 2: those wh
 // (index ks * ns + band). With tri, targets and sources are the same fields (t0 == j0,
 // nt == nj) and only the pairs whose target tile is not below the source tile are run.
 // W of pair (t, j) is field j * nt + t of the batch.
+struct PairBlock {
+  int t0, nt, j0, nj, tri;
+  long npairs;      // pairs the block runs
+};
 template <typename T>
 struct PairArgs {
   const cx<T>* X;   // targets [ntk][nx][nr]
@@ -19,9 +23,25 @@ struct PairArgs {
   const T* Kt;      // [nq][nr] kernel tables in the z-phase order, 1/N_r folded
   const int* qidx;  // [ntk][nsk]
   cx<T>* W;
-  int t0, nt, j0, nj, nx, ns, nsk, tri;
-  long npairs;      // pairs the block runs
+  int nx, ns, nsk;
+  PairBlock b;
 };
+// The same block for the plane passes (planes.hip): inputs in complex128, rounded to T as they
+// are read, and tables [nq][l1][l3][l2] in FP64.
+template <typename T>
+struct PlaneArgs {
+  const c128* X;
+  const c128* P;
+  const double* K;
+  const int* qidx;
+  cx<T>* W;
+  int nx, ns, nsk, n1;
+  PairBlock b;
+};
+template <typename T>
+hipError_t launch_pair_planes(int n2, int n3, const PlaneArgs<T>& a, int num_cus, hipStream_t st);
+hipError_t launch_plane_table(double* Kp, const double* K, int nq, const Geom& g, hipStream_t st);
+
 inline long pair_count(int nt, int nj, bool tri) {
   if (!tri) return (long)nt * nj;
   long n = 0;
@@ -39,12 +59,13 @@ template <typename T>
 hipError_t launch_pair_w(int n, const PairArgs<T>& a, int num_cus, hipStream_t st);
 
 // The sums over one block. out: the targets' sums; mir (NULL: one-sided): the sources' sums
-// of F_t conj(W), unscaled, over the pairs of different tiles when tri.
-template <typename T>
+// of F_t conj(W), unscaled, over the pairs of different tiles when tri. TM float: FP32 products and
+// partial sums, compensated FP64 sums; double: FP64 throughout (W widened).
+template <typename TW, typename TM>
 struct WsumArgs {
-  const cx<T>* W;
-  const cx<T>* M;   // [sources][nr]
-  const cx<T>* F;   // [targets][nr]
+  const cx<TW>* W;
+  const cx<TM>* M;  // [sources][nr]
+  const cx<TM>* F;  // [targets][nr]
   c128* out;        // [targets][nr]
   cx<float>* comp;  // FP32: compensation of out between the blocks of one target
   c128* run;        // FP64: the unscaled sum between the blocks of one target
@@ -59,8 +80,8 @@ struct WsumArgs {
   int accumulate;   // add to the existing out
   double scale;
 };
-template <typename T>
-hipError_t launch_wsum(const WsumArgs<T>& a, hipStream_t st);
+template <typename TW, typename TM>
+hipError_t launch_wsum(const WsumArgs<TW, TM>& a, hipStream_t st);
 // dst = (accumulate ? dst : 0) + scale * sum over the groups of (mir + mcomp); mcomp may be NULL
 hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double scale, int accumulate, int nsrc,
                              int nr, int rows, int tri, hipStream_t st);

@@ -87,28 +87,16 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
   return r;
 }
 
-// the blocks of a sum: rows of `rows` targets, at most njmax sources each
-template <typename T>
-fock_status pairs_blocks(int n, int nr, int num_cus, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P,
-                         const cx<T>* M, int ns, c128* out, double scale, bool accumulate, const T* Kt,
-                         const Mirror<T>& mr, int rows, long njmax, cx<T>* W, void* run, c128* mir, c64* mcomp,
-                         hipStream_t st) {
-  constexpr bool F32 = sizeof(T) == 4;
-  const int nt = ps.ntk * nx, nj = ps.nsk * ns;
+template <typename TW, typename TM>
+fock_status pairs_blocks(int nr, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M,
+                         const Mirror<TM>& mr, c128* out, double scale, bool accumulate, int rows, long njmax,
+                         cx<TW>* W, void* run, c128* mir, c64* mcomp, hipStream_t st) {
+  constexpr bool F32 = sizeof(TM) == 4;
   const bool two = mr.dst != nullptr;
   fock_status s;
   hipError_t e;
-  PairArgs<T> pa{};
-  pa.X = X;
-  pa.P = P;
-  pa.Kt = Kt;
-  pa.qidx = ps.qidx;
-  pa.W = W;
-  pa.nx = nx;
-  pa.ns = ns;
-  pa.nsk = ps.nsk;
-  WsumArgs<T> wa{};
-  wa.W = pa.W;
+  WsumArgs<TW, TM> wa{};
+  wa.W = W;
   wa.M = M;
   wa.F = mr.F;
   wa.out = out;
@@ -120,12 +108,11 @@ fock_status pairs_blocks(int n, int nr, int num_cus, const PairSet& ps, const cx
   wa.accumulate = accumulate ? 1 : 0;
   wa.scale = scale;
   auto block = [&](int t0, int ntb, int j0, int njb, bool tri, bool first, bool last, bool mfirst) -> fock_status {
-    pa.t0 = wa.t0 = t0;
-    pa.nt = wa.nt = ntb;
-    pa.j0 = wa.j0 = j0;
-    pa.nj = wa.nj = njb;
-    pa.tri = wa.tri = tri ? 1 : 0;
-    pa.npairs = pair_count(ntb, njb, tri);
+    wa.t0 = t0;
+    wa.nt = ntb;
+    wa.j0 = j0;
+    wa.nj = njb;
+    wa.tri = tri ? 1 : 0;
     wa.jb0 = j0 % ns;
     wa.first = first ? 1 : 0;
     wa.last = last ? 1 : 0;
@@ -133,8 +120,9 @@ fock_status pairs_blocks(int n, int nr, int num_cus, const PairSet& ps, const cx
     // the sums kept between the blocks of a row, indexed by target
     wa.comp = F32 ? (c64*)run - (long)t0 * nr : nullptr;
     wa.run = F32 ? nullptr : (c128*)run - (long)t0 * nr;
-    if ((e = launch_pair_w<T>(n, pa, num_cus, st)) != hipSuccess) return hip_fail(e, "pair kernel");
-    if ((e = launch_wsum<T>(wa, st)) != hipSuccess) return hip_fail(e, "pair sums");
+    if ((e = stage(PairBlock{t0, ntb, j0, njb, tri ? 1 : 0, pair_count(ntb, njb, tri)}, W)) != hipSuccess)
+      return hip_fail(e, "pair kernel");
+    if ((e = launch_wsum<TW, TM>(wa, st)) != hipSuccess) return hip_fail(e, "pair sums");
     return FOCK_OK;
   };
   for (int t0 = 0; t0 < nt; t0 += rows) {
@@ -154,22 +142,19 @@ fock_status pairs_blocks(int n, int nr, int num_cus, const PairSet& ps, const cx
     }
     if (mr.tri && (s = block(t0, ntb, t0, ntb, true, t0 == 0, true, true)) != FOCK_OK) return s;
   }
-  if (two && (e = launch_mirror_add(mr.dst, mir, wa.mcomp, mr.scale, mr.accumulate ? 1 : 0,
-                                    nj, nr, rows, mr.tri ? 1 : 0, st)) != hipSuccess)
+  if (two && (e = launch_mirror_add(mr.dst, mir, wa.mcomp, mr.scale, mr.accumulate ? 1 : 0, nj, nr, rows,
+                                    mr.tri ? 1 : 0, st)) != hipSuccess)
     return hip_fail(e, "mirror sums");
   return FOCK_OK;
 }
 
-template <typename T>
-fock_status Plan::run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P, const cx<T>* M,
-                            int ns, c128* out, double scale, bool accumulate, const T* Kt, const Mirror<T>& mr,
-                            hipStream_t st) {
-  constexpr bool F32 = sizeof(T) == 4;
-  const int nr = c.nr, nt = ps.ntk * nx, nj = ps.nsk * ns;
-  const size_t fb = (size_t)nr * sizeof(cx<T>);
+template <typename TW, typename TM>
+fock_status Plan::run_pairs(int nr, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M, c128* out,
+                            double scale, bool accumulate, const Mirror<TM>& mr, size_t batch, hipStream_t st) {
+  constexpr bool F32 = sizeof(TM) == 4;
+  const size_t fb = (size_t)nr * sizeof(cx<TW>);
   const bool two = mr.dst != nullptr;
-  if (const char* g = std::getenv("XX_BATCH_MB")) pair_batch = (size_t)std::atol(g) << 20;
-  size_t budget = workspace_cap ? std::min(workspace_cap, pair_batch) : pair_batch;
+  size_t budget = workspace_cap ? std::min(workspace_cap, batch) : batch;
   fock_status s;
   int rows = 0;
   long njmax = 0;
@@ -186,20 +171,72 @@ fock_status Plan::run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, in
   const int groups = (rows + kPairGroup - 1) / kPairGroup;
   if (two) {
     if ((s = pmir.ensure((size_t)groups * nj * nr * sizeof(c128), workspace_cap, "mirror sums")) != FOCK_OK) return s;
-    if (F32 && (s = pmcomp.ensure((size_t)groups * nj * nr * sizeof(c64), workspace_cap, "mirror compensation")) != FOCK_OK)
+    if (F32 && (s = pmcomp.ensure((size_t)groups * nj * nr * sizeof(c64), workspace_cap, "mirror compensation")) !=
+                   FOCK_OK)
       return s;
   }
-  return pairs_blocks<T>(c.geom.n1, nr, num_cus, ps, X, nx, P, M, ns, out, scale, accumulate, Kt, mr, rows, njmax,
-                         (cx<T>*)pbatch.ptr, prun.ptr, (c128*)pmir.ptr, (c64*)pmcomp.ptr, st);
+  return pairs_blocks<TW, TM>(nr, nt, nj, ns, stage, M, mr, out, scale, accumulate, rows, njmax, (cx<TW>*)pbatch.ptr,
+                              prun.ptr, (c128*)pmir.ptr, (c64*)pmcomp.ptr, st);
 }
 
-template fock_status pairs_blocks<float>(int, int, int, const PairSet&, const c64*, int, const c64*, const c64*, int,
-                                         c128*, double, bool, const float*, const Mirror<float>&, int, long, c64*,
-                                         void*, c128*, c64*, hipStream_t);
-template fock_status Plan::run_pairs<float>(const Cell&, const PairSet&, const c64*, int, const c64*, const c64*, int,
-                                            c128*, double, bool, const float*, const Mirror<float>&, hipStream_t);
-template fock_status Plan::run_pairs<double>(const Cell&, const PairSet&, const c128*, int, const c128*, const c128*,
-                                             int, c128*, double, bool, const double*, const Mirror<double>&,
-                                             hipStream_t);
+template <typename T>
+PairStage<T> cube_stage(int n, int num_cus, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P, int ns,
+                        const T* Kt, hipStream_t st) {
+  PairArgs<T> pa{};
+  pa.X = X;
+  pa.P = P;
+  pa.Kt = Kt;
+  pa.qidx = ps.qidx;
+  pa.nx = nx;
+  pa.ns = ns;
+  pa.nsk = ps.nsk;
+  return [=](const PairBlock& b, cx<T>* W) {
+    PairArgs<T> q = pa;
+    q.b = b;
+    q.W = W;
+    return launch_pair_w<T>(n, q, num_cus, st);
+  };
+}
+
+template <typename T>
+PairStage<T> plane_stage(const Geom& g, int num_cus, const PairSet& ps, const c128* X, int nx, const c128* P, int ns,
+                         const double* K, hipStream_t st) {
+  PlaneArgs<T> pa{};
+  pa.X = X;
+  pa.P = P;
+  pa.K = K;
+  pa.qidx = ps.qidx;
+  pa.nx = nx;
+  pa.ns = ns;
+  pa.nsk = ps.nsk;
+  pa.n1 = g.n1;
+  const int n2 = g.n2, n3 = g.n3;
+  return [=](const PairBlock& b, cx<T>* W) {
+    PlaneArgs<T> q = pa;
+    q.b = b;
+    q.W = W;
+    return launch_pair_planes<T>(n2, n3, q, num_cus, st);
+  };
+}
+
+template PairStage<float> cube_stage<float>(int, int, const PairSet&, const c64*, int, const c64*, int, const float*,
+                                            hipStream_t);
+template PairStage<double> cube_stage<double>(int, int, const PairSet&, const c128*, int, const c128*, int,
+                                              const double*, hipStream_t);
+template PairStage<float> plane_stage<float>(const Geom&, int, const PairSet&, const c128*, int, const c128*, int,
+                                             const double*, hipStream_t);
+template PairStage<double> plane_stage<double>(const Geom&, int, const PairSet&, const c128*, int, const c128*, int,
+                                               const double*, hipStream_t);
+
+template fock_status pairs_blocks<float, float>(int, int, int, int, const PairStage<float>&, const c64*,
+                                                const Mirror<float>&, c128*, double, bool, int, long, c64*, void*,
+                                                c128*, c64*, hipStream_t);
+#define FOCKMI_RUN_PAIRS(TW, TM)                                                                                  \
+  template fock_status Plan::run_pairs<TW, TM>(int, int, int, int, const PairStage<TW>&, const cx<TM>*, c128*,    \
+                                               double, bool, const Mirror<TM>&, size_t, hipStream_t);
+FOCKMI_RUN_PAIRS(float, float)
+FOCKMI_RUN_PAIRS(double, double)
+FOCKMI_RUN_PAIRS(float, double)
+#undef FOCKMI_RUN_PAIRS
 
 }  // namespace fockmi

@@ -131,33 +131,38 @@ fock_status Plan::init_cell(Cell& c, const fock_cell_desc& d, int index) {
   if ((e = hipMemcpy(c.kvec.ptr, c.kpts.data(), c.kpts.size() * sizeof(double), hipMemcpyHostToDevice)) !=
       hipSuccess)
     return hip_fail(e, "upload k-points");
-  if ((s = c.K64.ensure((size_t)c.nq * c.nr * sizeof(double), 0, "FP64 kernel tables")) != FOCK_OK) return s;
-  if ((e = launch_build_table_f64((double*)c.K64.ptr, (const double*)c.qvec.ptr, (const int*)c.qzero.ptr, c.nq,
+  if ((s = ktmp.ensure((size_t)c.nq * c.nr * sizeof(double), 0, "FP64 kernel tables")) != FOCK_OK) return s;
+  if ((e = launch_build_table_f64((double*)ktmp.ptr, (const double*)c.qvec.ptr, (const int*)c.qzero.ptr, c.nq,
                                   c.geom, c.omega, 1.0 / c.nr, 0)) != hipSuccess)
     return hip_fail(e, "kernel table");
   if (prec == FOCK_FP32_COMP && !(c.geom.n1 == c.geom.n2 && c.geom.n2 == c.geom.n3)) {
-    // the fused kernels take cubic grids; this cell runs the plain stages in FP32
+    // the fused kernels take cubic grids; this cell runs the two-stage form with plane passes
     c.f32plain = true;
   } else if (prec == FOCK_FP32_COMP) {
     if ((s = c.Kt.ensure((size_t)c.nq * c.nr * sizeof(float), 0, "FP32 kernel tables")) != FOCK_OK) return s;
-    if ((e = launch_build_table_fused((float*)c.Kt.ptr, (const double*)c.K64.ptr, c.nq, c.geom.n1, 0)) !=
+    if ((e = launch_build_table_fused((float*)c.Kt.ptr, (const double*)ktmp.ptr, c.nq, c.geom.n1, 0)) !=
         hipSuccess)
       return hip_fail(e, "FP32 kernel table");
     if (c.geom.n1 == 32) {
       // (S, D) pairs of the split 32^3 form
       if ((s = c.SD.ensure(split32_sd_floats(c.nq) * sizeof(float), 0, "split-form kernel tables")) != FOCK_OK)
         return s;
-      if ((e = launch_build_sd32((float*)c.SD.ptr, (const double*)c.K64.ptr, c.nq, 0)) != hipSuccess)
+      if ((e = launch_build_sd32((float*)c.SD.ptr, (const double*)ktmp.ptr, c.nq, 0)) != hipSuccess)
         return hip_fail(e, "split-form kernel table");
     }
   }
-  if (prec == FOCK_FP64_FUSED && c.geom.n1 == c.geom.n2 && c.geom.n2 == c.geom.n3 && fused64_supported(c.geom.n1)) {
+  const bool cube = c.geom.n1 == c.geom.n2 && c.geom.n2 == c.geom.n3;
+  if (prec != FOCK_FP32_COMP && cube && fused64_supported(c.geom.n1)) {
     if ((s = c.Kt64.ensure((size_t)c.nq * c.nr * sizeof(double), 0, "fused FP64 kernel tables")) != FOCK_OK)
       return s;
-    if ((e = launch_build_table_fused64((double*)c.Kt64.ptr, (const double*)c.K64.ptr, c.nq, c.geom.n1,
+    if ((e = launch_build_table_fused64((double*)c.Kt64.ptr, (const double*)ktmp.ptr, c.nq, c.geom.n1,
                                         fused64_phases(c.geom.n1), 0)) != hipSuccess)
       return hip_fail(e, "fused FP64 kernel table");
-    c.f64f = true;
+    c.f64f = prec == FOCK_FP64_FUSED;
+  } else if (prec != FOCK_FP32_COMP || c.f32plain) {
+    if ((s = c.Kpl.ensure((size_t)c.nq * c.nr * sizeof(double), 0, "plane-pass kernel tables")) != FOCK_OK) return s;
+    if ((e = launch_plane_table((double*)c.Kpl.ptr, (const double*)ktmp.ptr, c.nq, c.geom, 0)) != hipSuccess)
+      return hip_fail(e, "plane-pass kernel table");
   }
   if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(e, "plan set-up");
   return FOCK_OK;
@@ -208,13 +213,13 @@ void Plan::destroy() {
     c.qidx_st.release();
     c.qvec.release();
     c.qzero.release();
-    c.K64.release();
     c.Kt.release();
     c.SD.release();
     c.Kt64.release();
+    c.Kpl.release();
     c.kvec.release();
   }
-  for (DevBuf* b : {&batch, &shadow_x, &shadow_p, &shadow_m, &comp, &accs, &vu, &partial, &dotres, &srcbuf, &srcout,
+  for (DevBuf* b : {&ktmp, &shadow_x, &shadow_p, &shadow_m, &comp, &accs, &vu, &partial, &dotres, &srcbuf, &srcout,
                     &psi0, &phiA, &phiB, &predb, &srcbuf2, &kin, &vxb, &lam, &lam2, &gtmp, &ftmp, &phis, &norms,
                     &red6, &vloc_buf, &sync, &parts, &xbuf, &sflags, &sstatus, &fallbacks, &mpart, &msum, &mcomp,
                     &mdone, &sym_rank, &sym_cnt, &pbatch, &prun, &pmir, &pmcomp})

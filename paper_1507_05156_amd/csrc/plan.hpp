@@ -3,12 +3,14 @@
 
 #include <hip/hip_runtime.h>
 
+#include <functional>
 #include <initializer_list>
 #include <string>
 #include <vector>
 
 #include "../../include/fockmi.h"
 #include "kernels.hpp"
+#include "pairs.hpp"
 #include "tune.hpp"
 
 namespace fockmi {
@@ -50,12 +52,12 @@ struct Cell {
   int nq = 0;                 // distinct q = k_t - k_s
   std::vector<int> qidx_host; // [nk][nk]
   DevBuf qidx, qvec, qzero;   // int[nk*nk], double[nq*3], int[nq]
-  DevBuf K64;                 // double[nq][nr], 1/N_r folded, natural slot order
   DevBuf Kt;                  // float[nq][nr], fused-kernel layout (FP32 plans)
   DevBuf SD;                  // float[nq][nr/2][2], (S, D) pairs of the split 32^3 form (FP32 plans, n = 32)
-  DevBuf Kt64;                // double[nq][nr], fused FP64 kernel layout (FP64-fused plans)
+  DevBuf Kt64;                // double[nq][nr], fused FP64 kernel layout (FP64 plans, cubic grids up to 24)
+  DevBuf Kpl;                 // double[nq][nr] as [l1][l3][l2], for the plane passes (grids without a one-CU kernel)
   bool f64f = false;          // this cell runs the fused FP64 kernel
-  bool f32plain = false;      // an FP32-form cell on a grid that is not cubic: the plain stages in FP32
+  bool f32plain = false;      // an FP32-form cell on a grid that is not cubic: complex64 plane passes, FP64 sums
   DevBuf kvec;                // double[nk][3] k-points on the device
   // down-sampling: the source sub-mesh S (all k-points when ds is false)
   bool ds = false;
@@ -111,13 +113,25 @@ struct Mirror {
 // (whole_partials: blocks of at least one FP32 partial sum of at most 16 bands).
 void pairs_block_shape(int nt, int nj, int ns, int nr, size_t fb, size_t budget, bool whole_partials, bool tri,
                        int* rows, long* njmax);
-// The blocks of a two-stage pair sum over buffers of the caller's: W holds rows * njmax fields,
-// run rows * nr sums (complex64 in FP32, complex128 in FP64).
+// Stage 1 of a two-stage pair sum: W of a block's pairs into the batch.
+template <typename TW>
+using PairStage = std::function<hipError_t(const PairBlock&, cx<TW>*)>;
+// one pair per workgroup pass, on a cubic grid whose field fits on a CU; Kt: tables in the
+// fused kernel's order
 template <typename T>
-fock_status pairs_blocks(int n, int nr, int num_cus, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P,
-                         const cx<T>* M, int ns, c128* out, double scale, bool accumulate, const T* Kt,
-                         const Mirror<T>& mr, int rows, long njmax, cx<T>* W, void* run, c128* mir, c64* mcomp,
-                         hipStream_t st);
+PairStage<T> cube_stage(int n, int num_cus, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P, int ns,
+                        const T* Kt, hipStream_t st);
+// the plane passes, any grid; K: tables in the plane passes' order
+template <typename T>
+PairStage<T> plane_stage(const Geom& g, int num_cus, const PairSet& ps, const c128* X, int nx, const c128* P, int ns,
+                         const double* K, hipStream_t st);
+// The blocks of a two-stage pair sum (nt targets, nj sources of ns per k-point) over buffers of
+// the caller's: W holds rows * njmax fields, run rows * nr sums (complex64 for FP32 sums,
+// complex128 for FP64 ones). TW: the type of W, TM: of the products and sums.
+template <typename TW, typename TM>
+fock_status pairs_blocks(int nr, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M,
+                         const Mirror<TM>& mr, c128* out, double scale, bool accumulate, int rows, long njmax,
+                         cx<TW>* W, void* run, c128* mir, c64* mcomp, hipStream_t st);
 
 // bytes of the fixed scratch array of fock_apply_noalloc, and what a sum needs of it
 // (x_is_u: the targets are the sources' array)
@@ -139,9 +153,9 @@ struct Plan {
   std::string tune_path;
   std::vector<Cell> cells;
   size_t workspace_cap = 0;                 // 0 = no cap (FOCKMI_WORKSPACE_CAP overrides)
-  size_t batch_cap = size_t(16) << 30;      // plain path: bytes per pair batch
   int xcd_map = 1;
-  DevBuf batch, shadow_x, shadow_p, shadow_m, comp, accs, vu, partial, dotres, srcbuf, srcout;
+  DevBuf ktmp;                              // one cell's tables in natural order, while its forms' copies are made
+  DevBuf shadow_x, shadow_p, shadow_m, comp, accs, vu, partial, dotres, srcbuf, srcout;
   DevBuf psi0, phiA, phiB, predb, srcbuf2, kin, vxb, lam, lam2, gtmp, ftmp, phis, norms, red6, vloc_buf;
   DevBuf sync;                              // lockstep counters of the persistent fused form
   DevBuf parts;                             // FP64 part sums of the lockstep form's k' split
@@ -192,11 +206,10 @@ struct Plan {
                         c128* out, double scale, bool accumulate, hipStream_t st);
   fock_status run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx, const c128* P, const c128* M,
                           int ns, c128* out, double scale, bool accumulate, hipStream_t st);
-  // the same sum in the two-stage pair form; Kt: tables in the pair kernel's order
-  template <typename T>
-  fock_status run_pairs(const Cell& c, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P, const cx<T>* M,
-                        int ns, c128* out, double scale, bool accumulate, const T* Kt, const Mirror<T>& mr,
-                        hipStream_t st);
+  // a sum in the two-stage pair form, its batch at most `batch` bytes
+  template <typename TW, typename TM>
+  fock_status run_pairs(int nr, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M, c128* out,
+                        double scale, bool accumulate, const Mirror<TM>& mr, size_t batch, hipStream_t st);
   // whether the sum runs in the two-stage pair form (cubic grids up to 24), and with the pair symmetry
   struct PairRule {
     bool pairs = false, tri = false;

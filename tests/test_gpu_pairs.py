@@ -2,11 +2,11 @@
 at the sizes where its blocks and tiles end: one field, a target tile (8 fields) less and more
 than full, a group of 64 fields and one more, several rows of blocks with rectangles beside
 the triangle, k-points whose bands end inside a tile, more than 16 bands (two FP32 partial
-sums per k-point). Every k-point against a reference of the same sum, with u as targets and
-sources (each pair transformed once) and with separate targets (one-sided).
+sums per k-point). Every k-point against torch's complex128 FFTs over the oracle's kernel
+tables, with u as targets and sources (each pair transformed once) and with separate targets
+(one-sided).
 
-The tolerances are the forms' stated ones, per k-point against the plain FP64 path: 1e-6 in FP32,
-1e-10 in FP64."""
+The tolerances are the forms' stated ones, per k-point: 1e-6 in FP32, 1e-10 in FP64."""
 
 import os
 
@@ -27,18 +27,52 @@ def make(n, mesh, nb, prec, cap=None):
     if cap is not None:
         os.environ["FOCKMI_WORKSPACE_CAP"] = str(cap)
     try:
-        return Plan(dict(n=n, a=cell, kpts=kp, nb=nb, omega=OMEGA), prec=prec), len(kp)
+        return Plan(dict(n=n, a=cell, kpts=kp, nb=nb, omega=OMEGA), prec=prec), kp
     finally:
         os.environ.pop("FOCKMI_WORKSPACE_CAP", None)
+
+
+class Ref:
+    """sum over (k', j) of M_jk' IDFT(K DFT(conj(P_jk') X_ik)) / -N_k, one k-point pair at a time."""
+
+    def __init__(self, n, kp):
+        import torch
+        from oracle.kernel import kernel_table
+        B = synth.reciprocal_rows(synth.cubic_cell())
+        n = (n,) * 3 if isinstance(n, int) else n
+        self.nk, tab = len(kp), {}
+        for t in range(self.nk):
+            for s in range(self.nk):
+                q = tuple(np.round(kp[t] - kp[s], 12))
+                if q not in tab:
+                    tab[q] = torch.from_numpy(np.ascontiguousarray(kernel_table(kp[t] - kp[s], t == s, n, B, OMEGA))).to("cuda:0")
+        self.K = [[tab[tuple(np.round(kp[t] - kp[s], 12))] for s in range(self.nk)] for t in range(self.nk)]
+
+    def sum(self, x, p, m):
+        import torch
+        out = torch.zeros_like(x)
+        for t in range(self.nk):
+            for s in range(self.nk):
+                for j in range(p.shape[1]):
+                    w = torch.fft.fftn(p[s, j].conj() * x[t], dim=(1, 2, 3)) * self.K[t][s]
+                    out[t] += m[s, j] * torch.fft.ifftn(w, dim=(1, 2, 3))
+        return out / -self.nk
+
+    def apply(self, u, phi=None):
+        return self.sum(u if phi is None else phi, u, u)
+
+    def vjp(self, u, phi, g):
+        return self.sum(u, phi, g) + self.sum(u, g, phi), self.sum(g, u, u)
 
 
 def fields(nk, nb, n, seed):
     """Random fields with the spectrum of orbitals (the FP32 error bound assumes a decaying one)."""
     import torch
+    n = (n,) * 3 if isinstance(n, int) else n
     g = torch.Generator(device="cuda:0").manual_seed(seed)
-    x = torch.randn((nk, nb, n, n, n), dtype=torch.complex128, device="cuda:0", generator=g)
-    f = torch.fft.fftfreq(n, dtype=torch.float64, device="cuda:0") * n
-    k2 = f[:, None, None] ** 2 + f[None, :, None] ** 2 + f[None, None, :] ** 2
+    x = torch.randn((nk, nb) + n, dtype=torch.complex128, device="cuda:0", generator=g)
+    f = [torch.fft.fftfreq(m, dtype=torch.float64, device="cuda:0") * m for m in n]
+    k2 = f[0][:, None, None] ** 2 + f[1][None, :, None] ** 2 + f[2][None, None, :] ** 2
     return torch.fft.ifftn(x * torch.exp(-k2 / 16.0), dim=(2, 3, 4)).contiguous()
 
 
@@ -51,8 +85,8 @@ def per_k(a, b):
                                          ((3, 1, 1), 19, 40 << 20)])
 def test_fp32_32cube_blocks(device, mesh, nb, cap):
     print(f"[gpu] pair form 32^3 mesh={mesh} nb={nb} cap={cap}", flush=True)
-    plan, nk = make(32, mesh, nb, "fp32", cap)
-    ref, _ = make(32, mesh, nb, "fp64")
+    plan, kp = make(32, mesh, nb, "fp32", cap)
+    ref, nk = Ref(32, kp), len(kp)
     u = fields(nk, nb, 32, 11 + nb)
     got = plan.apply(u)
     assert bool((plan.apply(u) == got).all())
@@ -76,8 +110,13 @@ def test_small_cube_blocks(device, n, prec, mesh, nb, cap):
     blocks of a few sources."""
     print(f"[gpu] pair form {n}^3 {prec} mesh={mesh} nb={nb} cap={cap}", flush=True)
     tol = 1e-6 if prec == "fp32" else 1e-10
-    plan, nk = make(n, mesh, nb, prec, cap)
-    ref, _ = make(n, mesh, nb, "fp64")
+    plan, kp = make(n, mesh, nb, prec, cap)
+    ref, nk = Ref(n, kp), len(kp)
+    u = fields(nk, nb, n, 21 + nb)
+    every_call(plan, ref, n, nk, nb, tol)
+
+
+def every_call(plan, ref, n, nk, nb, tol):
     u = fields(nk, nb, n, 21 + nb)
     got = plan.apply(u)
     assert bool((plan.apply(u) == got).all())
@@ -91,13 +130,44 @@ def test_small_cube_blocks(device, n, prec, mesh, nb, cap):
         assert per_k(a, b) < tol
 
 
+LENGTHS = (16, 20, 24, 32)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("n2", LENGTHS)
+@pytest.mark.parametrize("n3", LENGTHS)
+def test_plane_passes(device, n2, n3, prec):
+    """Every plane shape of the passes that serve grids without a one-CU kernel (n1 cycles through
+    the lengths), and 32^3 in FP64; 3 k-points x 9 bands: 27 fields, whose last tile has 3."""
+    n = (LENGTHS[(LENGTHS.index(n2) + LENGTHS.index(n3) + 1) % 4], n2, n3)
+    if n[0] == n2 == n3:
+        n = (16 if n2 != 16 else 32, n2, n3)
+    if (n2, n3, prec) == (32, 32, "fp64"):
+        n = (32, 32, 32)
+    print(f"[gpu] plane passes {n} {prec}", flush=True)
+    plan, kp = make(n, (3, 1, 1), 9, prec)
+    every_call(plan, Ref(n, kp), n, len(kp), 9, 1e-6 if prec == "fp32" else 1e-10)
+
+
+@pytest.mark.parametrize("n,mesh,nb,cap", [((32, 32, 32), (1, 1, 1), 1, None), ((32, 32, 32), (5, 1, 1), 13, 2200 << 20),
+                                           ((24, 32, 16), (2, 1, 1), 40, 12 << 20), ((16, 16, 16), (2, 1, 1), 20, None),
+                                           ((24, 24, 24), (5, 1, 1), 13, 910 << 20)])
+def test_fp64_blocks(device, n, mesh, nb, cap):
+    """The FP64 precision: one field, rows of 64 fields with a second row, a cap of a few sources
+    per block, and cubic grids whose field fits on a CU."""
+    print(f"[gpu] fp64 blocks {n} mesh={mesh} nb={nb} cap={cap}", flush=True)
+    plan, kp = make(n, mesh, nb, "fp64", cap)
+    every_call(plan, Ref(n, kp), n, len(kp), nb, 1e-10)
+
+
 @pytest.mark.parametrize("n,prec,nb", [(24, "fp64f", 9), (32, "fp32", 5)])
 def test_pair_form_in_a_graph(device, n, prec, nb):
     """Captured once (every buffer sized by an eager call before), replayed on changed inputs with
     eager work between the replays: each replay gives the eager call's bits."""
     import torch
     print(f"[gpu] pair form captured, {n}^3 {prec}", flush=True)
-    plan, nk = make(n, (4, 1, 1), nb, prec)
+    plan, kp = make(n, (4, 1, 1), nb, prec)
+    nk = len(kp)
     u = fields(nk, nb, n, 31)
     out = torch.empty_like(u)
     plan.apply(u, out=out)
