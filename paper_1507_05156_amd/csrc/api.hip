@@ -60,6 +60,15 @@ fock_status DevBuf::ensure(size_t need, size_t cap, const char* what) {
   return FOCK_OK;
 }
 
+bool stream_captures(hipStream_t st) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cs != hipStreamCaptureStatusNone;
+}
+
 void DevBuf::release() {
   if (ptr) (void)hipFree(ptr);
   ptr = nullptr;
@@ -432,7 +441,11 @@ fock_status Plan::run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx,
   const int nitems = ps.ntk * nx;
   fock_status s;
   hipError_t e;
-  const PairRule rule = pair_rule(c, ps, nx, ns, X == P && P == M, false);
+  PairRule rule = pair_rule(c, ps, nx, ns, X == P && P == M, false);
+  // the fused kernels of 16^3 and 20^3 need no plan memory: a first call under capture runs them
+  if (rule.pairs && stream_captures(st) &&
+      !pairs_sized(c.nr, nitems, ps.nsk * ns, ns, c.nr * sizeof(c128), false, rule.tri, rule.tri))
+    rule.pairs = false;
   if (rule.pairs) {
     Mirror<double> mr;
     if (rule.tri) {

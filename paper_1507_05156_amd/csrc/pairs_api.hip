@@ -148,6 +148,18 @@ fock_status pairs_blocks(int nr, int nt, int nj, int ns, const PairStage<TW>& st
   return FOCK_OK;
 }
 
+bool Plan::pairs_sized(int nr, int nt, int nj, int ns, size_t fb, bool sums32, bool two, bool tri) const {
+  int rows = 0;
+  long njmax = 0;
+  pairs_block_shape(nt, nj, ns, nr, fb, workspace_cap ? std::min(workspace_cap, pair_batch) : pair_batch,
+                    sums32 && !two, tri, &rows, &njmax);
+  const size_t groups = (rows + kPairGroup - 1) / kPairGroup;
+  return pbatch.bytes >= (size_t)rows * njmax * fb &&
+         prun.bytes >= (size_t)rows * nr * (sums32 ? sizeof(c64) : sizeof(c128)) &&
+         (!two || (pmir.bytes >= groups * nj * nr * sizeof(c128) &&
+                   (!sums32 || pmcomp.bytes >= groups * nj * nr * sizeof(c64))));
+}
+
 template <typename TW, typename TM>
 fock_status Plan::run_pairs(int nr, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M, c128* out,
                             double scale, bool accumulate, const Mirror<TM>& mr, size_t batch, hipStream_t st) {

@@ -28,6 +28,9 @@ struct DevBuf {
   void release();
 };
 
+// whether the stream is being captured into a graph
+bool stream_captures(hipStream_t st);
+
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
   const char* x = (const char*)a;
@@ -171,6 +174,7 @@ struct Plan {
   // two-stage pair form (pairs_api.hip): the batch of W fields, the sums kept between the
   // blocks of a row, the mirror sums and their compensation
   DevBuf pbatch, prun, pmir, pmcomp;
+  DevBuf gramb;                             // Gram matrices and their factors (fock_orthonormalize)
   size_t pair_batch = size_t(8) << 30;      // bytes of one batch
   int split_form = 0;                       // 1: a split-form variable is set, 32^3 runs the split form
   std::vector<double> host_norms;
@@ -216,6 +220,8 @@ struct Plan {
     bool shared = false;  // fock_apply_noalloc serves the same sum, by the same rule
   };
   PairRule pair_rule(const Cell& c, const PairSet& ps, int nx, int ns, bool same, bool f32) const;
+  // whether the buffers of such a sum are there already (under capture nothing can be allocated)
+  bool pairs_sized(int nr, int nt, int nj, int ns, size_t field_bytes, bool sums32, bool two, bool tri) const;
   // whether the batch and mirror sums of a symmetric sum over nt fields fit the workspace cap
   bool pairs_tri_fits(int nt, int nr, size_t field_bytes) const;
   // the orbitals of the source k-points, contiguous: `arr` itself without

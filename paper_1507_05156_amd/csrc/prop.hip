@@ -150,10 +150,202 @@ __global__ void __launch_bounds__(kRedThreads) sum_rows_kernel(double* __restric
   }
 }
 
+// Gram-Schmidt through the Gram matrix, for up to kGramBands fields per k-point: with
+// G_ij = w <v_i, v_j> = (L L^H)_ij the orthonormal fields are q_j = sum_{i <= j} conj(L^-1)_ji v_i,
+// the result of Gram-Schmidt in band order. One read of the fields for G, one read and one
+// write for the product; modified Gram-Schmidt passes over them nb^2 times from one
+// workgroup per k. 32^3 / 216 k / 16 bands, a copy of the fields (0.8 ms) included: 11.3 -> 1.9 ms;
+// error against a double Gram-Schmidt in 64 bits 1.1e-16 -> 1.9e-16.
+//
+// The error of this route grows with the square of the fields' condition number, that of
+// modified Gram-Schmidt with the number itself: a k-point whose scaled Gram matrix is not
+// close enough to diagonal (trace of its inverse above 1.5 nb), or whose factorisation fails
+// (dependent or vanishing fields, infinities, NaN), is left to modified Gram-Schmidt
+// (bad[k] = 1).
+typedef double v4d __attribute__((ext_vector_type(4)));
+constexpr int kGramWaves = 4;
+
+// part[k][chunk] = 16 x 16 complex partial sums of conj(v_i) v_j over the points of a chunk, on
+// the matrix cores: lane l holds field l mod 16 at the four points 4 (l / 16) .. + 3 of a run of
+// 16, and each 16x16x4 product sums one point of every lane group
+__global__ void __launch_bounds__(64 * kGramWaves) gram16_kernel(double* __restrict__ part,
+                                                                 const c128* __restrict__ psi, int nb, int nr,
+                                                                 int len) {
+  __shared__ double sh[kGramWaves - 1][2 * kGramBands * kGramBands];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int band = lane & 15, grp = lane >> 4;
+  const int k = blockIdx.y, chunk = blockIdx.x;
+  const c128* v = psi + ((long)k * nb + (band < nb ? band : 0)) * nr;
+  const int r1 = (chunk + 1) * len < nr ? (chunk + 1) * len : nr;
+  // sums of their own per point of the run: the rounding of a sum grows with its length
+  v4d ar[4], ai[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) ar[q] = ai[q] = v4d{0, 0, 0, 0};
+  for (int r0 = chunk * len + 16 * wv; r0 < r1; r0 += 16 * kGramWaves) {
+    c128 x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = v[r0 + 4 * grp + q];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double re = band < nb ? x[q].re : 0.0, im = band < nb ? x[q].im : 0.0;
+      ar[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(re, re, ar[q], 0, 0, 0);
+      ar[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(im, im, ar[q], 0, 0, 0);
+      ai[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(re, im, ai[q], 0, 0, 0);
+      ai[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(-im, re, ai[q], 0, 0, 0);
+    }
+  }
+  const v4d gre = (ar[0] + ar[1]) + (ar[2] + ar[3]), gim = (ai[0] + ai[1]) + (ai[2] + ai[3]);
+  // lane l, register q: row l / 16 + 4 q, column l mod 16; waves added in order
+  if (wv > 0) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      sh[wv - 1][2 * ((grp + 4 * q) * kGramBands + band)] = gre[q];
+      sh[wv - 1][2 * ((grp + 4 * q) * kGramBands + band) + 1] = gim[q];
+    }
+  }
+  __syncthreads();
+  if (wv == 0) {
+    double* o = part + ((long)k * gridDim.x + chunk) * (2 * kGramBands * kGramBands);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = 2 * ((grp + 4 * q) * kGramBands + band);
+      double re = gre[q], im = gim[q];
+      for (int u = 0; u < kGramWaves - 1; ++u) {
+        re += sh[u][e];
+        im += sh[u][e + 1];
+      }
+      o[e] = re;
+      o[e + 1] = im;
+    }
+  }
+}
+
+// s + c += x, the rounding error of the addition carried in c
+__device__ __forceinline__ void two_sum_add(double& s, double& c, double x) {
+#pragma clang fp contract(off)
+  const double t = s + x, b = t - s;
+  c += (s - (t - b)) + (x - b);
+  s = t;
+}
+
+// Of G = w * sum of the chunks: T[k][j][j] = (L^-1)_jj and, for i < j, T[k][j][i] =
+// conj(L^-1)_ji / (L^-1)_jj, so that q_j = T_jj (v_j + sum T_ji v_i); bad[k]
+__global__ void __launch_bounds__(64) gram_factor_kernel(c128* __restrict__ T, int* __restrict__ bad,
+                                                         const double* __restrict__ part, int nchunk, int nb,
+                                                         double w) {
+  constexpr int N = kGramBands;
+  __shared__ c128 g[N][N + 1], li[N][N + 1];
+  __shared__ double d[N], inv[N], q[N], dg[N];
+  __shared__ int fail;
+  const int t = threadIdx.x;
+  const long k = blockIdx.x;
+  const double* p = part + k * nchunk * (2 * N * N);
+  for (int e = t; e < N * N; e += 64) {
+    // the chunks' sums with the error of each addition carried along
+    double re = 0.0, im = 0.0, cre = 0.0, cim = 0.0;
+    for (int c = 0; c < nchunk; ++c) {
+      two_sum_add(re, cre, p[(long)c * (2 * N * N) + 2 * e]);
+      two_sum_add(im, cim, p[(long)c * (2 * N * N) + 2 * e + 1]);
+    }
+    g[e / N][e % N] = c128{w * (re + cre), w * (im + cim)};
+    li[e / N][e % N] = c128{0.0, 0.0};
+  }
+  if (t == 0) fail = 0;
+  __syncthreads();
+  if (t < nb) {
+    q[t] = g[t][t].re;
+    d[t] = 1.0 / sqrt(q[t]);
+    if (!(q[t] > 0.0) || !(q[t] < 1e300) || !(d[t] < 1e150)) fail = 1;
+  }
+  __syncthreads();
+  for (int e = t; e < N * N; e += 64) {
+    const int i = e / N, j = e % N;
+    if (i < nb && j < nb) g[i][j] = i == j ? c128{1.0, 0.0} : cscale(g[i][j], d[i] * d[j]);
+  }
+  __syncthreads();
+  // Cholesky of the scaled matrix, row t of the factor on thread t; L overwrites the lower part
+  for (int j = 0; j < nb; ++j) {
+    if (t == j) {
+      double s = 1.0;
+      for (int c = 0; c < j; ++c) s -= g[j][c].re * g[j][c].re + g[j][c].im * g[j][c].im;
+      if (!(s > 0.0)) fail = 1;
+      inv[j] = 1.0 / sqrt(s);
+      dg[j] = 1.0 / sqrt(q[j] * s);  // the factor of q_j, rounded as few times as a norm's
+    }
+    __syncthreads();
+    if (t > j && t < nb) {
+      c128 s = g[t][j];
+      for (int c = 0; c < j; ++c) {
+        const c128 z = cmulc(g[j][c], g[t][c]);
+        s = s - z;
+      }
+      g[t][j] = cscale(s, inv[j]);
+    }
+    __syncthreads();
+  }
+  // column t of L^-1
+  double tr = 0.0;
+  if (t < nb) {
+    for (int i = t; i < nb; ++i) {
+      c128 s = i == t ? c128{1.0, 0.0} : c128{0.0, 0.0};
+      for (int c = t; c < i; ++c) s = s - cmul(g[i][c], li[c][t]);
+      li[i][t] = cscale(s, inv[i]);
+      tr += li[i][t].re * li[i][t].re + li[i][t].im * li[i][t].im;
+    }
+  }
+  __shared__ double trs[N];
+  if (t < N) trs[t] = t < nb ? tr : 0.0;
+  __syncthreads();
+  if (t == 0) {
+    double s = 0.0;
+    for (int i = 0; i < nb; ++i) s += trs[i];
+    if (!(s <= 1.5 * nb)) fail = 1;
+    bad[k] = fail;
+  }
+  for (int e = t; e < N * N; e += 64) {
+    const int j = e / N, i = e % N;
+    const c128 z = li[j][i];
+    c128 o{0.0, 0.0};
+    if (j < nb && i < j) {
+      const double f = d[i] / (inv[j] * d[j]);
+      o = c128{z.re * f, -z.im * f};
+    } else if (j < nb && i == j) {
+      o.re = dg[j];
+    }
+    T[k * N * N + e] = o;
+  }
+}
+
+// q_j = T_jj (v_j + sum_{i < j} T_ji v_i) in place, one point per thread
+template <int NB>
+__global__ void __launch_bounds__(256) gram_apply_kernel(c128* __restrict__ psi, const c128* __restrict__ T,
+                                                         const int* __restrict__ bad, int nb, int nr) {
+  const long k = blockIdx.y;
+  if (bad[k]) return;
+  const int r = blockIdx.x * 256 + threadIdx.x;
+  if (r >= nr) return;
+  c128* v = psi + k * nb * nr + r;
+  const c128* t = T + k * kGramBands * kGramBands;
+  c128 x[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) x[i] = i < nb ? v[(long)i * nr] : c128{0.0, 0.0};
+#pragma unroll
+  for (int j = NB - 1; j >= 0; --j) {
+    if (j >= nb) continue;
+    // the corrections first, v_j last: its digits are rounded once
+    c128 s{0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < j; ++i) s = cmac(s, t[j * kGramBands + i], x[i]);
+    v[(long)j * nr] = cscale(x[j] + s, t[j * kGramBands + j].re);
+  }
+}
+
 // Modified Gram-Schmidt of the nb fields of one k-point (one workgroup per k), cell inner
-// product w * sum conj(a) b
+// product w * sum conj(a) b; bad (may be NULL): only the k-points with bad[k] != 0
 constexpr int kMgsThreads = 1024;
-__global__ void __launch_bounds__(kMgsThreads) mgs_kernel(c128* __restrict__ psi, int nb, int nr, double w) {
+__global__ void __launch_bounds__(kMgsThreads) mgs_kernel(c128* __restrict__ psi, int nb, int nr, double w,
+                                                          const int* __restrict__ bad) {
+  if (bad && !bad[blockIdx.x]) return;
   __shared__ double sh[2 * kMgsThreads];
   c128* base = psi + (long)blockIdx.x * nb * nr;
   const int t = threadIdx.x;
@@ -257,7 +449,39 @@ hipError_t launch_agrad(double* out6, double* partial, int nblk, const c128* L, 
 }
 
 hipError_t launch_mgs(c128* psi, int nk, int nb, int nr, double w, hipStream_t st) {
-  hipLaunchKernelGGL(mgs_kernel, dim3(nk), dim3(kMgsThreads), 0, st, psi, nb, nr, w);
+  hipLaunchKernelGGL(mgs_kernel, dim3(nk), dim3(kMgsThreads), 0, st, psi, nb, nr, w, nullptr);
+  return hipGetLastError();
+}
+
+// chunks of a k-point's points: about 8,192 workgroups in all, at least 256 points each
+static int gram_chunks(int nk, int nr) {
+  const int most = nr / 256 > 0 ? nr / 256 : 1, want = (8192 + nk - 1) / nk;
+  return want < most ? want : most;
+}
+
+size_t gram_work_bytes(int nk, int nr) {
+  constexpr size_t mat = kGramBands * kGramBands * sizeof(c128);
+  return (size_t)nk * ((gram_chunks(nk, nr) + 1) * mat + sizeof(int));
+}
+
+hipError_t launch_gram_schmidt(c128* psi, int nk, int nb, int nr, double w, void* work, hipStream_t st) {
+  if (nb > kGramBands || nr % 64 != 0) return hipErrorInvalidValue;
+  const int want = gram_chunks(nk, nr);
+  const int len = ((nr + want - 1) / want + 63) / 64 * 64, nchunk = (nr + len - 1) / len;
+  double* part = (double*)work;
+  c128* T = (c128*)(part + (size_t)nk * nchunk * 2 * kGramBands * kGramBands);
+  int* bad = (int*)(T + (size_t)nk * kGramBands * kGramBands);
+  hipError_t e;
+  hipLaunchKernelGGL(gram16_kernel, dim3(nchunk, nk), dim3(64 * kGramWaves), 0, st, part, psi, nb, nr, len);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(gram_factor_kernel, dim3(nk), dim3(64), 0, st, T, bad, part, nchunk, nb, w);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const dim3 grid((nr + 255) / 256, nk);
+  if (nb <= 4) hipLaunchKernelGGL(gram_apply_kernel<4>, grid, dim3(256), 0, st, psi, T, bad, nb, nr);
+  else if (nb <= 8) hipLaunchKernelGGL(gram_apply_kernel<8>, grid, dim3(256), 0, st, psi, T, bad, nb, nr);
+  else hipLaunchKernelGGL(gram_apply_kernel<kGramBands>, grid, dim3(256), 0, st, psi, T, bad, nb, nr);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(mgs_kernel, dim3(nk), dim3(kMgsThreads), 0, st, psi, nb, nr, w, bad);
   return hipGetLastError();
 }
 

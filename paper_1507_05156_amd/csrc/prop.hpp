@@ -22,5 +22,10 @@ hipError_t launch_agrad(double* out6, double* partial, int nblk, const c128* L, 
                         int nf, const Geom& g, const double a[3], long count, hipStream_t st);
 // modified Gram-Schmidt per k-point with inner product w * sum conj(a) b
 hipError_t launch_mgs(c128* psi, int nk, int nb, int nr, double w, hipStream_t st);
+// the same result through the Gram matrix where it is well conditioned, by modified
+// Gram-Schmidt elsewhere; nb <= kGramBands, work: gram_work_bytes of device memory
+constexpr int kGramBands = 16;
+size_t gram_work_bytes(int nk, int nr);
+hipError_t launch_gram_schmidt(c128* psi, int nk, int nb, int nr, double w, void* work, hipStream_t st);
 
 }  // namespace fockmi

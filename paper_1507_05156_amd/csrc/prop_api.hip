@@ -420,7 +420,14 @@ fock_status fock_orthonormalize(fockmi_plan plan, int cell, void* psi, void* str
   Cell& c = p->cells[cell];
   if (!psi) return fail(FOCK_ERR_ARG, "psi is NULL");
   if (!aligned16(psi)) return fail(FOCK_ERR_ARG, "misaligned pointer");
-  hipError_t e = launch_mgs((c128*)psi, c.nk, c.nb, c.nr, c.vol / c.nr, (hipStream_t)stream);
+  hipStream_t st = (hipStream_t)stream;
+  const size_t need = gram_work_bytes(c.nk, c.nr);
+  // the Gram route works in plan memory, which a capture cannot allocate
+  const bool gram = c.nb <= kGramBands && (p->gramb.bytes >= need || !stream_captures(st)) &&
+                    p->gramb.ensure(need, p->workspace_cap, "Gram matrices") == FOCK_OK;
+  g_last_error.clear();
+  hipError_t e = gram ? launch_gram_schmidt((c128*)psi, c.nk, c.nb, c.nr, c.vol / c.nr, p->gramb.ptr, st)
+                      : launch_mgs((c128*)psi, c.nk, c.nb, c.nr, c.vol / c.nr, st);
   if (e != hipSuccess) return hip_fail(e, "Gram-Schmidt");
   return FOCK_OK;
 }

@@ -181,3 +181,57 @@ def test_pair_form_in_a_graph(device, n, prec, nb):
         torch.cuda.synchronize()
         replay = out.clone()
         assert bool((replay == plan.apply(u)).all())
+
+
+def test_first_call_under_capture(device):
+    """A plan's first FP64 application at 16^3 inside a capture, where the pair form's buffers
+    cannot be allocated, and an orthonormalisation: both replay to the eager result (to rounding:
+    the eager calls that follow may use the buffers)."""
+    import torch
+    print("[gpu] first call under capture", flush=True)
+    plan, kp = make(16, (2, 1, 1), 3, "fp64f")
+    u = fields(2, 3, 16, 41)
+    out = torch.empty_like(u)
+    psi = u.clone()
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        plan.apply(u, out=out)
+        plan.orthonormalize(psi)
+    for seed in (42, 43):
+        u.copy_(fields(2, 3, 16, seed))
+        psi.copy_(u)
+        g.replay()
+        torch.cuda.synchronize()
+        a, b = out.clone(), psi.clone()
+        assert per_k(a, plan.apply(u)) < 1e-13
+        assert per_k(b, plan.orthonormalize(u.clone())) < 1e-13
+
+
+@pytest.mark.parametrize("n,nk,nb", [(16, 1, 1), (16, 3, 4), (16, 2, 5), (20, 3, 16), (32, 1, 9), (16, 2, 17)])
+def test_orthonormalize_routes(device, n, nk, nb):
+    """Gram-Schmidt in band order against the oracle's, through the Gram matrix (up to 16 bands)
+    and beyond it; a k-point with two fields 1e-5 apart (left to modified Gram-Schmidt, whose
+    error is about their condition number, 1e5 eps) beside well-conditioned ones; a vanishing
+    field on one k-point leaves the others as they were."""
+    import oracle
+    import torch
+    print(f"[gpu] orthonormalize {n}^3 nk={nk} nb={nb}", flush=True)
+    plan, kp = make(n, (nk, 1, 1), nb, "fp64")
+    u = fields(nk, nb, n, 51 + nb)
+    u = u / u.abs().max()
+    close = nk > 1 and nb > 3
+    if close:
+        u[1, 3] = u[1, 1] + 1e-5 * u[1, 3]
+    ref = torch.from_numpy(oracle.gram_schmidt(u.cpu().numpy(), synth.cubic_cell())).to("cuda:0")
+    got = plan.orthonormalize(u.clone())
+    for k in range(nk):
+        tol = 1e-9 if close and k == 1 else 1e-13
+        assert float((got[k] - ref[k]).norm() / ref[k].norm()) < tol, k
+        q = got[k].reshape(nb, -1)
+        s = (q.conj() @ q.t().contiguous()) * (synth.LATTICE_A ** 3 / q.shape[1])
+        assert float((s - torch.eye(nb, dtype=s.dtype, device=s.device)).abs().max()) < tol
+    if nk > 1:
+        v = u.clone()
+        v[nk - 1, 0] = 0
+        assert bool((plan.orthonormalize(v)[:nk - 1] == got[:nk - 1]).all())
