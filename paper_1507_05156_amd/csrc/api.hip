@@ -108,12 +108,12 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
     if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
     if (c.f32plain)
       s = run_pairs<float, double>(
-          nr, nt, nj, ns, plane_stage<float>(c.geom, num_cus, ps, X, nx, P, ns, (const double*)c.Kpl.ptr, st), M, out,
+          nr, 0, nt, nj, ns, plane_stage<float>(c.geom, num_cus, ps, X, nx, P, ns, (const double*)c.Kpl.ptr, st), M, out,
           scale, accumulate, mr, batch, st);
     else
       s = run_pairs<double, double>(
-          nr, nt, nj, ns,
-          cube ? cube_stage<double>(c.geom.n1, num_cus, ps, X, nx, P, ns, (const double*)c.Kt64.ptr, st)
+          nr, 0, nt, nj, ns,
+          cube ? cube_stage<double>(c.geom.n1, num_cus, ps, X, nx, P, ns, (const double*)c.Kp.ptr, st)
                : plane_stage<double>(c.geom, num_cus, ps, X, nx, P, ns, (const double*)c.Kpl.ptr, st),
           M, out, scale, accumulate, mr, batch, st);
     if (s != FOCK_OK) return s;
@@ -153,11 +153,12 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
   return run((size_t)bmb << 20);
 }
 
-fock_status Plan::shadow(DevBuf& buf, const c128* src, size_t count, const char* what, hipStream_t st,
+fock_status Plan::shadow(DevBuf& buf, const c128* src, size_t count, const char* what, hipStream_t st, int np,
                          const c64** out) {
   fock_status s = buf.ensure(count * sizeof(c64), workspace_cap, what);
   if (s != FOCK_OK) return s;
-  hipError_t e = launch_to_c64((c64*)buf.ptr, src, (long)count, st);
+  hipError_t e = np ? launch_to_c64_paired((c64*)buf.ptr, src, (long)count, np, st)
+                    : launch_to_c64((c64*)buf.ptr, src, (long)count, st);
   if (e != hipSuccess) return hip_fail(e, what);
   *out = (const c64*)buf.ptr;
   return FOCK_OK;
@@ -168,20 +169,28 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   const int nr = c.nr;
   const c64 *Xs = nullptr, *Ps = nullptr, *Ms = nullptr;
   fock_status s;
-  if ((s = shadow(shadow_p, P, (size_t)ps.nsk * ns * nr, "complex64 shadow (P)", st, &Ps)) != FOCK_OK) return s;
-  if (M == P) {
-    Ms = Ps;
-  } else if ((s = shadow(shadow_m, M, (size_t)ps.nsk * ns * nr, "complex64 shadow (M)", st, &Ms)) != FOCK_OK) {
-    return s;
-  }
-  const bool same_k = ps.ntk == ps.nsk && nx == ns;  // then X may share a source array's shadow
-  if (same_k && X == P) {
-    Xs = Ps;
-  } else if (same_k && X == M) {
-    Xs = Ms;
-  } else if ((s = shadow(shadow_x, X, (size_t)ps.ntk * nx * nr, "complex64 shadow (X)", st, &Xs)) != FOCK_OK) {
-    return s;
-  }
+  // the complex64 shadows, in natural order or in the pair form's
+  int shadow_np = -1;
+  auto shadows = [&](int np) -> fock_status {
+    fock_status st2;
+    if (np == shadow_np) return FOCK_OK;
+    if ((st2 = shadow(shadow_p, P, (size_t)ps.nsk * ns * nr, "complex64 shadow (P)", st, np, &Ps)) != FOCK_OK) return st2;
+    if (M == P) {
+      Ms = Ps;
+    } else if ((st2 = shadow(shadow_m, M, (size_t)ps.nsk * ns * nr, "complex64 shadow (M)", st, np, &Ms)) != FOCK_OK) {
+      return st2;
+    }
+    const bool same_k = ps.ntk == ps.nsk && nx == ns;  // then X may share a source array's shadow
+    if (same_k && X == P) {
+      Xs = Ps;
+    } else if (same_k && X == M) {
+      Xs = Ms;
+    } else if ((st2 = shadow(shadow_x, X, (size_t)ps.ntk * nx * nr, "complex64 shadow (X)", st, np, &Xs)) != FOCK_OK) {
+      return st2;
+    }
+    shadow_np = np;
+    return FOCK_OK;
+  };
   const int nitems = ps.ntk * nx;
   const int n = c.geom.n1;
   // the lockstep form runs one workgroup per CU (a multiple of 8: one share per XCD)
@@ -231,9 +240,6 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
     }
   }
   FusedArgs a{};
-  a.X = Xs;
-  a.P = Ps;
-  a.M = Ms;
   a.Kt = (const float*)c.Kt.ptr;
   a.qidx = ps.qidx;
   a.out = out;
@@ -252,6 +258,10 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   // buffers of one variant (grown on demand, kept by the plan)
   auto prepare = [&](int v) -> fock_status {
     fock_status st2;
+    if ((st2 = shadows(v == 3 ? n * n : 0)) != FOCK_OK) return st2;
+    a.X = Xs;
+    a.P = Ps;
+    a.M = Ms;
     if (v == 3) return FOCK_OK;  // run_pairs sizes its own buffers
     const int h = v == 1 ? ksplit : 1;
     if ((st2 = comp.ensure((size_t)h * nitems * nr * sizeof(c64), workspace_cap, "compensation buffer")) != FOCK_OK)
@@ -328,8 +338,8 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
         mr.tri = true;
       }
       pairs_status = run_pairs<float, float>(
-          nr, nitems, ps.nsk * ns, ns, cube_stage<float>(n, num_cus, ps, Xs, nx, Ps, ns, (const float*)c.Kt.ptr, st), Ms,
-          out, scale, accumulate, mr, pair_batch, st);
+          nr, n * n, nitems, ps.nsk * ns, ns,
+          cube_stage<float>(n, num_cus, ps, Xs, nx, Ps, ns, (const float*)c.Kp.ptr, st), Ms, out, scale, accumulate, mr, pair_batch, st);
       return hipSuccess;
     }
     if (v != 2) return launch_fused_apply(n, a, st, v, &ls);
@@ -456,8 +466,8 @@ fock_status Plan::run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx,
     }
     if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
     if ((s = run_pairs<double, double>(
-             c.nr, nitems, ps.nsk * ns, ns,
-             cube_stage<double>(c.geom.n1, num_cus, ps, X, nx, P, ns, (const double*)c.Kt64.ptr, st), M, out, scale,
+             c.nr, 0, nitems, ps.nsk * ns, ns,
+             cube_stage<double>(c.geom.n1, num_cus, ps, X, nx, P, ns, (const double*)c.Kp.ptr, st), M, out, scale,
              accumulate, mr, pair_batch, st)) != FOCK_OK)
       return s;
     if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");

@@ -137,6 +137,9 @@ size_t fused64_acc_scratch_elems(int n, int nslots);  // c128 elements needed in
 hipError_t launch_fused64_apply(int n, const Fused64Args& a, hipStream_t st);
 // FP64 copy of the tables in the fused FP64 kernel's layout (nph rounds)
 hipError_t launch_build_table_fused64(double* Kt, const double* K, int nq, int n, int nph, hipStream_t st);
+// the same orders with 16 bytes of values of one thread side by side (the pair kernel's tables)
+hipError_t launch_build_table_pair32(float* Kp, const double* K, int nq, int n, hipStream_t st);
+hipError_t launch_build_table_pair64(double* Kp, const double* K, int nq, int n, int nph, hipStream_t st);
 
 // Persistent launch over several cells: nwg workgroups of nthreads pop entries
 // (queue[3i] = cell, queue[3i+1] = target item, queue[3i+2] = a second target
@@ -156,6 +159,8 @@ hipError_t launch_fused_batched(const BatchArgs& b, int nthreads, int nwg, hipSt
 
 // ---- helpers ---------------------------------------------------------------
 hipError_t launch_to_c64(c64* dst, const c128* src, long count, hipStream_t st);
+// the same values with points m1 = 2h, 2h + 1 side by side (the pair form's order); np = n2 * n3
+hipError_t launch_to_c64_paired(c64* dst, const c128* src, long count, int np, hipStream_t st);
 // partial[4b..4b+3] for b < nblk, then dst[0..3] = sum conj(a) b as double-double
 // (re.hi, re.lo, im.hi, im.lo), fixed order
 hipError_t launch_dot(double* dst, double* partial, int nblk, const c128* a, const c128* b, long count,

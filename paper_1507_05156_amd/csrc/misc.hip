@@ -12,6 +12,17 @@ __global__ void to_c64_kernel(c64* __restrict__ dst, const c128* __restrict__ sr
   }
 }
 
+// The pair form's order: points m1 = 2h, 2h + 1 of a line along n1 side by side, element
+// (h, pos, b) of a field at (h * np + pos) * 2 + b; np = n2 * n3
+__global__ void to_c64_paired_kernel(c64* __restrict__ dst, const c128* __restrict__ src, long pairs, int np) {
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < pairs; i += (long)gridDim.x * blockDim.x) {
+    const c128* p = src + i / np * 2 * np + i % np;  // i = (field * n1/2 + h) * np + pos
+    const c128 a = p[0], b = p[np];
+    *(v4*)(dst + 2 * i) = v4{(float)a.re, (float)a.im, (float)b.re, (float)b.im};
+  }
+}
+
 constexpr int kDotThreads = 256;
 
 // Double-double accumulation (hi + lo, |lo| <= ulp(hi)/2): x is added to hi with an
@@ -128,6 +139,11 @@ unsigned grid_for(long count, int bs) {
 
 hipError_t launch_to_c64(c64* dst, const c128* src, long count, hipStream_t st) {
   hipLaunchKernelGGL(to_c64_kernel, dim3(grid_for(count, 256)), dim3(256), 0, st, dst, src, count);
+  return hipGetLastError();
+}
+
+hipError_t launch_to_c64_paired(c64* dst, const c128* src, long count, int np, hipStream_t st) {
+  hipLaunchKernelGGL(to_c64_paired_kernel, dim3(grid_for(count / 2, 256)), dim3(256), 0, st, dst, src, count / 2, np);
   return hipGetLastError();
 }
 

@@ -113,26 +113,31 @@ extern "C" fock_status fock_apply_noalloc(fockmi_plan plan, int cell, const void
   c64* sx = x_is_u ? su : (c64*)(sp + o_x);
   hipStream_t st = (hipStream_t)stream;
   hipError_t e;
+  const bool pairs = c.geom.n1 <= 24 && p->pair_rule(c, ps, nphi, c.nb, x_is_u, true).pairs;
+  const int np = c.geom.n2 * c.geom.n3;
+  auto convert = [&](c64* dst, const c128* src, long count) {
+    return pairs ? launch_to_c64_paired(dst, src, count, np, st) : launch_to_c64(dst, src, count, st);
+  };
   // shadows: the source k-points' orbitals (gathered from S when down-sampled), then the targets
   const c128* U = (const c128*)u_occ;
   if (!c.ds) {
-    if ((e = launch_to_c64(su, U, (long)ps.nsk * (long)blk, st)) != hipSuccess) return hip_fail(e, "complex64 shadow (u)");
+    if ((e = convert(su, U, (long)ps.nsk * (long)blk)) != hipSuccess) return hip_fail(e, "complex64 shadow (u)");
   } else {
     for (int i = 0; i < ps.nsk; ++i)
-      if ((e = launch_to_c64(su + (size_t)i * blk, U + (size_t)c.src[i] * blk, (long)blk, st)) != hipSuccess)
+      if ((e = convert(su + (size_t)i * blk, U + (size_t)c.src[i] * blk, (long)blk)) != hipSuccess)
         return hip_fail(e, "complex64 shadow (u)");
   }
-  if (!x_is_u && (e = launch_to_c64(sx, (const c128*)phi, (long)nitems * c.nr, st)) != hipSuccess)
+  if (!x_is_u && (e = convert(sx, (const c128*)phi, (long)nitems * c.nr)) != hipSuccess)
     return hip_fail(e, "complex64 shadow (phi)");
-  if (c.geom.n1 <= 24 && p->pair_rule(c, ps, nphi, c.nb, x_is_u, true).pairs) {
+  if (pairs) {
     // the sums kept between blocks take the compensation's place, the batch what is left
     const size_t fb = (size_t)c.nr * sizeof(c64);
     int rows = 0;
     long njmax = 0;
     pairs_block_shape(nitems, ps.nsk * c.nb, c.nb, c.nr, fb, kNoAllocBytes - o_a, true, false, &rows, &njmax);
     return pairs_blocks<float, float>(
-        c.nr, nitems, ps.nsk * c.nb, c.nb,
-        cube_stage<float>(c.geom.n1, p->num_cus, ps, sx, nphi, su, c.nb, (const float*)c.Kt.ptr, st), su,
+        c.nr, np, nitems, ps.nsk * c.nb, c.nb,
+        cube_stage<float>(c.geom.n1, p->num_cus, ps, sx, nphi, su, c.nb, (const float*)c.Kp.ptr, st), su,
         Mirror<float>{}, (c128*)vphi, -1.0 / c.nsrc, false, rows, njmax, (c64*)(sp + o_a), sp + o_c, nullptr, nullptr,
         st);
   }

@@ -16,18 +16,52 @@
 // field per CU cannot overlap), stage 2 by the one read of W. 32^3 / 216 k / 16 bands, FP32:
 // 1,732 ms per application with every pair of k-points pushed between CU pairs (split32.hip),
 // 1,270 ms in this form with plain W accesses, 1,142 ms with non-temporal ones, 1,088 ms with
-// the next pair's first operands loaded before the stores. One of eight k-point shards of it
-// (one-sided sums): 284.6 -> 247 ms.
+// the next pair's first operands loaded before the stores, 1,076 ms with every access of stage 1
+// 16 bytes wide (stage 1 at 24^3 in FP32: 50.8 -> 45.1 ns per pair). One of eight k-point shards
+// of it (one-sided sums): 284.6 -> 241 ms.
 #include "pairs_dev.hpp"
 
 namespace fockmi {
 
 namespace {
 
-__device__ __forceinline__ cx<float> ld_cx(rsrc_t r, unsigned vo, unsigned so, float) { return ld_c64(r, vo, so); }
-__device__ __forceinline__ cx<double> ld_cx(rsrc_t r, unsigned vo, unsigned so, double) { return ld_c128(r, vo, so); }
-__device__ __forceinline__ float ld_re(rsrc_t r, unsigned vo, unsigned so, float) { return ld_f32(r, vo, so); }
-__device__ __forceinline__ double ld_re(rsrc_t r, unsigned vo, unsigned so, double) { return ld_f64(r, vo, so); }
+// Every access moves 16 bytes per lane: 8-byte ones take as many cycles of the L1 for half the
+// data, and the kernel's operands, tables and W (900 KiB per pair of 32^3 in FP32) are what the
+// transforms do not hide. points 2h and 2h + 1 of a line along n1:
+template <int NTI>
+__device__ __forceinline__ void ld_two(rsrc_t r, unsigned t, int h, cx<float>* v) {
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  const v4 q = __builtin_bit_cast(v4, __builtin_amdgcn_raw_buffer_load_b128(r, t * 16u, (unsigned)(h * NTI * 16), 0));
+  v[0] = {q.x, q.y};
+  v[1] = {q.z, q.w};
+}
+template <int NTI>
+__device__ __forceinline__ void ld_two(rsrc_t r, unsigned t, int h, cx<double>* v) {
+  v[0] = ld_c128(r, t * 16u, (unsigned)(2 * h * NTI * 16));
+  v[1] = ld_c128(r, t * 16u, (unsigned)((2 * h + 1) * NTI * 16));
+}
+template <int NTI>
+__device__ __forceinline__ void st_two(cx<float>* w, unsigned t, int h, const cx<float>* v) {
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  __builtin_nontemporal_store(v4{v[0].re, v[0].im, v[1].re, v[1].im}, (v4*)((char*)w + h * (NTI * 16) + t * 16u));
+}
+template <int NTI>
+__device__ __forceinline__ void st_two(cx<double>* w, unsigned t, int h, const cx<double>* v) {
+  st_w((cx<double>*)((char*)w + 2 * h * (NTI * 16) + t * 16u), v[0]);
+  st_w((cx<double>*)((char*)w + (2 * h + 1) * (NTI * 16) + t * 16u), v[1]);
+}
+// 16 bytes of table values of the thread
+template <int NTI>
+__device__ __forceinline__ void ld_tab(rsrc_t r, unsigned t, int g, float* k) {
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  const v4 q = __builtin_bit_cast(v4, __builtin_amdgcn_raw_buffer_load_b128(r, t * 16u, (unsigned)(g * NTI * 16), 0));
+  k[0] = q.x, k[1] = q.y, k[2] = q.z, k[3] = q.w;
+}
+template <int NTI>
+__device__ __forceinline__ void ld_tab(rsrc_t r, unsigned t, int g, double* k) {
+  const cx<double> q = ld_c128(r, t * 16u, (unsigned)(g * NTI * 16));
+  k[0] = q.re, k[1] = q.im;
+}
 
 // rounds of a transpose through LDS and the LDS elements they need
 template <int N, int NPH>
@@ -83,8 +117,7 @@ __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE)
   const unsigned ly0 = INPLACE ? (unsigned)((chi * N * (N + 1) + hl) * E) : (unsigned)((chi * N * H + hl) * E);
   const unsigned lyz0 = (unsigned)((lrow * N * (N + 1) + clo) * E);
   const unsigned lz0 = (unsigned)((lrow * N + clo) * (N + 1) * E);
-  const unsigned voff = (unsigned)((chi * N + clo) * E);
-  const unsigned voff_t = (unsigned)(t * (int)sizeof(T));
+  const unsigned pos = (unsigned)(chi * N + clo);
   constexpr unsigned FB = (unsigned)NR * E;
 
   PairWalk walk(a.b);
@@ -97,10 +130,10 @@ __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE)
   cx<T> fp[PF], fx[PF];
   auto fetch = [&] {
     const rsrc_t rX = res_x(), rP = res_p();
-    static_for<PF>([&](auto e) {
-      const unsigned so = (unsigned)(decltype(e)::value * NTI * E);
-      fp[e] = ld_cx(rP, voff, so, T{});
-      fx[e] = ld_cx(rX, voff, so, T{});
+    static_for<PF / 2>([&](auto e) {
+      constexpr int H = decltype(e)::value;
+      ld_two<NTI>(rP, pos, H, fp + 2 * H);
+      ld_two<NTI>(rX, pos, H, fx + 2 * H);
     });
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -112,13 +145,15 @@ __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE)
     const rsrc_t rK = make_rsrc(a.Kt + (long)qi * NR, NR * (unsigned)sizeof(T));
     cx<T> v[N];
     constexpr int G = pw_grp_px<N, T>(), NG = (N - PF + G - 1) / G;
+    if constexpr (NG == 0) static_for<PF>([&](auto e) { v[decltype(e)::value] = cmulc(fp[e], fx[e]); });
     static_for<NG>([&](auto cc) {
       constexpr int C0 = PF + decltype(cc)::value * G, CN = (N - C0 < G) ? N - C0 : G;
       cx<T> p[CN], xx[CN];
-      static_for<CN>([&](auto e) {
-        const unsigned so = (unsigned)((C0 + decltype(e)::value) * NTI * E);
-        p[e] = ld_cx(rP, voff, so, T{});
-        xx[e] = ld_cx(rX, voff, so, T{});
+      static_assert(PF % 2 == 0 && CN % 2 == 0, "points go in twos");
+      static_for<CN / 2>([&](auto e) {
+        constexpr int H = decltype(e)::value;
+        ld_two<NTI>(rP, pos, C0 / 2 + H, p + 2 * H);
+        ld_two<NTI>(rX, pos, C0 / 2 + H, xx + 2 * H);
       });
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (decltype(cc)::value == 0) static_for<PF>([&](auto e) { v[decltype(e)::value] = cmulc(fp[e], fx[e]); });
@@ -162,7 +197,9 @@ __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE)
     static_for<(N + pw_grp_k<N, T>() - 1) / pw_grp_k<N, T>()>([&](auto cc) {
       constexpr int G = pw_grp_k<N, T>(), C0 = decltype(cc)::value * G, CN = (N - C0 < G) ? N - C0 : G;
       T kv[CN];
-      static_for<CN>([&](auto e) { kv[e] = ld_re(rK, voff_t, (unsigned)((C0 + decltype(e)::value) * NTI * (int)sizeof(T)), T{}); });
+      constexpr int V = 16 / (int)sizeof(T);
+      static_assert(C0 % V == 0 && CN % V == 0, "table values go 16 bytes at a time");
+      static_for<CN / V>([&](auto e) { ld_tab<NTI>(rK, (unsigned)t, C0 / V + decltype(e)::value, kv + V * decltype(e)::value); });
       __builtin_amdgcn_sched_barrier(0);
       static_for<CN>([&](auto e) { v[C0 + decltype(e)::value] = cscale(v[C0 + decltype(e)::value], kv[e]); });
     });
@@ -201,10 +238,10 @@ __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE)
       if constexpr (!INPLACE) __syncthreads();
     }
     fft<N, +1>(v);
-    char* w = (char*)(a.W + ((long)walk.j * a.b.nt + walk.ti) * NR);
+    cx<T>* w = a.W + ((long)walk.j * a.b.nt + walk.ti) * NR;
     const bool more = walk.next();
     if (more) fetch();
-    static_for<N>([&](auto m1) { st_w((cx<T>*)(w + decltype(m1)::value * (NTI * E) + voff), v[m1]); });
+    static_for<N / 2>([&](auto h) { st_two<NTI>(w, pos, decltype(h)::value, v + 2 * decltype(h)::value); });
     if (!more) return;
   }
 }
@@ -240,6 +277,7 @@ __global__ void __launch_bounds__(64 * NW) wsum_kernel(WsumArgs<TW, T> a) {
   const int n = left < 0 ? 0 : (left < TI ? left : TI);
   const long nr = a.nr;
   const long tg0 = (long)(a.t0 + tile * TI);  // first target of this wave
+  const int rn = natural_index(r, a.np);      // where the outputs hold this point
 
   cx<T> f[TWO ? TI : 1];
   cx<T> acc[TI];
@@ -250,7 +288,7 @@ __global__ void __launch_bounds__(64 * NW) wsum_kernel(WsumArgs<TW, T> a) {
     acc[I] = cx<T>{0, 0};
     if constexpr (TWO) f[I] = I < n ? a.F[(tg0 + I) * nr + r] : cx<T>{0, 0};
     if constexpr (F32) {
-      s[I] = (I < n && (!a.first || a.accumulate)) ? a.out[(tg0 + I) * nr + r] : c128{0.0, 0.0};
+      s[I] = (I < n && (!a.first || a.accumulate)) ? a.out[(tg0 + I) * nr + rn] : c128{0.0, 0.0};
       c[I] = (I < n && !a.first) ? a.comp[(tg0 + I) * nr + r] : cx<float>{0.0f, 0.0f};
     } else {
       if (I < n && !a.first) acc[I] = a.run[(tg0 + I) * nr + r];
@@ -332,14 +370,14 @@ __global__ void __launch_bounds__(64 * NW) wsum_kernel(WsumArgs<TW, T> a) {
   static_for<TI>([&](auto i) {
     constexpr int I = decltype(i)::value;
     if (I < n) {
-      const long o = (tg0 + I) * nr + r;
+      const long o = (tg0 + I) * nr + r, on = (tg0 + I) * nr + rn;
       if constexpr (F32) {
-        a.out[o] = a.last ? c128{s[I].re + (double)c[I].re, s[I].im + (double)c[I].im} : s[I];
+        a.out[on] = a.last ? c128{s[I].re + (double)c[I].re, s[I].im + (double)c[I].im} : s[I];
         if (!a.last) a.comp[o] = c[I];
       } else if (a.last) {
         c128 v = cscale(acc[I], a.scale);
-        if (a.accumulate) v = a.out[o] + v;
-        a.out[o] = v;
+        if (a.accumulate) v = a.out[on] + v;
+        a.out[on] = v;
       } else {
         a.run[o] = acc[I];
       }
@@ -353,7 +391,8 @@ __global__ void __launch_bounds__(64 * NW) wsum_kernel(WsumArgs<TW, T> a) {
 template <bool F32>
 __global__ void __launch_bounds__(256) mirror_add_kernel(c128* __restrict__ dst, const c128* __restrict__ mir,
                                                          const cx<float>* __restrict__ mcomp, double scale,
-                                                         int accumulate, int nsrc, int nr, int rows, int tri) {
+                                                         int accumulate, int nsrc, int nr, int rows, int tri,
+                                                         int np) {
   const long count = (long)nsrc * nr;
   for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < count; i += (long)gridDim.x * 256) {
     int in_row = rows;
@@ -362,7 +401,8 @@ __global__ void __launch_bounds__(256) mirror_add_kernel(c128* __restrict__ dst,
       in_row = nsrc - row0 < rows ? nsrc - row0 : rows;
     }
     const int ng = (in_row + kPairGroup - 1) / kPairGroup;
-    c128 d = accumulate ? dst[i] : c128{0.0, 0.0};
+    const long o = np ? i / nr * nr + natural_index((int)(i % nr), np) : i;
+    c128 d = accumulate ? dst[o] : c128{0.0, 0.0};
     for (int g = 0; g < ng; ++g) {
       c128 m = mir[g * count + i];
       if constexpr (F32) {
@@ -372,7 +412,7 @@ __global__ void __launch_bounds__(256) mirror_add_kernel(c128* __restrict__ dst,
       d.re += scale * m.re;
       d.im += scale * m.im;
     }
-    dst[i] = d;
+    dst[o] = d;
   }
 }
 
@@ -436,15 +476,15 @@ template hipError_t launch_wsum<double, double>(const WsumArgs<double, double>&,
 template hipError_t launch_wsum<float, double>(const WsumArgs<float, double>&, hipStream_t);
 
 hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double scale, int accumulate, int nsrc,
-                             int nr, int rows, int tri, hipStream_t st) {
+                             int nr, int rows, int tri, int np, hipStream_t st) {
   long g = ((long)nsrc * nr + 255) / 256;
   if (g > 65536) g = 65536;
   if (mcomp)
     hipLaunchKernelGGL(mirror_add_kernel<true>, dim3((unsigned)g), dim3(256), 0, st, dst, mir, mcomp, scale, accumulate,
-                       nsrc, nr, rows, tri);
+                       nsrc, nr, rows, tri, np);
   else
     hipLaunchKernelGGL(mirror_add_kernel<false>, dim3((unsigned)g), dim3(256), 0, st, dst, mir, mcomp, scale,
-                       accumulate, nsrc, nr, rows, tri);
+                       accumulate, nsrc, nr, rows, tri, np);
   return hipGetLastError();
 }
 

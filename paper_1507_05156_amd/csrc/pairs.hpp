@@ -11,7 +11,10 @@ constexpr int kPairGroup = 64;  // targets of one workgroup of stage 2: those wh
 // A block of pairs: nt targets from t0 on (index kt * nx + s) against nj sources from j0 on
 // (index ks * ns + band). With tri, targets and sources are the same fields (t0 == j0,
 // nt == nj) and only the pairs whose target tile is not below the source tile are run.
-// W of pair (t, j) is field j * nt + t of the batch.
+// W of pair (t, j) is field j * nt + t of the batch. In FP32 the one-CU kernel's fields (X, P,
+// W, and with them M and F of stage 2) hold the points m1 = 2h, 2h + 1 side by side, element
+// (h, m2, m3, b) at ((h * n2 + m2) * n3 + m3) * 2 + b, so that a lane moves 16 bytes at a time;
+// elsewhere they are in natural order.
 struct PairBlock {
   int t0, nt, j0, nj, tri;
   long npairs;      // pairs the block runs
@@ -20,7 +23,7 @@ template <typename T>
 struct PairArgs {
   const cx<T>* X;   // targets [ntk][nx][nr]
   const cx<T>* P;   // sources [nsk][ns][nr], conjugated in the density
-  const T* Kt;      // [nq][nr] kernel tables in the z-phase order, 1/N_r folded
+  const T* Kt;      // [nq][nr] kernel tables in the pair kernel's order, 1/N_r folded
   const int* qidx;  // [ntk][nsk]
   cx<T>* W;
   int nx, ns, nsk;
@@ -75,6 +78,7 @@ struct WsumArgs {
   int nsrc;         // all sources
   int jb0;          // band index of source j0 within its k-point
   int nr;
+  int np;           // n2 * n3 when the fields are in the paired order (out is natural), else 0
   int first, last;  // first / last block of these targets
   int mfirst;       // first block of these sources' mirror sums
   int accumulate;   // add to the existing out
@@ -84,6 +88,6 @@ template <typename TW, typename TM>
 hipError_t launch_wsum(const WsumArgs<TW, TM>& a, hipStream_t st);
 // dst = (accumulate ? dst : 0) + scale * sum over the groups of (mir + mcomp); mcomp may be NULL
 hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double scale, int accumulate, int nsrc,
-                             int nr, int rows, int tri, hipStream_t st);
+                             int nr, int rows, int tri, int np, hipStream_t st);
 
 }  // namespace fockmi

@@ -88,7 +88,7 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
 }
 
 template <typename TW, typename TM>
-fock_status pairs_blocks(int nr, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M,
+fock_status pairs_blocks(int nr, int np, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M,
                          const Mirror<TM>& mr, c128* out, double scale, bool accumulate, int rows, long njmax,
                          cx<TW>* W, void* run, c128* mir, c64* mcomp, hipStream_t st) {
   constexpr bool F32 = sizeof(TM) == 4;
@@ -105,6 +105,7 @@ fock_status pairs_blocks(int nr, int nt, int nj, int ns, const PairStage<TW>& st
   wa.ns = ns;
   wa.nsrc = nj;
   wa.nr = nr;
+  wa.np = np;
   wa.accumulate = accumulate ? 1 : 0;
   wa.scale = scale;
   auto block = [&](int t0, int ntb, int j0, int njb, bool tri, bool first, bool last, bool mfirst) -> fock_status {
@@ -143,7 +144,7 @@ fock_status pairs_blocks(int nr, int nt, int nj, int ns, const PairStage<TW>& st
     if (mr.tri && (s = block(t0, ntb, t0, ntb, true, t0 == 0, true, true)) != FOCK_OK) return s;
   }
   if (two && (e = launch_mirror_add(mr.dst, mir, wa.mcomp, mr.scale, mr.accumulate ? 1 : 0, nj, nr, rows,
-                                    mr.tri ? 1 : 0, st)) != hipSuccess)
+                                    mr.tri ? 1 : 0, np, st)) != hipSuccess)
     return hip_fail(e, "mirror sums");
   return FOCK_OK;
 }
@@ -161,7 +162,7 @@ bool Plan::pairs_sized(int nr, int nt, int nj, int ns, size_t fb, bool sums32, b
 }
 
 template <typename TW, typename TM>
-fock_status Plan::run_pairs(int nr, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M, c128* out,
+fock_status Plan::run_pairs(int nr, int np, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M, c128* out,
                             double scale, bool accumulate, const Mirror<TM>& mr, size_t batch, hipStream_t st) {
   constexpr bool F32 = sizeof(TM) == 4;
   const size_t fb = (size_t)nr * sizeof(cx<TW>);
@@ -187,7 +188,7 @@ fock_status Plan::run_pairs(int nr, int nt, int nj, int ns, const PairStage<TW>&
                    FOCK_OK)
       return s;
   }
-  return pairs_blocks<TW, TM>(nr, nt, nj, ns, stage, M, mr, out, scale, accumulate, rows, njmax, (cx<TW>*)pbatch.ptr,
+  return pairs_blocks<TW, TM>(nr, np, nt, nj, ns, stage, M, mr, out, scale, accumulate, rows, njmax, (cx<TW>*)pbatch.ptr,
                               prun.ptr, (c128*)pmir.ptr, (c64*)pmcomp.ptr, st);
 }
 
@@ -240,11 +241,11 @@ template PairStage<float> plane_stage<float>(const Geom&, int, const PairSet&, c
 template PairStage<double> plane_stage<double>(const Geom&, int, const PairSet&, const c128*, int, const c128*, int,
                                                const double*, hipStream_t);
 
-template fock_status pairs_blocks<float, float>(int, int, int, int, const PairStage<float>&, const c64*,
+template fock_status pairs_blocks<float, float>(int, int, int, int, int, const PairStage<float>&, const c64*,
                                                 const Mirror<float>&, c128*, double, bool, int, long, c64*, void*,
                                                 c128*, c64*, hipStream_t);
 #define FOCKMI_RUN_PAIRS(TW, TM)                                                                                  \
-  template fock_status Plan::run_pairs<TW, TM>(int, int, int, int, const PairStage<TW>&, const cx<TM>*, c128*,    \
+  template fock_status Plan::run_pairs<TW, TM>(int, int, int, int, int, const PairStage<TW>&, const cx<TM>*, c128*,    \
                                                double, bool, const Mirror<TM>&, size_t, hipStream_t);
 FOCKMI_RUN_PAIRS(float, float)
 FOCKMI_RUN_PAIRS(double, double)

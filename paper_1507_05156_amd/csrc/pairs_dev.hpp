@@ -26,6 +26,13 @@ __device__ __forceinline__ cx<T> ld_w(const cx<T>* p) {
   return {v.x, v.y};
 }
 
+// natural index of element i of a field in the paired order (np = n2 * n3; 0: natural order)
+__device__ __forceinline__ int natural_index(int i, int np) {
+  if (np == 0) return i;
+  const int h = i / (2 * np), e = i - h * 2 * np;
+  return (2 * h + (e & 1)) * np + (e >> 1);
+}
+
 // The pairs of a block in order: target tiles of kPairTile, for each tile its sources, for
 // each source the tile's targets. XCD x (workgroups b = x mod 8) walks a contiguous eighth of
 // them, so that the tile's targets, the current sources and the kernel table meet in its L2.

@@ -143,6 +143,9 @@ fock_status Plan::init_cell(Cell& c, const fock_cell_desc& d, int index) {
     if ((e = launch_build_table_fused((float*)c.Kt.ptr, (const double*)ktmp.ptr, c.nq, c.geom.n1, 0)) !=
         hipSuccess)
       return hip_fail(e, "FP32 kernel table");
+    if ((s = c.Kp.ensure((size_t)c.nq * c.nr * sizeof(float), 0, "pair kernel tables")) != FOCK_OK) return s;
+    if ((e = launch_build_table_pair32((float*)c.Kp.ptr, (const double*)ktmp.ptr, c.nq, c.geom.n1, 0)) != hipSuccess)
+      return hip_fail(e, "pair kernel table");
     if (c.geom.n1 == 32) {
       // (S, D) pairs of the split 32^3 form
       if ((s = c.SD.ensure(split32_sd_floats(c.nq) * sizeof(float), 0, "split-form kernel tables")) != FOCK_OK)
@@ -158,6 +161,10 @@ fock_status Plan::init_cell(Cell& c, const fock_cell_desc& d, int index) {
     if ((e = launch_build_table_fused64((double*)c.Kt64.ptr, (const double*)ktmp.ptr, c.nq, c.geom.n1,
                                         fused64_phases(c.geom.n1), 0)) != hipSuccess)
       return hip_fail(e, "fused FP64 kernel table");
+    if ((s = c.Kp.ensure((size_t)c.nq * c.nr * sizeof(double), 0, "pair kernel tables")) != FOCK_OK) return s;
+    if ((e = launch_build_table_pair64((double*)c.Kp.ptr, (const double*)ktmp.ptr, c.nq, c.geom.n1,
+                                       fused64_phases(c.geom.n1), 0)) != hipSuccess)
+      return hip_fail(e, "pair kernel table");
     c.f64f = prec == FOCK_FP64_FUSED;
   } else if (prec != FOCK_FP32_COMP || c.f32plain) {
     if ((s = c.Kpl.ensure((size_t)c.nq * c.nr * sizeof(double), 0, "plane-pass kernel tables")) != FOCK_OK) return s;
@@ -217,6 +224,7 @@ void Plan::destroy() {
     c.SD.release();
     c.Kt64.release();
     c.Kpl.release();
+    c.Kp.release();
     c.kvec.release();
   }
   for (DevBuf* b : {&ktmp, &shadow_x, &shadow_p, &shadow_m, &comp, &accs, &vu, &partial, &dotres, &srcbuf, &srcout,

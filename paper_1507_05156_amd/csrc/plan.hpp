@@ -58,6 +58,7 @@ struct Cell {
   DevBuf Kt;                  // float[nq][nr], fused-kernel layout (FP32 plans)
   DevBuf SD;                  // float[nq][nr/2][2], (S, D) pairs of the split 32^3 form (FP32 plans, n = 32)
   DevBuf Kt64;                // double[nq][nr], fused FP64 kernel layout (FP64 plans, cubic grids up to 24)
+  DevBuf Kp;                  // float or double [nq][nr], the pair kernel's order (cubic grids with a one-CU kernel)
   DevBuf Kpl;                 // double[nq][nr] as [l1][l3][l2], for the plane passes (grids without a one-CU kernel)
   bool f64f = false;          // this cell runs the fused FP64 kernel
   bool f32plain = false;      // an FP32-form cell on a grid that is not cubic: complex64 plane passes, FP64 sums
@@ -120,7 +121,7 @@ void pairs_block_shape(int nt, int nj, int ns, int nr, size_t fb, size_t budget,
 template <typename TW>
 using PairStage = std::function<hipError_t(const PairBlock&, cx<TW>*)>;
 // one pair per workgroup pass, on a cubic grid whose field fits on a CU; Kt: tables in the
-// fused kernel's order
+// pair kernel's order
 template <typename T>
 PairStage<T> cube_stage(int n, int num_cus, const PairSet& ps, const cx<T>* X, int nx, const cx<T>* P, int ns,
                         const T* Kt, hipStream_t st);
@@ -130,9 +131,10 @@ PairStage<T> plane_stage(const Geom& g, int num_cus, const PairSet& ps, const c1
                          const double* K, hipStream_t st);
 // The blocks of a two-stage pair sum (nt targets, nj sources of ns per k-point) over buffers of
 // the caller's: W holds rows * njmax fields, run rows * nr sums (complex64 for FP32 sums,
-// complex128 for FP64 ones). TW: the type of W, TM: of the products and sums.
+// complex128 for FP64 ones). TW: the type of W, TM: of the products and sums; np: n2 * n3 when
+// M and F are in the paired order of the FP32 one-CU kernel, else 0.
 template <typename TW, typename TM>
-fock_status pairs_blocks(int nr, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M,
+fock_status pairs_blocks(int nr, int np, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M,
                          const Mirror<TM>& mr, c128* out, double scale, bool accumulate, int rows, long njmax,
                          cx<TW>* W, void* run, c128* mir, c64* mcomp, hipStream_t st);
 
@@ -212,7 +214,7 @@ struct Plan {
                           int ns, c128* out, double scale, bool accumulate, hipStream_t st);
   // a sum in the two-stage pair form, its batch at most `batch` bytes
   template <typename TW, typename TM>
-  fock_status run_pairs(int nr, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M, c128* out,
+  fock_status run_pairs(int nr, int np, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M, c128* out,
                         double scale, bool accumulate, const Mirror<TM>& mr, size_t batch, hipStream_t st);
   // whether the sum runs in the two-stage pair form (cubic grids up to 24), and with the pair symmetry
   struct PairRule {
@@ -232,7 +234,8 @@ struct Plan {
                            hipStream_t st);
   // V_x[u] phi into out (forward sums over S, weight 1/|S|)
   fock_status apply_op(Cell& c, const c128* u, const c128* phi, int nphi, c128* out, hipStream_t st);
-  fock_status shadow(DevBuf& buf, const c128* src, size_t count, const char* what, hipStream_t st,
+  // complex64 copy of src in buf; np > 0: in the pair form's order (np = n2 * n3)
+  fock_status shadow(DevBuf& buf, const c128* src, size_t count, const char* what, hipStream_t st, int np,
                      const c64** out);
   // sum conj(a) b over count elements in FP64 (fixed order); synchronises st
   fock_status dot(const c128* a, const c128* b, size_t count, hipStream_t st, double* re, double* im);

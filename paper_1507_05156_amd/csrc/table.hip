@@ -59,8 +59,9 @@ __global__ void build_table_f64_kernel(double* __restrict__ K, const double* __r
 }
 
 // Fused layout: value index l3 of thread t in the z phase of the fused kernel,
-// with the same (l1, l2) <- t map as that kernel (see fused.hip).
-template <typename T>
+// with the same (l1, l2) <- t map as that kernel (see fused.hip); V consecutive values of a
+// thread side by side.
+template <typename T, int V>
 __global__ void build_table_fused_kernel(T* __restrict__ Kt, const double* __restrict__ K, int nq, int n,
                                          int nph) {
   const int nt = n * n;
@@ -74,7 +75,7 @@ __global__ void build_table_fused_kernel(T* __restrict__ Kt, const double* __res
   const int grp = t / tpg, tl = t % tpg;
   const int l2 = tl % h + h * grp;
   const int l1 = tl / h;
-  Kt[(long)q * nr + idx] = (T)K[(long)q * nr + ((long)l1 * n + l2) * n + l3];
+  Kt[(long)q * nr + ((long)(l3 / V) * nt + t) * V + l3 % V] = (T)K[(long)q * nr + ((long)l1 * n + l2) * n + l3];
 }
 
 }  // namespace
@@ -95,30 +96,38 @@ hipError_t launch_build_table_f64(double* K, const double* qvec, const int* qzer
 
 int fused_phases(int n);  // fused.hip
 
-hipError_t launch_build_table_fused(float* Kt, const double* K, int nq, int n, hipStream_t st) {
+namespace {
+
+template <typename T, int V>
+hipError_t build_fused_tables(T* Kt, const double* K, int nq, int n, int nph, hipStream_t st) {
   const long nr = (long)n * n * n;
   for (int q0 = 0; q0 < nq; q0 += 65535) {
     const int cnt = nq - q0 < 65535 ? nq - q0 : 65535;
     dim3 grid((unsigned)((nr + 255) / 256), (unsigned)cnt);
-    hipLaunchKernelGGL(build_table_fused_kernel<float>, grid, dim3(256), 0, st, Kt + (long)q0 * nr,
-                       K + (long)q0 * nr, cnt, n, fused_phases(n));
+    hipLaunchKernelGGL((build_table_fused_kernel<T, V>), grid, dim3(256), 0, st, Kt + (long)q0 * nr,
+                       K + (long)q0 * nr, cnt, n, nph);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
+}  // namespace
+
+hipError_t launch_build_table_fused(float* Kt, const double* K, int nq, int n, hipStream_t st) {
+  return build_fused_tables<float, 1>(Kt, K, nq, n, fused_phases(n), st);
+}
+
 hipError_t launch_build_table_fused64(double* Kt, const double* K, int nq, int n, int nph, hipStream_t st) {
-  const long nr = (long)n * n * n;
-  for (int q0 = 0; q0 < nq; q0 += 65535) {
-    const int cnt = nq - q0 < 65535 ? nq - q0 : 65535;
-    dim3 grid((unsigned)((nr + 255) / 256), (unsigned)cnt);
-    hipLaunchKernelGGL(build_table_fused_kernel<double>, grid, dim3(256), 0, st, Kt + (long)q0 * nr,
-                       K + (long)q0 * nr, cnt, n, nph);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return build_fused_tables<double, 1>(Kt, K, nq, n, nph, st);
+}
+
+hipError_t launch_build_table_pair32(float* Kp, const double* K, int nq, int n, hipStream_t st) {
+  return build_fused_tables<float, 4>(Kp, K, nq, n, fused_phases(n), st);
+}
+
+hipError_t launch_build_table_pair64(double* Kp, const double* K, int nq, int n, int nph, hipStream_t st) {
+  return build_fused_tables<double, 2>(Kp, K, nq, n, nph, st);
 }
 
 }  // namespace fockmi
