@@ -104,18 +104,24 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
   }
   auto run = [&](size_t batch) -> fock_status {
     hipError_t e;
-    fock_status s;
     if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
-    if (c.f32plain)
-      s = run_pairs<float, double>(
-          nr, 0, nt, nj, ns, plane_stage<float>(c.geom, num_cus, ps, X, nx, P, ns, (const double*)c.Kpl.ptr, st), M, out,
-          scale, accumulate, mr, batch, st);
-    else
-      s = run_pairs<double, double>(
+    auto sums = [&](const Mirror<double>& m) -> fock_status {
+      if (c.f32plain)
+        return run_pairs<float, double>(
+            nr, 0, nt, nj, ns, plane_stage<float>(c.geom, num_cus, ps, X, nx, P, ns, (const double*)c.Kpl.ptr, st), M,
+            out, scale, accumulate, m, batch, st);
+      return run_pairs<double, double>(
           nr, 0, nt, nj, ns,
           cube ? cube_stage<double>(c.geom.n1, num_cus, ps, X, nx, P, ns, (const double*)c.Kp.ptr, st)
                : plane_stage<double>(c.geom, num_cus, ps, X, nx, P, ns, (const double*)c.Kpl.ptr, st),
-          M, out, scale, accumulate, mr, batch, st);
+          M, out, scale, accumulate, m, batch, st);
+    };
+    fock_status s = sums(mr);
+    if (s == FOCK_ERR_NOMEM && mr.dst) {
+      // no room for the mirror sums: every pair (nothing has been launched)
+      g_last_error.clear();
+      s = sums(Mirror<double>{});
+    }
     if (s != FOCK_OK) return s;
     if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
     return FOCK_OK;
@@ -422,6 +428,14 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   if ((s = prepare(variant)) != FOCK_OK) return s;
   if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
   if ((e = launch(variant)) != hipSuccess) return hip_fail(e, "fused pair kernel");
+  if (pairs_status == FOCK_ERR_NOMEM) {
+    // no room for a batch (nothing has been launched): the forms that sum on the CU need less
+    g_last_error.clear();
+    pairs_status = FOCK_OK;
+    variant = n == 32 ? (has_split ? 2 : (has_ls ? 1 : 0)) : 0;
+    if ((s = prepare(variant)) != FOCK_OK) return s;
+    if ((e = launch(variant)) != hipSuccess) return hip_fail(e, "fused pair kernel");
+  }
   if (pairs_status != FOCK_OK) return pairs_status;
   if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
   return FOCK_OK;
@@ -457,21 +471,30 @@ fock_status Plan::run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx,
       !pairs_sized(c.nr, nitems, ps.nsk * ns, ns, c.nr * sizeof(c128), false, rule.tri, rule.tri))
     rule.pairs = false;
   if (rule.pairs) {
-    Mirror<double> mr;
-    if (rule.tri) {
-      mr.F = X;
-      mr.dst = out;
-      mr.scale = scale;
-      mr.accumulate = mr.tri = true;
-    }
     if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
-    if ((s = run_pairs<double, double>(
-             c.nr, 0, nitems, ps.nsk * ns, ns,
-             cube_stage<double>(c.geom.n1, num_cus, ps, X, nx, P, ns, (const double*)c.Kp.ptr, st), M, out, scale,
-             accumulate, mr, pair_batch, st)) != FOCK_OK)
-      return s;
-    if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
-    return FOCK_OK;
+    auto sums = [&](bool tri) -> fock_status {
+      Mirror<double> mr;
+      if (tri) {
+        mr.F = X;
+        mr.dst = out;
+        mr.scale = scale;
+        mr.accumulate = mr.tri = true;
+      }
+      return run_pairs<double, double>(
+          c.nr, 0, nitems, ps.nsk * ns, ns,
+          cube_stage<double>(c.geom.n1, num_cus, ps, X, nx, P, ns, (const double*)c.Kp.ptr, st), M, out, scale,
+          accumulate, mr, pair_batch, st);
+    };
+    s = sums(rule.tri);
+    if (s == FOCK_ERR_NOMEM && rule.tri) s = sums(false);
+    if (s == FOCK_OK) {
+      g_last_error.clear();
+      if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
+      return FOCK_OK;
+    }
+    prof_drop();
+    if (s != FOCK_ERR_NOMEM) return s;
+    g_last_error.clear();  // no room for a batch (nothing has been launched): the fused kernel needs less
   }
   const size_t acc_elems = fused64_acc_scratch_elems(c.geom.n1, nitems);
   if (acc_elems && (s = accs.ensure(acc_elems * sizeof(c128), workspace_cap, "FP64 sums")) != FOCK_OK) return s;
@@ -494,6 +517,62 @@ fock_status Plan::run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx,
   if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
   if ((e = launch_fused64_apply(c.geom.n1, a, st)) != hipSuccess) return hip_fail(e, "fused FP64 pair kernel");
   if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
+  return FOCK_OK;
+}
+
+fock_status Plan::two_sided(Cell& c, const c128* X, int nx, const c128* us, double scale, c128* out, const c128* F,
+                            double mre, double mim, bool maccumulate, c128* gu, hipStream_t st, bool* done) {
+  const PairSet ps = c.fwd();
+  const int nr = c.nr, nt = ps.ntk * nx, nj = ps.nsk * c.nb, n = c.geom.n1;
+  const bool f32 = prec == FOCK_FP32_COMP;
+  const bool planes = f32 ? c.f32plain : c.Kt64.ptr == nullptr;
+  *done = false;
+  if (f32 && !planes && n == 32 && split_form) return FOCK_OK;
+  if (!planes && n <= 24) {
+    // against the faster form of each side; the mirror sums add about a twentieth
+    const PairRule a = pair_rule(c, ps, nx, c.nb, false, f32), b = pair_rule(c, c.rev(), c.nb, nx, false, f32);
+    if (a.pairs_ns == 0.0 || b.pairs_ns == 0.0) return FOCK_OK;  // no room for a batch
+    const double two = 1.05 * a.pairs_ns * nj;
+    const double one = std::min(a.fused_ns, a.pairs_ns) * nj + std::min(b.fused_ns, b.pairs_ns) * nt;
+    if (two > one) return FOCK_OK;
+  }
+  if (stream_captures(st) && !pairs_sized(nr, nt, nj, c.nb, (size_t)nr * (f32 ? sizeof(c64) : sizeof(c128)),
+                                          f32 && !planes, true, false))
+    return FOCK_OK;
+  fock_status s;
+  hipError_t e;
+  if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
+  if (f32 && !planes) {
+    const c64 *Xs = nullptr, *Ps = nullptr, *Fs = nullptr;
+    if ((s = shadow(shadow_p, us, (size_t)nj * nr, "complex64 shadow (P)", st, n * n, &Ps)) != FOCK_OK) return s;
+    if ((s = shadow(shadow_x, X, (size_t)nt * nr, "complex64 shadow (X)", st, n * n, &Xs)) != FOCK_OK) return s;
+    if ((s = shadow(shadow_m, F, (size_t)nt * nr, "complex64 shadow (M)", st, n * n, &Fs)) != FOCK_OK) return s;
+    Mirror<float> mr{Fs, gu, mre, mim, maccumulate, false};
+    s = run_pairs<float, float>(nr, n * n, nt, nj, c.nb,
+                                cube_stage<float>(n, num_cus, ps, Xs, nx, Ps, c.nb, (const float*)c.Kp.ptr, st), Ps, out,
+                                scale, false, mr, pair_batch, st);
+  } else {
+    Mirror<double> mr{F, gu, mre, mim, maccumulate, false};
+    if (f32)
+      s = run_pairs<float, double>(
+          nr, 0, nt, nj, c.nb, plane_stage<float>(c.geom, num_cus, ps, X, nx, us, c.nb, (const double*)c.Kpl.ptr, st), us,
+          out, scale, false, mr, pair_batch, st);
+    else
+      s = run_pairs<double, double>(
+          nr, 0, nt, nj, c.nb,
+          planes ? plane_stage<double>(c.geom, num_cus, ps, X, nx, us, c.nb, (const double*)c.Kpl.ptr, st)
+                 : cube_stage<double>(n, num_cus, ps, X, nx, us, c.nb, (const double*)c.Kp.ptr, st),
+          us, out, scale, false, mr, pair_batch, st);
+  }
+  if (s == FOCK_ERR_NOMEM) {
+    // no room for the batch or the mirror sums (nothing has been launched): two separate sums
+    prof_drop();
+    g_last_error.clear();
+    return FOCK_OK;
+  }
+  if (s != FOCK_OK) return s;
+  if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
+  *done = true;
   return FOCK_OK;
 }
 
@@ -747,22 +826,27 @@ fock_status fock_vjp(fockmi_plan plan, int cell, const void* u_occ, const void* 
   const c128* G = (const c128*)g_vphi;
   const c128* Us = nullptr;
   if ((s = p->sources(c, U, c.nb, p->srcbuf, st, &Us)) != FOCK_OK) return s;
-  if (g_phi) {
+  c128* gu = (c128*)g_u_occ;
+  if (g_u_occ && c.ds) {
+    const size_t block = (size_t)c.nb * c.nr;
+    if ((s = p->srcout.ensure((size_t)c.nsrc * block * sizeof(c128), p->workspace_cap, "source gradient")) != FOCK_OK)
+      return s;
+    gu = (c128*)p->srcout.ptr;
+  }
+  // the pairs of g_phi = V_x[u] g give the third family below as well: W of (g_ik, u_jk')
+  // in that order is the conjugate of W of (u_jk', g_ik)
+  bool shared = false;
+  if (g_phi && g_u_occ &&
+      (s = p->two_sided(c, G, nphi, Us, scale, (c128*)g_phi, F, scale, 0.0, false, gu, st, &shared)) != FOCK_OK)
+    return s;
+  if (g_phi && !shared) {
     if ((s = p->general(c, c.fwd(), G, nphi, Us, Us, c.nb, (c128*)g_phi, scale, false, st)) != FOCK_OK) return s;
   }
   if (g_u_occ) {
     // targets u at the source k-points k', sources (phi or g) at every k, kernel K_{k'-k}
-    c128* gu = (c128*)g_u_occ;
     hipError_t e;
-    if (c.ds) {
-      const size_t block = (size_t)c.nb * c.nr;
-      if ((s = p->srcout.ensure((size_t)c.nsrc * block * sizeof(c128), p->workspace_cap, "source gradient")) !=
-          FOCK_OK)
-        return s;
-      gu = (c128*)p->srcout.ptr;
-    }
-    if ((s = p->general(c, c.rev(), Us, c.nb, F, G, nphi, gu, scale, false, st)) != FOCK_OK) return s;
-    if ((s = p->general(c, c.rev(), Us, c.nb, G, F, nphi, gu, scale, true, st)) != FOCK_OK) return s;
+    if ((s = p->general(c, c.rev(), Us, c.nb, F, G, nphi, gu, scale, shared, st)) != FOCK_OK) return s;
+    if (!shared && (s = p->general(c, c.rev(), Us, c.nb, G, F, nphi, gu, scale, true, st)) != FOCK_OK) return s;
     if (c.ds) {
       // orbitals off the sub-mesh carry no gradient; scatter the sub-mesh rows
       const size_t block = (size_t)c.nb * c.nr;

@@ -385,12 +385,12 @@ __global__ void __launch_bounds__(64 * NW) wsum_kernel(WsumArgs<TW, T> a) {
   });
 }
 
-// dst[j] = (accumulate ? dst[j] : 0) + scale * sum over the groups g of mir[g][j] + mcomp[g][j],
+// dst[j] = (accumulate ? dst[j] : 0) + (sre + i sim) * sum over the groups g of mir[g][j] + mcomp[g][j],
 // groups in order. Of a symmetric sum in rows of `rows` fields, the fields of the last row
 // have the groups of that row only.
 template <bool F32>
 __global__ void __launch_bounds__(256) mirror_add_kernel(c128* __restrict__ dst, const c128* __restrict__ mir,
-                                                         const cx<float>* __restrict__ mcomp, double scale,
+                                                         const cx<float>* __restrict__ mcomp, double sre, double sim,
                                                          int accumulate, int nsrc, int nr, int rows, int tri,
                                                          int np) {
   const long count = (long)nsrc * nr;
@@ -409,8 +409,8 @@ __global__ void __launch_bounds__(256) mirror_add_kernel(c128* __restrict__ dst,
         m.re += (double)mcomp[g * count + i].re;
         m.im += (double)mcomp[g * count + i].im;
       }
-      d.re += scale * m.re;
-      d.im += scale * m.im;
+      d.re += sre * m.re - sim * m.im;
+      d.im += sre * m.im + sim * m.re;
     }
     dst[o] = d;
   }
@@ -475,15 +475,15 @@ template hipError_t launch_wsum<float, float>(const WsumArgs<float, float>&, hip
 template hipError_t launch_wsum<double, double>(const WsumArgs<double, double>&, hipStream_t);
 template hipError_t launch_wsum<float, double>(const WsumArgs<float, double>&, hipStream_t);
 
-hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double scale, int accumulate, int nsrc,
+hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double sre, double sim, int accumulate, int nsrc,
                              int nr, int rows, int tri, int np, hipStream_t st) {
   long g = ((long)nsrc * nr + 255) / 256;
   if (g > 65536) g = 65536;
   if (mcomp)
-    hipLaunchKernelGGL(mirror_add_kernel<true>, dim3((unsigned)g), dim3(256), 0, st, dst, mir, mcomp, scale, accumulate,
+    hipLaunchKernelGGL(mirror_add_kernel<true>, dim3((unsigned)g), dim3(256), 0, st, dst, mir, mcomp, sre, sim, accumulate,
                        nsrc, nr, rows, tri, np);
   else
-    hipLaunchKernelGGL(mirror_add_kernel<false>, dim3((unsigned)g), dim3(256), 0, st, dst, mir, mcomp, scale,
+    hipLaunchKernelGGL(mirror_add_kernel<false>, dim3((unsigned)g), dim3(256), 0, st, dst, mir, mcomp, sre, sim,
                        accumulate, nsrc, nr, rows, tri, np);
   return hipGetLastError();
 }

@@ -86,8 +86,8 @@ struct WsumArgs {
 };
 template <typename TW, typename TM>
 hipError_t launch_wsum(const WsumArgs<TW, TM>& a, hipStream_t st);
-// dst = (accumulate ? dst : 0) + scale * sum over the groups of (mir + mcomp); mcomp may be NULL
-hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double scale, int accumulate, int nsrc,
+// dst = (accumulate ? dst : 0) + (sre + i sim) * sum over the groups of (mir + mcomp); mcomp may be NULL
+hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double sre, double sim, int accumulate, int nsrc,
                              int nr, int rows, int tri, int np, hipStream_t st);
 
 }  // namespace fockmi

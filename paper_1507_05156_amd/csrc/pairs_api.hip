@@ -19,23 +19,23 @@ extern thread_local std::string g_last_error;
 // targets, whose mirror sums meet in one workgroup. At 32^3 that is 128 targets; with the
 // 8 GiB batch a block then runs 16,384 to 32,768 pairs, so that its last round costs under 2%
 // (32^3 / 216 k / 16 bands: 1,159 ms with batches of 512 MiB, 1,110 with 4 GiB, 1,088 with 8).
-static int row_targets(int nt, int nr, size_t field_bytes, size_t budget, bool tri) {
-  static const int sh = std::getenv("XX_ROWS") ? std::atoi(std::getenv("XX_ROWS")) : 22;
-  long want = std::max<long>(64, ((1L << sh) / nr + 63) / 64 * 64);
+static int row_targets(int nt, int nr, size_t field_bytes, size_t budget, int least, bool tri) {
+  long want = std::max<long>(64, ((1L << 22) / nr + 63) / 64 * 64);
   if (tri) {
     while (want > 64 && (size_t)want * want * field_bytes > budget) want -= 64;
   } else {
-    // at least 16 sources (one FP32 partial sum) per block
     while (want > kPairTile && (size_t)want * 16 * field_bytes > budget) want -= want > 64 ? 64 : kPairTile;
+    while (want > 1 && (size_t)want * least * field_bytes > budget) --want;
   }
   return (int)std::min<long>(want, nt);
 }
 
 void pairs_block_shape(int nt, int nj, int ns, int nr, size_t fb, size_t budget, bool whole_partials, bool tri,
                        int* rows, long* njmax) {
-  *rows = row_targets(nt, nr, fb, budget, tri);
+  const int least = whole_partials ? std::min(16, ns) : 1;
+  *rows = row_targets(nt, nr, fb, budget, least, tri);
   long m = std::min<long>((long)(budget / ((size_t)*rows * fb)), nj);
-  m = std::max<long>(m, whole_partials ? std::min(16, ns) : 1);
+  m = std::max<long>(m, least);
   *njmax = tri ? std::max<long>(m, *rows) : m;
 }
 
@@ -63,8 +63,13 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
     if (x.n == c.geom.n1) fc = &x;
   if (!fc) return r;
   same = same && nx == ns && !c.ds;
+  // a cap without room for one FP32 partial sum's pairs (FP64: one pair) of one target
+  if (workspace_cap && (size_t)(f32 ? std::min(ns, 16) : 1) * c.nr * (f32 ? sizeof(c64) : sizeof(c128)) > workspace_cap)
+    return r;
+  r.pairs_ns = nt * fc->pair;
   const double scale = num_cus / 256.0;
   const double fused = fc->round * 1e3 * (double)((nt + (long)(fc->slots * scale) - 1) / std::max<long>(1, (long)(fc->slots * scale)));
+  r.fused_ns = fused;
   // below 4 tiles the triangle is nearly the whole square, and the mirror sums cost a launch
   const bool tri_ok = same && ps.ntk == c.nk && ps.nsk == c.nk && ps.qidx == (const int*)c.qidx.ptr &&
                       nt > 3 * kPairTile &&
@@ -76,7 +81,7 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
       // fock_apply_noalloc serves this sum with the same bits: one-sided in both (its sums do
       // not depend on the blocks), and only where its 64 MiB hold a batch that is still the
       // faster form
-      const size_t least = (size_t)std::min<long>(nt, kPairTile) * std::min(ns, 16) * c.nr * sizeof(c64);
+      const size_t least = (size_t)std::min(ns, 16) * c.nr * sizeof(c64);
       r.pairs = nt * nj <= (fc->n == 24 ? 96 * 96 : 128 * 128) && nt * fc->pair < fused &&
                 need + least <= kNoAllocBytes;
       return r;
@@ -143,7 +148,7 @@ fock_status pairs_blocks(int nr, int np, int nt, int nj, int ns, const PairStage
     }
     if (mr.tri && (s = block(t0, ntb, t0, ntb, true, t0 == 0, true, true)) != FOCK_OK) return s;
   }
-  if (two && (e = launch_mirror_add(mr.dst, mir, wa.mcomp, mr.scale, mr.accumulate ? 1 : 0, nj, nr, rows,
+  if (two && (e = launch_mirror_add(mr.dst, mir, wa.mcomp, mr.scale, mr.scale_im, mr.accumulate ? 1 : 0, nj, nr, rows,
                                     mr.tri ? 1 : 0, np, st)) != hipSuccess)
     return hip_fail(e, "mirror sums");
   return FOCK_OK;

@@ -193,6 +193,13 @@ hipError_t Plan::prof_end(hipStream_t st) {
   return hipEventRecord(prof_events.back().second, st);
 }
 
+void Plan::prof_drop() {
+  if (!profiling || prof_events.empty()) return;
+  (void)hipEventDestroy(prof_events.back().first);
+  (void)hipEventDestroy(prof_events.back().second);
+  prof_events.pop_back();
+}
+
 fock_status Plan::prof_collect() {
   for (auto& ev : prof_events) {
     hipError_t e = hipEventSynchronize(ev.second);

@@ -101,14 +101,14 @@ struct BatchState {
   void release();
 };
 
-// The mirror side of a two-sided pair sum: dst[j] = (accumulate ? dst[j] : 0) + scale *
-// sum_i F_i conj(W_ji) over the targets i. dst NULL: one-sided. tri: the targets are the
+// The mirror side of a two-sided pair sum: dst[j] = (accumulate ? dst[j] : 0) +
+// (scale + i scale_im) sum_i F_i conj(W_ji) over the targets i. dst NULL: one-sided. tri: the targets are the
 // sources, every pair of fields is transformed once and the mirror adds the other half.
 template <typename T>
 struct Mirror {
   const cx<T>* F = nullptr;
   c128* dst = nullptr;
-  double scale = 0.0;
+  double scale = 0.0, scale_im = 0.0;
   bool accumulate = false;
   bool tri = false;
 };
@@ -196,6 +196,7 @@ struct Plan {
   long long prof_launches = 0;
   hipError_t prof_begin(hipStream_t st);
   hipError_t prof_end(hipStream_t st);
+  void prof_drop();                         // forgets a prof_begin whose launches did not happen
   fock_status prof_collect();
 
   fock_status init_cell(Cell& c, const fock_cell_desc& d, int index);
@@ -220,6 +221,7 @@ struct Plan {
   struct PairRule {
     bool pairs = false, tri = false;
     bool shared = false;  // fock_apply_noalloc serves the same sum, by the same rule
+    double fused_ns = 0.0, pairs_ns = 0.0;  // modelled cost of the one-sided sum per source (0: no fused form)
   };
   PairRule pair_rule(const Cell& c, const PairSet& ps, int nx, int ns, bool same, bool f32) const;
   // whether the buffers of such a sum are there already (under capture nothing can be allocated)
@@ -234,6 +236,12 @@ struct Plan {
                            hipStream_t st);
   // V_x[u] phi into out (forward sums over S, weight 1/|S|)
   fock_status apply_op(Cell& c, const c128* u, const c128* phi, int nphi, c128* out, hipStream_t st);
+  // Both sides of one set of pairs, each transformed once: the forward sum out = scale *
+  // sum_j u_j W_ji over targets X ([nk][nx] fields, sources us as in Plan::sources), and
+  // gu[j] (+)= (mre + i mim) sum_i F_i conj(W_ji) over the source orbitals. *done = false (and
+  // nothing written): two separate sums are the faster way.
+  fock_status two_sided(Cell& c, const c128* X, int nx, const c128* us, double scale, c128* out, const c128* F,
+                        double mre, double mim, bool maccumulate, c128* gu, hipStream_t st, bool* done);
   // complex64 copy of src in buf; np > 0: in the pair form's order (np = n2 * n3)
   fock_status shadow(DevBuf& buf, const c128* src, size_t count, const char* what, hipStream_t st, int np,
                      const c64** out);
@@ -244,8 +252,10 @@ struct Plan {
 
   // propagator pieces (prop_api.hip)
   fock_status kinetic(Cell& c, const c128* x, int nf, c128* y, const double a[3], hipStream_t st);
+  // vx_ready: vxb holds V_x x already
   fock_status h_apply(Cell& c, const c128* us, const c128* us2, const c128* x, c128* out, const c128* base,
-                      double cre, double cim, const double* vloc, const double a[3], double alpha, hipStream_t st);
+                      double cre, double cim, const double* vloc, const double a[3], double alpha, hipStream_t st,
+                      bool vx_ready = false);
   // acc <- x0 + sum_{m=1}^{order} phi_m, phi_m = (-i dt/m) h phi_{m-1}, phi_0 = x0 (acc distinct from x0)
   fock_status taylor_sum(Cell& c, const c128* us, const c128* us2, const c128* x0, c128* acc, const double* vloc,
                          const double a[3], double dt, double alpha, int order, hipStream_t st);

@@ -47,7 +47,7 @@ fock_status Plan::kinetic(Cell& c, const c128* x, int nf, c128* y, const double 
 // second source set us2, the exchange term is the average alpha (V_x[u] + V_x[u2]) / 2.
 fock_status Plan::h_apply(Cell& c, const c128* us, const c128* us2, const c128* x, c128* out, const c128* base,
                           double cre, double cim, const double* vloc, const double a[3], double alpha,
-                          hipStream_t st) {
+                          hipStream_t st, bool vx_ready) {
   fock_status s;
   if ((s = field_bufs(c, {&kin}, c.nb)) != FOCK_OK) return s;
   if ((s = kinetic(c, x, c.nb, (c128*)kin.ptr, a, st)) != FOCK_OK) return s;
@@ -55,7 +55,8 @@ fock_status Plan::h_apply(Cell& c, const c128* us, const c128* us2, const c128* 
   if (alpha != 0.0) {
     if ((s = field_bufs(c, {&vxb}, c.nb)) != FOCK_OK) return s;
     const double w = (us2 ? 0.5 : 1.0) / c.nsrc;
-    if ((s = general(c, c.fwd(), x, c.nb, us, us, c.nb, (c128*)vxb.ptr, -w, false, st)) != FOCK_OK) return s;
+    if (!vx_ready && (s = general(c, c.fwd(), x, c.nb, us, us, c.nb, (c128*)vxb.ptr, -w, false, st)) != FOCK_OK)
+      return s;
     if (us2 && (s = general(c, c.fwd(), x, c.nb, us2, us2, c.nb, (c128*)vxb.ptr, -w, true, st)) != FOCK_OK)
       return s;
     vx = (const c128*)vxb.ptr;
@@ -244,15 +245,26 @@ fock_status taylor_step_vjp(fockmi_plan plan, int cell, const void* psi_n, const
     if ((e = launch_agrad((double*)p->red6.ptr + 6 * (m - 1), (double*)p->partial.ptr, nblk, gt, ft,
                           (const double*)c.kvec.ptr, c.nb, c.geom, A_over_c, count, st)) != hipSuccess)
       return hip_fail(e, "A gradient");
+    bool vx_ready = false;
     if (alpha != 0.0) {
-      // cotangent of V_x[u] phi_{m-1} is conj(c_m) alpha lam_m
+      // cotangent of V_x[u] phi_{m-1} is conj(c_m) alpha lam_m = i t lam_m, t = alpha dt / m. Its source side
+      // has two families; the one with the cotangent in the density runs the pairs of
+      // V_x[u] lam_m, which the next line needs: W of (i t lam, u) is -i t conj(W of (u, lam)).
+      const double t = alpha * dt / m;
+      if ((s = p->field_bufs(c, {&p->vxb}, c.nb)) != FOCK_OK) return s;
+      if ((s = p->two_sided(c, lam, c.nb, U, -1.0 / c.nsrc, (c128*)p->vxb.ptr, phim1, 0.0, t / c.nsrc, true, GP, st,
+                            &vx_ready)) != FOCK_OK)
+        return s;
       if ((e = hipMemsetAsync(gt, 0, bytes, st)) != hipSuccess) return hip_fail(e, "zero");
-      if ((e = launch_scale_add(gt, lam, 0.0, alpha * dt / m, count, st)) != hipSuccess) return hip_fail(e, "scale");
+      if ((e = launch_scale_add(gt, lam, 0.0, t, count, st)) != hipSuccess) return hip_fail(e, "scale");
       if ((s = p->general(c, c.rev(), U, c.nb, phim1, gt, c.nb, GP, -1.0 / c.nsrc, true, st)) != FOCK_OK) return s;
-      if ((s = p->general(c, c.rev(), U, c.nb, gt, phim1, c.nb, GP, -1.0 / c.nsrc, true, st)) != FOCK_OK) return s;
+      if (!vx_ready &&
+          (s = p->general(c, c.rev(), U, c.nb, gt, phim1, c.nb, GP, -1.0 / c.nsrc, true, st)) != FOCK_OK)
+        return s;
     }
     // lam_{m-1} = g + conj(c_m) h lam_m
-    if ((s = p->h_apply(c, U, nullptr, lam, lam2, G, 0.0, dt / m, vloc, A_over_c, alpha, st)) != FOCK_OK) return s;
+    if ((s = p->h_apply(c, U, nullptr, lam, lam2, G, 0.0, dt / m, vloc, A_over_c, alpha, st, vx_ready)) != FOCK_OK)
+      return s;
     std::swap(lam, lam2);
   }
   if ((e = launch_scale_add(GP, lam, 1.0, 0.0, count, st)) != hipSuccess) return hip_fail(e, "accumulate");
