@@ -63,17 +63,6 @@ __device__ __forceinline__ void ld_tab(rsrc_t r, unsigned t, int g, double* k) {
   k[0] = q.re, k[1] = q.im;
 }
 
-// rounds of a transpose through LDS and the LDS elements they need
-template <int N, int NPH>
-constexpr int pw_lds_elems() {
-  constexpr int H = N / NPH;
-  return NPH == 1 ? N * N * (N + 1) : (N * N * H > H * N * (N + 1) ? N * N * H : H * N * (N + 1));
-}
-
-template <int N, typename T>
-constexpr int pw_nph() {
-  return ((long)N * N * (N + 1) * (long)sizeof(cx<T>) > 160L * 1024) ? 2 : 1;
-}
 // elements whose loads are in flight together: operands of the pair product, kernel values
 // (24^3 FP64: groups of 4 took 120 ns per pair, of 12 115 ns; 24 kernel values at once spill)
 template <int N, typename T>
@@ -87,38 +76,15 @@ constexpr int pw_grp_k() { return sizeof(T) == 8 ? 12 : (N <= 24 ? N : 8); }
 
 template <int N, typename T, int WPE>
 __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE))) pair_w_kernel(PairArgs<T> a) {
-  constexpr int NPH = pw_nph<N, T>();
-  constexpr int E = (int)sizeof(cx<T>);
   constexpr int NTI = N * N;
   constexpr int NR = N * N * N;
-  constexpr int H = N / NPH;
-  constexpr int TPG = NTI / NPH;
-  constexpr int NBK = N / NPH;
-  constexpr bool XY_WAVES = TPG % 64 == 0;
-  constexpr bool YZ_WAVES = XY_WAVES && (NBK * H) % 64 == 0;
-  __shared__ cx<T> lds[pw_lds_elems<N, NPH>()];
+  __shared__ cx<T> lds[CubeTransform<N, T>::kLdsElems];
   static_assert(sizeof(lds) <= 160 * 1024, "LDS of the pair kernel");
 
   const int t = threadIdx.x;
-  const int grp = (NPH == 1) ? 0 : (XY_WAVES ? __builtin_amdgcn_readfirstlane(t / TPG) : t / TPG);
-  const int tl = t % TPG;
-  const int hl = tl % H;
-  const int clo = hl + H * grp;  // m3 in the x and y phases, l2 in the z phase
-  const int chi = tl / H;        // m2 in the x phase, l1 in the y and z phases
-  const int gyz = (NPH == 1) ? 0 : (YZ_WAVES ? __builtin_amdgcn_readfirstlane(chi / NBK) : chi / NBK);
-  const int lrow = chi % NBK;
-
-  // LDS byte offsets of this thread's elements in the transposes (see fused.hip)
-  constexpr bool INPLACE = NPH == 1;
-  constexpr unsigned SX = INPLACE ? (unsigned)(N * (N + 1) * E) : (unsigned)(N * H * E);
-  constexpr unsigned SY = INPLACE ? (unsigned)((N + 1) * E) : (unsigned)(H * E);
-  constexpr int L1S = (int)((65535u / SX) + 1) < N ? (int)((65535u / SX) + 1) : N;
-  const unsigned lx0 = INPLACE ? (unsigned)((chi * (N + 1) + hl) * E) : (unsigned)((chi * H + hl) * E);
-  const unsigned ly0 = INPLACE ? (unsigned)((chi * N * (N + 1) + hl) * E) : (unsigned)((chi * N * H + hl) * E);
-  const unsigned lyz0 = (unsigned)((lrow * N * (N + 1) + clo) * E);
-  const unsigned lz0 = (unsigned)((lrow * N + clo) * (N + 1) * E);
-  const unsigned pos = (unsigned)(chi * N + clo);
-  constexpr unsigned FB = (unsigned)NR * E;
+  const CubeTransform<N, T> cube(t);
+  const unsigned pos = (unsigned)(cube.chi * N + cube.clo);
+  constexpr unsigned FB = (unsigned)(NR * sizeof(cx<T>));
 
   PairWalk walk(a.b);
   if (!walk.start()) return;
@@ -159,41 +125,7 @@ __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE)
       if constexpr (decltype(cc)::value == 0) static_for<PF>([&](auto e) { v[decltype(e)::value] = cmulc(fp[e], fx[e]); });
       static_for<CN>([&](auto e) { v[C0 + decltype(e)::value] = cmulc(p[e], xx[e]); });
     });
-    fft<N, -1>(v);
-    // x -> y
-#pragma unroll
-    for (int g = 0; g < NPH; ++g) {
-      if (grp == g) {
-        const unsigned b0 = opaque(lx0), b1 = opaque(lx0 + L1S * SX);
-        static_for<N>([&](auto l1) {
-          constexpr int L = decltype(l1)::value;
-          if constexpr (L < L1S) lds_at<L * SX>(lds, b0) = v[L];
-          else lds_at<(L - L1S) * SX>(lds, b1) = v[L];
-        });
-      }
-      __syncthreads();
-      if (grp == g) {
-        const unsigned b = opaque(ly0);
-        static_for<N>([&](auto m2) { v[m2] = lds_at<decltype(m2)::value * SY>(lds, b); });
-      }
-      if constexpr (!INPLACE) __syncthreads();
-    }
-    fft<N, -1>(v);
-    // y -> z
-#pragma unroll
-    for (int g = 0; g < NPH; ++g) {
-      if (gyz == g) {
-        const unsigned b = opaque(lyz0);
-        static_for<N>([&](auto l2) { lds_at<decltype(l2)::value * (N + 1) * E>(lds, b) = v[l2]; });
-      }
-      __syncthreads();
-      if (gyz == g) {
-        const unsigned b = opaque(lz0);
-        static_for<N>([&](auto m3) { v[m3] = lds_at<decltype(m3)::value * E>(lds, b); });
-      }
-      if constexpr (!INPLACE) __syncthreads();
-    }
-    fft<N, -1>(v);
+    cube.forward(v, lds);
     static_for<(N + pw_grp_k<N, T>() - 1) / pw_grp_k<N, T>()>([&](auto cc) {
       constexpr int G = pw_grp_k<N, T>(), C0 = decltype(cc)::value * G, CN = (N - C0 < G) ? N - C0 : G;
       T kv[CN];
@@ -203,41 +135,7 @@ __global__ void __launch_bounds__(N * N) __attribute__((amdgpu_waves_per_eu(WPE)
       __builtin_amdgcn_sched_barrier(0);
       static_for<CN>([&](auto e) { v[C0 + decltype(e)::value] = cscale(v[C0 + decltype(e)::value], kv[e]); });
     });
-    fft<N, +1>(v);
-    // z -> y
-#pragma unroll
-    for (int g = 0; g < NPH; ++g) {
-      if (gyz == g) {
-        const unsigned b = opaque(lz0);
-        static_for<N>([&](auto m3) { lds_at<decltype(m3)::value * E>(lds, b) = v[m3]; });
-      }
-      __syncthreads();
-      if (gyz == g) {
-        const unsigned b = opaque(lyz0);
-        static_for<N>([&](auto l2) { v[l2] = lds_at<decltype(l2)::value * (N + 1) * E>(lds, b); });
-      }
-      if constexpr (!INPLACE) __syncthreads();
-    }
-    fft<N, +1>(v);
-    // y -> x
-#pragma unroll
-    for (int g = 0; g < NPH; ++g) {
-      if (grp == g) {
-        const unsigned b = opaque(ly0);
-        static_for<N>([&](auto m2) { lds_at<decltype(m2)::value * SY>(lds, b) = v[m2]; });
-      }
-      __syncthreads();
-      if (grp == g) {
-        const unsigned b0 = opaque(lx0), b1 = opaque(lx0 + L1S * SX);
-        static_for<N>([&](auto l1) {
-          constexpr int L = decltype(l1)::value;
-          if constexpr (L < L1S) v[L] = lds_at<L * SX>(lds, b0);
-          else v[L] = lds_at<(L - L1S) * SX>(lds, b1);
-        });
-      }
-      if constexpr (!INPLACE) __syncthreads();
-    }
-    fft<N, +1>(v);
+    cube.inverse(v, lds);
     cx<T>* w = a.W + ((long)walk.j * a.b.nt + walk.ti) * NR;
     const bool more = walk.next();
     if (more) fetch();

@@ -6,6 +6,133 @@
 
 namespace fockmi {
 
+// rounds of a transpose through LDS and the LDS elements they need
+template <int N, int NPH>
+constexpr int pw_lds_elems() {
+  constexpr int H = N / NPH;
+  return NPH == 1 ? N * N * (N + 1) : (N * N * H > H * N * (N + 1) ? N * N * H : H * N * (N + 1));
+}
+
+template <int N, typename T>
+constexpr int pw_nph() {
+  return ((long)N * N * (N + 1) * (long)sizeof(cx<T>) > 160L * 1024) ? 2 : 1;
+}
+// 3D transform of one field of N^3 values by N * N threads, one line per thread in registers
+// (fft_reg.hpp); LDS carries the transposes (see fused.hip). x phase: the line along n1 at
+// (m2, m3) = (chi, clo); z phase: the line along n3 at (l1, l2) = (chi, clo).
+template <int N, typename T>
+struct CubeTransform {
+  static constexpr int NPH = pw_nph<N, T>();
+  static constexpr int E = (int)sizeof(cx<T>);
+  static constexpr int NTI = N * N;
+  static constexpr int H = N / NPH;
+  static constexpr int TPG = NTI / NPH;
+  static constexpr int NBK = N / NPH;
+  static constexpr bool XY_WAVES = TPG % 64 == 0;
+  static constexpr bool YZ_WAVES = XY_WAVES && (NBK * H) % 64 == 0;
+  static constexpr int kLdsElems = pw_lds_elems<N, NPH>();
+  // with one round both transposes use one array and every phase writes back to the slots it
+  // read, so each transpose needs one barrier
+  static constexpr bool INPLACE = NPH == 1;
+  static constexpr unsigned SX = INPLACE ? (unsigned)(N * (N + 1) * E) : (unsigned)(N * H * E);
+  static constexpr unsigned SY = INPLACE ? (unsigned)((N + 1) * E) : (unsigned)(H * E);
+  static constexpr int L1S = (int)((65535u / SX) + 1) < N ? (int)((65535u / SX) + 1) : N;
+  int grp, gyz, chi, clo;
+  unsigned lx0, ly0, lyz0, lz0;  // LDS byte offsets of the thread's elements in the transposes
+
+  __device__ __forceinline__ explicit CubeTransform(int t) {
+    grp = (NPH == 1) ? 0 : (XY_WAVES ? __builtin_amdgcn_readfirstlane(t / TPG) : t / TPG);
+    const int tl = t % TPG;
+    const int hl = tl % H;
+    clo = hl + H * grp;
+    chi = tl / H;
+    gyz = (NPH == 1) ? 0 : (YZ_WAVES ? __builtin_amdgcn_readfirstlane(chi / NBK) : chi / NBK);
+    const int lrow = chi % NBK;
+    lx0 = INPLACE ? (unsigned)((chi * (N + 1) + hl) * E) : (unsigned)((chi * H + hl) * E);
+    ly0 = INPLACE ? (unsigned)((chi * N * (N + 1) + hl) * E) : (unsigned)((chi * N * H + hl) * E);
+    lyz0 = (unsigned)((lrow * N * (N + 1) + clo) * E);
+    lz0 = (unsigned)((lrow * N + clo) * (N + 1) * E);
+  }
+
+  // v: the x-phase line in, the transformed z-phase line out
+  __device__ __forceinline__ void forward(cx<T> (&v)[N], cx<T>* lds) const {
+    fft<N, -1>(v);
+    // x -> y
+#pragma unroll
+    for (int g = 0; g < NPH; ++g) {
+      if (grp == g) {
+        const unsigned b0 = opaque(lx0), b1 = opaque(lx0 + L1S * SX);
+        static_for<N>([&](auto l1) {
+          constexpr int L = decltype(l1)::value;
+          if constexpr (L < L1S) lds_at<L * SX>(lds, b0) = v[L];
+          else lds_at<(L - L1S) * SX>(lds, b1) = v[L];
+        });
+      }
+      __syncthreads();
+      if (grp == g) {
+        const unsigned b = opaque(ly0);
+        static_for<N>([&](auto m2) { v[m2] = lds_at<decltype(m2)::value * SY>(lds, b); });
+      }
+      if constexpr (!INPLACE) __syncthreads();
+    }
+    fft<N, -1>(v);
+    // y -> z
+#pragma unroll
+    for (int g = 0; g < NPH; ++g) {
+      if (gyz == g) {
+        const unsigned b = opaque(lyz0);
+        static_for<N>([&](auto l2) { lds_at<decltype(l2)::value * (N + 1) * E>(lds, b) = v[l2]; });
+      }
+      __syncthreads();
+      if (gyz == g) {
+        const unsigned b = opaque(lz0);
+        static_for<N>([&](auto m3) { v[m3] = lds_at<decltype(m3)::value * E>(lds, b); });
+      }
+      if constexpr (!INPLACE) __syncthreads();
+    }
+    fft<N, -1>(v);
+  }
+
+  // v: the z-phase line in, the (unnormalised) x-phase line out
+  __device__ __forceinline__ void inverse(cx<T> (&v)[N], cx<T>* lds) const {
+    fft<N, +1>(v);
+    // z -> y
+#pragma unroll
+    for (int g = 0; g < NPH; ++g) {
+      if (gyz == g) {
+        const unsigned b = opaque(lz0);
+        static_for<N>([&](auto m3) { lds_at<decltype(m3)::value * E>(lds, b) = v[m3]; });
+      }
+      __syncthreads();
+      if (gyz == g) {
+        const unsigned b = opaque(lyz0);
+        static_for<N>([&](auto l2) { v[l2] = lds_at<decltype(l2)::value * (N + 1) * E>(lds, b); });
+      }
+      if constexpr (!INPLACE) __syncthreads();
+    }
+    fft<N, +1>(v);
+    // y -> x
+#pragma unroll
+    for (int g = 0; g < NPH; ++g) {
+      if (grp == g) {
+        const unsigned b = opaque(ly0);
+        static_for<N>([&](auto m2) { lds_at<decltype(m2)::value * SY>(lds, b) = v[m2]; });
+      }
+      __syncthreads();
+      if (grp == g) {
+        const unsigned b0 = opaque(lx0), b1 = opaque(lx0 + L1S * SX);
+        static_for<N>([&](auto l1) {
+          constexpr int L = decltype(l1)::value;
+          if constexpr (L < L1S) v[L] = lds_at<L * SX>(lds, b0);
+          else v[L] = lds_at<(L - L1S) * SX>(lds, b1);
+        });
+      }
+      if constexpr (!INPLACE) __syncthreads();
+    }
+    fft<N, +1>(v);
+  }
+};
+
 // a uniform load through the scalar cache: a vector load here would wait for the W stores
 // in flight, like every load that is waited for behind them
 __device__ __forceinline__ int ld_uniform(const int* p) {

@@ -252,10 +252,10 @@ struct Plan {
 
   // propagator pieces (prop_api.hip)
   fock_status kinetic(Cell& c, const c128* x, int nf, c128* y, const double a[3], hipStream_t st);
-  // vx_ready: vxb holds V_x x already
+  // vx_ready: vxb holds V_x x already; with acc, acc = acc_src + out as well
   fock_status h_apply(Cell& c, const c128* us, const c128* us2, const c128* x, c128* out, const c128* base,
                       double cre, double cim, const double* vloc, const double a[3], double alpha, hipStream_t st,
-                      bool vx_ready = false);
+                      bool vx_ready = false, const c128* acc_src = nullptr, c128* acc = nullptr);
   // acc <- x0 + sum_{m=1}^{order} phi_m, phi_m = (-i dt/m) h phi_{m-1}, phi_0 = x0 (acc distinct from x0)
   fock_status taylor_sum(Cell& c, const c128* us, const c128* us2, const c128* x0, c128* acc, const double* vloc,
                          const double a[3], double dt, double alpha, int order, hipStream_t st);

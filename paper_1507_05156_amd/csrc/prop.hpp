@@ -15,6 +15,25 @@ hipError_t launch_precond_mul(c128* F, const double* kpts, int nk, int nf, const
 hipError_t launch_hcombine(c128* out, const c128* base, const c128* kin, const c128* x, const c128* vx,
                            const double* vloc, double alpha, double cre, double cim, long count, int nr,
                            hipStream_t st);
+// The same with the kinetic term inside, for cubic grids of length 16, 20 and 24 (hfield.hip):
+// out = (base ? base : 0) + (cre + i cim) * (T[a] x + vloc .* x + alpha * vx), and with acc
+// acc = acc_src + out; out, base, vx, acc, acc_src are [nk][nf][nr] fields, out distinct from x
+struct HCubeArgs {
+  const c128* x;
+  c128* out;
+  const c128* base;
+  const c128* vx;
+  const double* vloc;
+  const c128* acc_src;
+  c128* acc;
+  const double* kpts;  // [nk][3]
+  Geom g;
+  double a[3];
+  double alpha, cre, cim;
+  int nf;
+};
+bool h_cube_supported(const Geom& g);
+hipError_t launch_h_cube(const HCubeArgs& a, int nk, hipStream_t st);
 // out[f] = sum_r |psi[f][r]|^2
 hipError_t launch_norms(double* out, const c128* psi, int nfields, int nr, hipStream_t st);
 // out6 = sum conj(L) * (k+G+a)_d * F, d = 0..2 as (re, im) pairs, over nk*nf Fourier-space fields

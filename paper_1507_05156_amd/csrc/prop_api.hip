@@ -47,10 +47,8 @@ fock_status Plan::kinetic(Cell& c, const c128* x, int nf, c128* y, const double 
 // second source set us2, the exchange term is the average alpha (V_x[u] + V_x[u2]) / 2.
 fock_status Plan::h_apply(Cell& c, const c128* us, const c128* us2, const c128* x, c128* out, const c128* base,
                           double cre, double cim, const double* vloc, const double a[3], double alpha,
-                          hipStream_t st, bool vx_ready) {
+                          hipStream_t st, bool vx_ready, const c128* acc_src, c128* acc) {
   fock_status s;
-  if ((s = field_bufs(c, {&kin}, c.nb)) != FOCK_OK) return s;
-  if ((s = kinetic(c, x, c.nb, (c128*)kin.ptr, a, st)) != FOCK_OK) return s;
   const c128* vx = nullptr;
   if (alpha != 0.0) {
     if ((s = field_bufs(c, {&vxb}, c.nb)) != FOCK_OK) return s;
@@ -62,8 +60,21 @@ fock_status Plan::h_apply(Cell& c, const c128* us, const c128* us2, const c128* 
     vx = (const c128*)vxb.ptr;
   }
   const long count = (long)c.nk * c.nb * c.nr;
-  hipError_t e = launch_hcombine(out, base, (const c128*)kin.ptr, x, vx, vloc, alpha, cre, cim, count, c.nr, st);
-  if (e != hipSuccess) return hip_fail(e, "h combine");
+  hipError_t e;
+  if (h_cube_supported(c.geom)) {
+    const HCubeArgs h{x, out, base, vx, vloc, acc_src, acc, (const double*)c.kvec.ptr, c.geom, {a[0], a[1], a[2]},
+                      alpha, cre, cim, c.nb};
+    if ((e = launch_h_cube(h, c.nk, st)) != hipSuccess) return hip_fail(e, "h");
+    return FOCK_OK;
+  }
+  if ((s = field_bufs(c, {&kin}, c.nb)) != FOCK_OK) return s;
+  if ((s = kinetic(c, x, c.nb, (c128*)kin.ptr, a, st)) != FOCK_OK) return s;
+  if ((e = launch_hcombine(out, base, (const c128*)kin.ptr, x, vx, vloc, alpha, cre, cim, count, c.nr, st)) != hipSuccess)
+    return hip_fail(e, "h combine");
+  if (!acc) return FOCK_OK;
+  if (acc != acc_src && (e = hipMemcpyAsync(acc, acc_src, count * sizeof(c128), hipMemcpyDeviceToDevice, st)) != hipSuccess)
+    return hip_fail(e, "copy psi");
+  if ((e = launch_scale_add(acc, out, 1.0, 0.0, count, st)) != hipSuccess) return hip_fail(e, "accumulate step");
   return FOCK_OK;
 }
 
@@ -72,19 +83,15 @@ fock_status Plan::taylor_sum(Cell& c, const c128* us, const c128* us2, const c12
                              hipStream_t st) {
   fock_status s;
   if ((s = field_bufs(c, {&phiA, &phiB}, c.nb)) != FOCK_OK) return s;
-  const size_t bytes = (size_t)c.nk * c.nb * c.nr * sizeof(c128);
-  const long count = (long)c.nk * c.nb * c.nr;
   c128* nxt = (c128*)phiB.ptr;
   c128* other = (c128*)phiA.ptr;
-  hipError_t e;
   // the first term reads x0 itself (when it is also the source array, its V_x has the pair symmetry)
   const c128* cur = x0;
-  if ((e = hipMemcpyAsync(acc, x0, bytes, hipMemcpyDeviceToDevice, st)) != hipSuccess)
-    return hip_fail(e, "copy psi");
   for (int m = 1; m <= order; ++m) {
     // phi_m = (-i dt/m) h phi_{m-1}
-    if ((s = h_apply(c, us, us2, cur, nxt, nullptr, 0.0, -dt / m, vloc, a, alpha, st)) != FOCK_OK) return s;
-    if ((e = launch_scale_add(acc, nxt, 1.0, 0.0, count, st)) != hipSuccess) return hip_fail(e, "accumulate step");
+    if ((s = h_apply(c, us, us2, cur, nxt, nullptr, 0.0, -dt / m, vloc, a, alpha, st, false, m == 1 ? x0 : acc, acc)) !=
+        FOCK_OK)
+      return s;
     cur = nxt;
     std::swap(nxt, other);
   }
