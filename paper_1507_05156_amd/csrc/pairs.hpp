@@ -7,6 +7,11 @@ namespace fockmi {
 
 constexpr int kPairTile = 8;   // targets of one tile: the targets one wave of stage 2 holds
 constexpr int kPairGroup = 64;  // targets of one workgroup of stage 2: those whose mirror sums meet there
+constexpr int kPairFew = 2;     // targets of a wave of stage 2 in rows too short to fill the device
+// the group of rows of `rows` targets: 8 waves of whole tiles where these make 2,048 waves (8 per CU)
+inline int pair_group(int rows, int nr) {
+  return (long)(nr / 64) * ((rows + kPairTile - 1) / kPairTile) < 2048 ? kPairGroup / kPairTile * kPairFew : kPairGroup;
+}
 
 // A block of pairs: nt targets from t0 on (index kt * nx + s) against nj sources from j0 on
 // (index ks * ns + band). With tri, targets and sources are the same fields (t0 == j0,
@@ -77,6 +82,7 @@ struct WsumArgs {
   int t0, nt, j0, nj, ns, tri;
   int nsrc;         // all sources
   int jb0;          // band index of source j0 within its k-point
+  int group;        // pair_group of the rows
   int nr;
   int np;           // n2 * n3 when the fields are in the paired order (out is natural), else 0
   int first, last;  // first / last block of these targets
@@ -88,6 +94,6 @@ template <typename TW, typename TM>
 hipError_t launch_wsum(const WsumArgs<TW, TM>& a, hipStream_t st);
 // dst = (accumulate ? dst : 0) + (sre + i sim) * sum over the groups of (mir + mcomp); mcomp may be NULL
 hipError_t launch_mirror_add(c128* dst, const c128* mir, const c64* mcomp, double sre, double sim, int accumulate, int nsrc,
-                             int nr, int rows, int tri, int np, hipStream_t st);
+                             int nr, int rows, int group, int tri, int np, hipStream_t st);
 
 }  // namespace fockmi

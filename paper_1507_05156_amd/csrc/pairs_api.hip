@@ -111,6 +111,7 @@ fock_status pairs_blocks(int nr, int np, int nt, int nj, int ns, const PairStage
   wa.nsrc = nj;
   wa.nr = nr;
   wa.np = np;
+  wa.group = pair_group(rows, nr);
   wa.accumulate = accumulate ? 1 : 0;
   wa.scale = scale;
   auto block = [&](int t0, int ntb, int j0, int njb, bool tri, bool first, bool last, bool mfirst) -> fock_status {
@@ -149,7 +150,7 @@ fock_status pairs_blocks(int nr, int np, int nt, int nj, int ns, const PairStage
     if (mr.tri && (s = block(t0, ntb, t0, ntb, true, t0 == 0, true, true)) != FOCK_OK) return s;
   }
   if (two && (e = launch_mirror_add(mr.dst, mir, wa.mcomp, mr.scale, mr.scale_im, mr.accumulate ? 1 : 0, nj, nr, rows,
-                                    mr.tri ? 1 : 0, np, st)) != hipSuccess)
+                                    wa.group, mr.tri ? 1 : 0, np, st)) != hipSuccess)
     return hip_fail(e, "mirror sums");
   return FOCK_OK;
 }
@@ -159,7 +160,7 @@ bool Plan::pairs_sized(int nr, int nt, int nj, int ns, size_t fb, bool sums32, b
   long njmax = 0;
   pairs_block_shape(nt, nj, ns, nr, fb, workspace_cap ? std::min(workspace_cap, pair_batch) : pair_batch,
                     sums32 && !two, tri, &rows, &njmax);
-  const size_t groups = (rows + kPairGroup - 1) / kPairGroup;
+  const size_t group = pair_group(rows, nr), groups = (rows + group - 1) / group;
   return pbatch.bytes >= (size_t)rows * njmax * fb &&
          prun.bytes >= (size_t)rows * nr * (sums32 ? sizeof(c64) : sizeof(c128)) &&
          (!two || (pmir.bytes >= groups * nj * nr * sizeof(c128) &&
@@ -186,7 +187,7 @@ fock_status Plan::run_pairs(int nr, int np, int nt, int nj, int ns, const PairSt
   g_last_error.clear();  // a smaller batch after a failed allocation is no failure
   if ((s = prun.ensure((size_t)rows * nr * (F32 ? sizeof(c64) : sizeof(c128)), workspace_cap, "pair sums")) != FOCK_OK)
     return s;
-  const int groups = (rows + kPairGroup - 1) / kPairGroup;
+  const int group = pair_group(rows, nr), groups = (rows + group - 1) / group;
   if (two) {
     if ((s = pmir.ensure((size_t)groups * nj * nr * sizeof(c128), workspace_cap, "mirror sums")) != FOCK_OK) return s;
     if (F32 && (s = pmcomp.ensure((size_t)groups * nj * nr * sizeof(c64), workspace_cap, "mirror compensation")) !=
