@@ -88,7 +88,7 @@ fock_status Plan::check_ready(int cell) const {
 fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, const c128* P, const c128* M, int ns,
                             c128* out, double scale, bool accumulate, hipStream_t st) {
   const int nr = c.nr, nt = ps.ntk * nx, nj = ps.nsk * ns;
-  const bool cube = c.Kt64.ptr != nullptr;  // the field fits on a CU
+  const bool cube = c.Kp.ptr != nullptr;  // the field fits on a CU
   // many targets: the fused FP64 kernel, which keeps each target's sum on its CU
   if (cube && !pair_rule(c, ps, nx, ns, X == P && P == M, false).pairs)
     return run_fused64(c, ps, X, nx, P, M, ns, out, scale, accumulate, st);
@@ -502,7 +502,7 @@ fock_status Plan::run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx,
   a.X = X;
   a.P = P;
   a.M = M;
-  a.Kt = (const double*)c.Kt64.ptr;
+  a.Kt = (const double*)c.Kp.ptr;
   a.qidx = ps.qidx;
   a.out = out;
   a.accs = (c128*)accs.ptr;
@@ -525,7 +525,7 @@ fock_status Plan::two_sided(Cell& c, const c128* X, int nx, const c128* us, doub
   const PairSet ps = c.fwd();
   const int nr = c.nr, nt = ps.ntk * nx, nj = ps.nsk * c.nb, n = c.geom.n1;
   const bool f32 = prec == FOCK_FP32_COMP;
-  const bool planes = f32 ? c.f32plain : c.Kt64.ptr == nullptr;
+  const bool planes = f32 ? c.f32plain : c.Kp.ptr == nullptr;
   *done = false;
   if (f32 && !planes && n == 32 && split_form) return FOCK_OK;
   if (!planes && n <= 24) {

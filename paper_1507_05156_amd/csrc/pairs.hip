@@ -348,7 +348,19 @@ hipError_t launch_pw(const PairArgs<T>& a, int slots, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <typename T>
+int phases(int n) {
+  switch (n) {
+    case 16: return pw_nph<16, T>();
+    case 20: return pw_nph<20, T>();
+    case 24: return pw_nph<24, T>();
+    default: return pw_nph<32, T>();
+  }
+}
+
 }  // namespace
+
+int pair_phases(int n, bool f64) { return f64 ? phases<double>(n) : phases<float>(n); }
 
 template <>
 int pair_w_slots<float>(int n, int num_cus) {

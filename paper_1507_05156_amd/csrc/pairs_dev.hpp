@@ -13,14 +13,22 @@ constexpr int pw_lds_elems() {
   return NPH == 1 ? N * N * (N + 1) : (N * N * H > H * N * (N + 1) ? N * N * H : H * N * (N + 1));
 }
 
+// Rounds per transpose where a field does not fit in LDS: three at 24^3 in FP64, whose rounds are
+// whole waves (two rounds of 288 threads are not) and of which two fit side by side; two at 32^3
+// in FP32 (four, two side by side, spill: 27 of the 216 k-points of 16 bands 233 -> 269 ms).
 template <int N, typename T>
 constexpr int pw_nph() {
-  return ((long)N * N * (N + 1) * (long)sizeof(cx<T>) > 160L * 1024) ? 2 : 1;
+  return (long)N * N * (N + 1) * (long)sizeof(cx<T>) <= 160L * 1024 ? 1 : (N % 3 == 0 ? 3 : 2);
 }
+
 // 3D transform of one field of N^3 values by N * N threads, one line per thread in registers
 // (fft_reg.hpp); LDS carries the transposes (see fused.hip). x phase: the line along n1 at
 // (m2, m3) = (chi, clo); z phase: the line along n3 at (l1, l2) = (chi, clo).
-template <int N, typename T>
+// TWOBUF: rounds go through two buffers in turn, over all transposes of a field: the threads of a
+// round read while those of the next one write, and one barrier per round covers both (a buffer
+// is written again only after the barrier that its readers have passed). Pairs of 24^3 in FP64,
+// 64 k-points of 16 bands: 78.1 ms in two rounds, 77.7 in three, 70.5 in three with two buffers.
+template <int N, typename T, bool TWOBUF = (pw_nph<N, T>() > 2)>
 struct CubeTransform {
   static constexpr int NPH = pw_nph<N, T>();
   static constexpr int E = (int)sizeof(cx<T>);
@@ -30,7 +38,8 @@ struct CubeTransform {
   static constexpr int NBK = N / NPH;
   static constexpr bool XY_WAVES = TPG % 64 == 0;
   static constexpr bool YZ_WAVES = XY_WAVES && (NBK * H) % 64 == 0;
-  static constexpr int kLdsElems = pw_lds_elems<N, NPH>();
+  static constexpr int kRound = pw_lds_elems<N, NPH>();  // elements of one round
+  static constexpr int kLdsElems = TWOBUF ? 2 * kRound : kRound;
   // with one round both transposes use one array and every phase writes back to the slots it
   // read, so each transpose needs one barrier
   static constexpr bool INPLACE = NPH == 1;
@@ -54,6 +63,10 @@ struct CubeTransform {
     lz0 = (unsigned)((lrow * N + clo) * (N + 1) * E);
   }
 
+  // byte offset of round r of the four transposes of a field
+  static constexpr unsigned buf(int r) { return TWOBUF && r % 2 ? (unsigned)(kRound * E) : 0u; }
+  static_assert(!TWOBUF || NPH > 1, "one round has one buffer");
+
   // v: the x-phase line in, the transformed z-phase line out
   __device__ __forceinline__ void forward(cx<T> (&v)[N], cx<T>* lds) const {
     fft<N, -1>(v);
@@ -61,7 +74,7 @@ struct CubeTransform {
 #pragma unroll
     for (int g = 0; g < NPH; ++g) {
       if (grp == g) {
-        const unsigned b0 = opaque(lx0), b1 = opaque(lx0 + L1S * SX);
+        const unsigned b0 = opaque(lx0 + buf(g)), b1 = opaque(lx0 + buf(g) + L1S * SX);
         static_for<N>([&](auto l1) {
           constexpr int L = decltype(l1)::value;
           if constexpr (L < L1S) lds_at<L * SX>(lds, b0) = v[L];
@@ -70,25 +83,25 @@ struct CubeTransform {
       }
       __syncthreads();
       if (grp == g) {
-        const unsigned b = opaque(ly0);
+        const unsigned b = opaque(ly0 + buf(g));
         static_for<N>([&](auto m2) { v[m2] = lds_at<decltype(m2)::value * SY>(lds, b); });
       }
-      if constexpr (!INPLACE) __syncthreads();
+      if constexpr (!INPLACE && !TWOBUF) __syncthreads();
     }
     fft<N, -1>(v);
     // y -> z
 #pragma unroll
     for (int g = 0; g < NPH; ++g) {
       if (gyz == g) {
-        const unsigned b = opaque(lyz0);
+        const unsigned b = opaque(lyz0 + buf(NPH + g));
         static_for<N>([&](auto l2) { lds_at<decltype(l2)::value * (N + 1) * E>(lds, b) = v[l2]; });
       }
       __syncthreads();
       if (gyz == g) {
-        const unsigned b = opaque(lz0);
+        const unsigned b = opaque(lz0 + buf(NPH + g));
         static_for<N>([&](auto m3) { v[m3] = lds_at<decltype(m3)::value * E>(lds, b); });
       }
-      if constexpr (!INPLACE) __syncthreads();
+      if constexpr (!INPLACE && !TWOBUF) __syncthreads();
     }
     fft<N, -1>(v);
   }
@@ -100,34 +113,34 @@ struct CubeTransform {
 #pragma unroll
     for (int g = 0; g < NPH; ++g) {
       if (gyz == g) {
-        const unsigned b = opaque(lz0);
+        const unsigned b = opaque(lz0 + buf(2 * NPH + g));
         static_for<N>([&](auto m3) { lds_at<decltype(m3)::value * E>(lds, b) = v[m3]; });
       }
       __syncthreads();
       if (gyz == g) {
-        const unsigned b = opaque(lyz0);
+        const unsigned b = opaque(lyz0 + buf(2 * NPH + g));
         static_for<N>([&](auto l2) { v[l2] = lds_at<decltype(l2)::value * (N + 1) * E>(lds, b); });
       }
-      if constexpr (!INPLACE) __syncthreads();
+      if constexpr (!INPLACE && !TWOBUF) __syncthreads();
     }
     fft<N, +1>(v);
     // y -> x
 #pragma unroll
     for (int g = 0; g < NPH; ++g) {
       if (grp == g) {
-        const unsigned b = opaque(ly0);
+        const unsigned b = opaque(ly0 + buf(3 * NPH + g));
         static_for<N>([&](auto m2) { lds_at<decltype(m2)::value * SY>(lds, b) = v[m2]; });
       }
       __syncthreads();
       if (grp == g) {
-        const unsigned b0 = opaque(lx0), b1 = opaque(lx0 + L1S * SX);
+        const unsigned b0 = opaque(lx0 + buf(3 * NPH + g)), b1 = opaque(lx0 + buf(3 * NPH + g) + L1S * SX);
         static_for<N>([&](auto l1) {
           constexpr int L = decltype(l1)::value;
           if constexpr (L < L1S) v[L] = lds_at<L * SX>(lds, b0);
           else v[L] = lds_at<(L - L1S) * SX>(lds, b1);
         });
       }
-      if constexpr (!INPLACE) __syncthreads();
+      if constexpr (!INPLACE && !TWOBUF) __syncthreads();
     }
     fft<N, +1>(v);
   }

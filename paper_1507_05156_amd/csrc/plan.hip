@@ -156,14 +156,8 @@ fock_status Plan::init_cell(Cell& c, const fock_cell_desc& d, int index) {
   }
   const bool cube = c.geom.n1 == c.geom.n2 && c.geom.n2 == c.geom.n3;
   if (prec != FOCK_FP32_COMP && cube && fused64_supported(c.geom.n1)) {
-    if ((s = c.Kt64.ensure((size_t)c.nq * c.nr * sizeof(double), 0, "fused FP64 kernel tables")) != FOCK_OK)
-      return s;
-    if ((e = launch_build_table_fused64((double*)c.Kt64.ptr, (const double*)ktmp.ptr, c.nq, c.geom.n1,
-                                        fused64_phases(c.geom.n1), 0)) != hipSuccess)
-      return hip_fail(e, "fused FP64 kernel table");
     if ((s = c.Kp.ensure((size_t)c.nq * c.nr * sizeof(double), 0, "pair kernel tables")) != FOCK_OK) return s;
-    if ((e = launch_build_table_pair64((double*)c.Kp.ptr, (const double*)ktmp.ptr, c.nq, c.geom.n1,
-                                       fused64_phases(c.geom.n1), 0)) != hipSuccess)
+    if ((e = launch_build_table_pair64((double*)c.Kp.ptr, (const double*)ktmp.ptr, c.nq, c.geom.n1, 0)) != hipSuccess)
       return hip_fail(e, "pair kernel table");
     c.f64f = prec == FOCK_FP64_FUSED;
   } else if (prec != FOCK_FP32_COMP || c.f32plain) {
@@ -229,7 +223,6 @@ void Plan::destroy() {
     c.qzero.release();
     c.Kt.release();
     c.SD.release();
-    c.Kt64.release();
     c.Kpl.release();
     c.Kp.release();
     c.kvec.release();

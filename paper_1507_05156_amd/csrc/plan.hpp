@@ -57,8 +57,7 @@ struct Cell {
   DevBuf qidx, qvec, qzero;   // int[nk*nk], double[nq*3], int[nq]
   DevBuf Kt;                  // float[nq][nr], fused-kernel layout (FP32 plans)
   DevBuf SD;                  // float[nq][nr/2][2], (S, D) pairs of the split 32^3 form (FP32 plans, n = 32)
-  DevBuf Kt64;                // double[nq][nr], fused FP64 kernel layout (FP64 plans, cubic grids up to 24)
-  DevBuf Kp;                  // float or double [nq][nr], the pair kernel's order (cubic grids with a one-CU kernel)
+  DevBuf Kp;                  // float or double [nq][nr], order of the pair kernels and the fused FP64 kernel (cubes of 16-32)
   DevBuf Kpl;                 // double[nq][nr] as [l1][l3][l2], for the plane passes (grids without a one-CU kernel)
   bool f64f = false;          // this cell runs the fused FP64 kernel
   bool f32plain = false;      // an FP32-form cell on a grid that is not cubic: complex64 plane passes, FP64 sums

@@ -94,7 +94,8 @@ hipError_t launch_build_table_f64(double* K, const double* qvec, const int* qzer
   return hipSuccess;
 }
 
-int fused_phases(int n);  // fused.hip
+int fused_phases(int n);           // fused.hip
+int pair_phases(int n, bool f64);  // pairs.hip
 
 namespace {
 
@@ -118,16 +119,12 @@ hipError_t launch_build_table_fused(float* Kt, const double* K, int nq, int n, h
   return build_fused_tables<float, 1>(Kt, K, nq, n, fused_phases(n), st);
 }
 
-hipError_t launch_build_table_fused64(double* Kt, const double* K, int nq, int n, int nph, hipStream_t st) {
-  return build_fused_tables<double, 1>(Kt, K, nq, n, nph, st);
-}
-
 hipError_t launch_build_table_pair32(float* Kp, const double* K, int nq, int n, hipStream_t st) {
-  return build_fused_tables<float, 4>(Kp, K, nq, n, fused_phases(n), st);
+  return build_fused_tables<float, 4>(Kp, K, nq, n, pair_phases(n, false), st);
 }
 
-hipError_t launch_build_table_pair64(double* Kp, const double* K, int nq, int n, int nph, hipStream_t st) {
-  return build_fused_tables<double, 2>(Kp, K, nq, n, nph, st);
+hipError_t launch_build_table_pair64(double* Kp, const double* K, int nq, int n, hipStream_t st) {
+  return build_fused_tables<double, 2>(Kp, K, nq, n, pair_phases(n, true), st);
 }
 
 }  // namespace fockmi

@@ -130,6 +130,19 @@ def every_call(plan, ref, n, nk, nb, tol):
         assert per_k(a, b) < tol
 
 
+@pytest.mark.parametrize("n,prec,nb,nphi", [(24, "fp64f", 1, 33), (24, "fp64f", 2, 31), (24, "fp32", 24, 7), (20, "fp32", 24, 13)])
+def test_separate_targets_of_either_form(device, n, prec, nb, nphi):
+    """phi apart from u with the targets on either side of a full device in FP64 (264 in the fused
+    kernel, whose 24^3 transposes take three rounds; 248 in pairs) and few of them in FP32 (pairs,
+    two partial sums per k-point); a k-range's bits are the full application's."""
+    print(f"[gpu] separate targets {n}^3 {prec} nb={nb} nphi={nphi}", flush=True)
+    plan, kp = make(n, (2, 2, 2), nb, prec)
+    u, phi = fields(8, nb, n, 51), fields(8, nphi, n, 52)
+    full = plan.apply(u, phi)
+    assert per_k(full, Ref(n, kp).apply(u, phi)) < (1e-6 if prec == "fp32" else 1e-10)
+    assert bool((plan.apply_krange(u, 3, 2, phi[3:5].contiguous()) == full[3:5]).all())
+
+
 LENGTHS = (16, 20, 24, 32)
 
 
@@ -181,6 +194,27 @@ def test_pair_form_in_a_graph(device, n, prec, nb):
         torch.cuda.synchronize()
         replay = out.clone()
         assert bool((replay == plan.apply(u)).all())
+
+
+def test_few_targets_first_under_capture(device):
+    """FP32 at 16^3: 512 targets eagerly (the fused kernel), then 56 for the first time inside a
+    capture, where their pair form finds no batch. Either form is within 1e-6 of the exact sum."""
+    import torch
+    print("[gpu] few targets first under capture", flush=True)
+    plan, _ = make(16, (2, 2, 2), 40, "fp32")
+    u, phi = fields(8, 40, 16, 61), fields(8, 7, 16, 62)
+    plan.apply(u, fields(8, 64, 16, 63))
+    out = torch.empty_like(phi)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        plan.apply(u, phi, out=out)
+    for seed in (64, 65):
+        phi.copy_(fields(8, 7, 16, seed))
+        g.replay()
+        torch.cuda.synchronize()
+        a = out.clone()
+        assert per_k(a, plan.apply(u, phi)) < 2e-6
 
 
 def test_first_call_under_capture(device):
