@@ -425,6 +425,10 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
     variant = bv;
     a.xcd_map = bx;
   }
+  // a first call under capture, where no batch can be allocated: a form that sums on the CU
+  if (variant == 3 && stream_captures(st) &&
+      !pairs_sized(nr, nitems, ps.nsk * ns, ns, nr * sizeof(c64), true, rule.tri, rule.tri))
+    variant = n == 32 && has_ls ? 1 : 0;
   if ((s = prepare(variant)) != FOCK_OK) return s;
   if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
   if ((e = launch(variant)) != hipSuccess) return hip_fail(e, "fused pair kernel");

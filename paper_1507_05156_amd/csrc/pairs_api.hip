@@ -44,16 +44,19 @@ bool Plan::pairs_tri_fits(int nt, int nr, size_t field_bytes) const {
   return !workspace_cap || (b * b * field_bytes <= workspace_cap && (size_t)nt * nr * sizeof(c128) <= workspace_cap);
 }
 
-// Measured costs of the forms on a 256-CU device, cubic grids: the fused kernels take `round`
-// us per source for every `slots` targets (a grid of fewer workgroups leaves CUs idle), the
-// pair form `pair` ns per pair one-sided and `sym` ns per pair of the sum with the pair
-// symmetry, whatever the shape of the sum.
+// Measured costs of the forms on a 256-CU device, cubic grids (64 k-points of 16 bands, phi apart
+// from u at 64 to 1,024 targets): `wg[m - 1]` us per source with m workgroups of a fused kernel
+// on every CU, one target each (fewer targets than CUs leave CUs idle); the pair form `pair` ns per
+// pair one-sided and `sym` ns per pair of the sum with the pair symmetry, whatever the shape of
+// the sum. Per source, 128 targets of 20^3: FP32 8.1 us fused and 4.4 in pairs, FP64 9.9 and 8.1;
+// 256: 8.3 and 8.3, 10.7 and 15.9.
 struct FormCost {
-  int n, slots;
-  double round, pair, sym;
+  int n, per_cu;  // grid length, workgroups of the fused kernel that a CU holds
+  double wg[4], pair, sym;
 };
-constexpr FormCost kCost64[] = {{16, 512, 7.1, 29.5, 15.6}, {20, 256, 11.2, 69.0, 37.0}, {24, 256, 36.0, 147.0, 79.0}};
-constexpr FormCost kCost32[] = {{16, 1024, 9.0, 15.0, 9.0}, {20, 512, 13.1, 36.0, 21.0}, {24, 256, 12.5, 68.0, 39.0}};
+constexpr FormCost kCost64[] = {{16, 2, {4.8, 6.9}, 27.5, 17.0}, {20, 1, {10.7}, 62.5, 35.0}, {24, 1, {31.9}, 126.0, 67.5}};
+constexpr FormCost kCost32[] = {
+    {16, 4, {4.2, 4.8, 7.0, 8.9}, 13.6, 10.5}, {20, 2, {8.3, 13.4}, 33.0, 20.5}, {24, 1, {13.1}, 62.5, 35.5}};
 
 Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns, bool same, bool f32) const {
   PairRule r;
@@ -66,9 +69,10 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
   // a cap without room for one FP32 partial sum's pairs (FP64: one pair) of one target
   if (workspace_cap && (size_t)(f32 ? std::min(ns, 16) : 1) * c.nr * (f32 ? sizeof(c64) : sizeof(c128)) > workspace_cap)
     return r;
-  r.pairs_ns = nt * fc->pair;
-  const double scale = num_cus / 256.0;
-  const double fused = fc->round * 1e3 * (double)((nt + (long)(fc->slots * scale) - 1) / std::max<long>(1, (long)(fc->slots * scale)));
+  r.pairs_ns = nt * fc->pair * 256.0 / num_cus;
+  const long per_cu = (nt + num_cus - 1) / num_cus;  // targets of the busiest CU
+  const int rest = (int)(per_cu % fc->per_cu);
+  const double fused = 1e3 * ((double)(per_cu / fc->per_cu) * fc->wg[fc->per_cu - 1] + (rest ? fc->wg[rest - 1] : 0.0));
   r.fused_ns = fused;
   // below 4 tiles the triangle is nearly the whole square, and the mirror sums cost a launch
   const bool tri_ok = same && ps.ntk == c.nk && ps.nsk == c.nk && ps.qidx == (const int*)c.qidx.ptr &&
@@ -82,13 +86,13 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
       // not depend on the blocks), and only where its 64 MiB hold a batch that is still the
       // faster form
       const size_t least = (size_t)std::min(ns, 16) * c.nr * sizeof(c64);
-      r.pairs = nt * nj <= (fc->n == 24 ? 96 * 96 : 128 * 128) && nt * fc->pair < fused &&
+      r.pairs = nt * nj <= (fc->n == 24 ? 96 * 96 : 128 * 128) && r.pairs_ns < fused &&
                 need + least <= kNoAllocBytes;
       return r;
     }
   }
-  if (tri_ok && nt * fc->sym < fused) r.pairs = r.tri = true;
-  else if (!f32) r.pairs = nt * fc->pair < fused;
+  if (tri_ok && nt * fc->sym * 256.0 / num_cus < fused) r.pairs = r.tri = true;
+  else r.pairs = r.pairs_ns < fused;
   return r;
 }
 
