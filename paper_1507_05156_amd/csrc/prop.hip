@@ -230,7 +230,8 @@ __device__ __forceinline__ void two_sum_add(double& s, double& c, double x) {
 
 // Of G = w * sum of the chunks: T[k][j][j] = (L^-1)_jj and, for i < j, T[k][j][i] =
 // conj(L^-1)_ji / (L^-1)_jj, so that q_j = T_jj (v_j + sum T_ji v_i); bad[k]
-__global__ void __launch_bounds__(64) gram_factor_kernel(c128* __restrict__ T, int* __restrict__ bad,
+constexpr int kFactorParts = 4;
+__global__ void __launch_bounds__(kFactorParts * kGramBands * kGramBands) gram_factor_kernel(c128* __restrict__ T, int* __restrict__ bad,
                                                          const double* __restrict__ part, int nchunk, int nb,
                                                          double w) {
   constexpr int N = kGramBands;
@@ -240,15 +241,37 @@ __global__ void __launch_bounds__(64) gram_factor_kernel(c128* __restrict__ T, i
   const int t = threadIdx.x;
   const long k = blockIdx.x;
   const double* p = part + k * nchunk * (2 * N * N);
-  for (int e = t; e < N * N; e += 64) {
-    // the chunks' sums with the error of each addition carried along
-    double re = 0.0, im = 0.0, cre = 0.0, cim = 0.0;
-    for (int c = 0; c < nchunk; ++c) {
-      two_sum_add(re, cre, p[(long)c * (2 * N * N) + 2 * e]);
-      two_sum_add(im, cim, p[(long)c * (2 * N * N) + 2 * e + 1]);
+  // the chunks' sums with the error of each addition carried along, a quarter of the chunks on each
+  // part of the workgroup. 32^3 / 1 k / 4 bands: 147 us with one wave for all of it (128 chunks in
+  // series), 31 us so
+  __shared__ double sh[kFactorParts - 1][N * N][4];
+  const int e0 = t % (N * N), pt = t / (N * N);
+  double re = 0.0, im = 0.0, cre = 0.0, cim = 0.0;
+  if (e0 / N < nb && e0 % N < nb) {
+    for (int c = pt; c < nchunk; c += kFactorParts) {
+      const c128 z = *(const c128*)(p + (long)c * (2 * N * N) + 2 * e0);
+      two_sum_add(re, cre, z.re);
+      two_sum_add(im, cim, z.im);
     }
-    g[e / N][e % N] = c128{w * (re + cre), w * (im + cim)};
-    li[e / N][e % N] = c128{0.0, 0.0};
+  }
+  if (pt > 0) {
+    double* o = sh[pt - 1][e0];
+    o[0] = re;
+    o[1] = cre;
+    o[2] = im;
+    o[3] = cim;
+  }
+  __syncthreads();
+  if (pt == 0) {
+    for (int u = 0; u < kFactorParts - 1; ++u) {
+      const double* o = sh[u][e0];
+      two_sum_add(re, cre, o[0]);
+      cre += o[1];
+      two_sum_add(im, cim, o[2]);
+      cim += o[3];
+    }
+    g[e0 / N][e0 % N] = c128{w * (re + cre), w * (im + cim)};
+    li[e0 / N][e0 % N] = c128{0.0, 0.0};
   }
   if (t == 0) fail = 0;
   __syncthreads();
@@ -258,7 +281,7 @@ __global__ void __launch_bounds__(64) gram_factor_kernel(c128* __restrict__ T, i
     if (!(q[t] > 0.0) || !(q[t] < 1e300) || !(d[t] < 1e150)) fail = 1;
   }
   __syncthreads();
-  for (int e = t; e < N * N; e += 64) {
+  if (const int e = t; e < N * N) {
     const int i = e / N, j = e % N;
     if (i < nb && j < nb) g[i][j] = i == j ? c128{1.0, 0.0} : cscale(g[i][j], d[i] * d[j]);
   }
@@ -302,7 +325,7 @@ __global__ void __launch_bounds__(64) gram_factor_kernel(c128* __restrict__ T, i
     if (!(s <= 1.5 * nb)) fail = 1;
     bad[k] = fail;
   }
-  for (int e = t; e < N * N; e += 64) {
+  if (const int e = t; e < N * N) {
     const int j = e / N, i = e % N;
     const c128 z = li[j][i];
     c128 o{0.0, 0.0};
@@ -464,6 +487,20 @@ size_t gram_work_bytes(int nk, int nr) {
   return (size_t)nk * ((gram_chunks(nk, nr) + 1) * mat + sizeof(int));
 }
 
+// The faster route by measured costs in us, 1 to 6 bands of 16^3 to 32^3 on 1 to 384 k-points.
+// Modified Gram-Schmidt keeps one CU per k-point busy (4 us and two passes per band, 5 passes per
+// pair of bands) until its traffic reaches 5 TB/s; the Gram matrix costs 4 launches and, per point,
+// what 16 fields cost on the matrix cores plus the bands' passes. 20^3 / 20 k / 1 band: 12 us
+// against 24; 16^3 / 8 k: 2 bands 16 against 21, 4 bands 41 against 22; 32^3 / 384 k: 2 bands 507
+// against 817, 4 bands 1,624 against 1,139.
+bool gram_pays(int nk, int nb, int nr) {
+  const double x = nr / 32768.0, pairs = 0.5 * nb * (nb - 1), points = (double)nk * nr;
+  const double alone = (nb * (4.0 + 16.0 * x) + pairs * 20.0 * x) * (1.0 + (nk < 256 ? nk / 256.0 : 1.0));
+  const double bytes = (3.0 * nb + 5.0 * pairs) * 16.0 * points;
+  const double mgs = alone > bytes / 5e6 ? alone : bytes / 5e6;
+  return 20.0 + points * (38.0 + 12.7 * nb) * 1e-6 < mgs;
+}
+
 hipError_t launch_gram_schmidt(c128* psi, int nk, int nb, int nr, double w, void* work, hipStream_t st) {
   if (nb > kGramBands || nr % 64 != 0) return hipErrorInvalidValue;
   const int want = gram_chunks(nk, nr);
@@ -474,7 +511,7 @@ hipError_t launch_gram_schmidt(c128* psi, int nk, int nb, int nr, double w, void
   hipError_t e;
   hipLaunchKernelGGL(gram16_kernel, dim3(nchunk, nk), dim3(64 * kGramWaves), 0, st, part, psi, nb, nr, len);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(gram_factor_kernel, dim3(nk), dim3(64), 0, st, T, bad, part, nchunk, nb, w);
+  hipLaunchKernelGGL(gram_factor_kernel, dim3(nk), dim3(kFactorParts * kGramBands * kGramBands), 0, st, T, bad, part, nchunk, nb, w);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const dim3 grid((nr + 255) / 256, nk);
   if (nb <= 4) hipLaunchKernelGGL(gram_apply_kernel<4>, grid, dim3(256), 0, st, psi, T, bad, nb, nr);

@@ -45,6 +45,7 @@ hipError_t launch_mgs(c128* psi, int nk, int nb, int nr, double w, hipStream_t s
 // Gram-Schmidt elsewhere; nb <= kGramBands, work: gram_work_bytes of device memory
 constexpr int kGramBands = 16;
 size_t gram_work_bytes(int nk, int nr);
+bool gram_pays(int nk, int nb, int nr);  // against launch_mgs
 hipError_t launch_gram_schmidt(c128* psi, int nk, int nb, int nr, double w, void* work, hipStream_t st);
 
 }  // namespace fockmi

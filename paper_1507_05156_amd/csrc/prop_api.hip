@@ -442,7 +442,8 @@ fock_status fock_orthonormalize(fockmi_plan plan, int cell, void* psi, void* str
   hipStream_t st = (hipStream_t)stream;
   const size_t need = gram_work_bytes(c.nk, c.nr);
   // the Gram route works in plan memory, which a capture cannot allocate
-  const bool gram = c.nb <= kGramBands && (p->gramb.bytes >= need || !stream_captures(st)) &&
+  const bool gram = c.nb <= kGramBands && gram_pays(c.nk, c.nb, c.nr) &&
+                    (p->gramb.bytes >= need || !stream_captures(st)) &&
                     p->gramb.ensure(need, p->workspace_cap, "Gram matrices") == FOCK_OK;
   g_last_error.clear();
   hipError_t e = gram ? launch_gram_schmidt((c128*)psi, c.nk, c.nb, c.nr, c.vol / c.nr, p->gramb.ptr, st)
