@@ -2,13 +2,14 @@
 """Throughput of the screened Fock-like exchange operator on one MI355X.
 
 A step is one full application V_x[u] u over every (k, i, k', j) pair of the
-workload (kernel tables resident, orbitals already in HBM), in the fused FP32
-form (complex64 pair FFTs; FP32 partial sums over at most 16 bands, added into
-Neumaier-compensated FP64 sums; at 32^3 each target split over two CUs, and,
-since the targets are the sources, each pair of k-points transformed once: the
-W of (k', j) on (k, i) is the conjugate of that of (k, i) on (k', j)).
-The plain FP64 path runs the same orbitals for the speed-up and the per-k
-error of the FP32 form; the FP64 oracle runs a bounded sample on the host.
+workload (kernel tables resident, orbitals already in HBM), in the FP32 form
+(complex64 pair FFTs; FP32 partial sums over at most 16 bands, added into
+Neumaier-compensated FP64 sums), in two stages: one kernel transforms the pairs
+of a block and writes their fields W, a second one reads them for the sums.
+Since the targets are the sources, each pair is transformed once: the W of
+(k', j) on (k, i) is the conjugate of that of (k, i) on (k', j).
+The FP64 path runs the same orbitals for the speed-up and the per-k error of
+the FP32 form; the FP64 oracle runs a bounded sample on the host.
 
 Prints one JSON line. Default workload: 32^3 grid, 6x6x6 k-mesh, 16 bands
 (11,943,936 pairs per step).
@@ -30,19 +31,20 @@ if ROOT not in sys.path:
 FP32_VALU_PEAK_TFLOPS = 157.3   # MI355X published FP32 vector peak
 HBM_PEAK_GBS = 8000.0           # MI355X HBM3E
 
-# Device-memory traffic of one fused 32^3 launch, from two rocprofv3 --pmc runs of
-# this script (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch), each scaled by what
-# the same counter reads for a 1 GiB device copy in the same run. Valid only for
-# the kernel sources whose digest is recorded; a changed kernel reports null.
+# Device-memory traffic of the pair kernels and sums of one application, from two
+# rocprofv3 --pmc runs of this script (FETCH_SIZE, then WRITE_SIZE, KiB summed over the
+# dispatches), each scaled by what the same counter reads for a 1 GiB device copy in the
+# same run. Valid only for the kernel sources whose digest is recorded; a changed kernel
+# reports null.
 COUNTER_TRAFFIC = {
     "sources_sha256": "ed3c6062830b6c85389eb1575f4bbd0ce3d19419dcf04a584a62100051d25fd3",
     "workload": 2,
     "fetch_kib": 1353198492.3125, "write_kib": 3354108010.0,
     "fetch_scale": 1048576 / 524319.625, "write_scale": 1.0,
 }
-# the sources of the dominant 32^3 kernel (split32_kernel) whose dispatches the counters measured
-KERNEL_SOURCES = ("paper_1507_05156_amd/csrc/split32.hip", "paper_1507_05156_amd/csrc/fft_reg.hpp",
-                  "paper_1507_05156_amd/csrc/fused_common.hpp", "paper_1507_05156_amd/csrc/kernels.hpp")
+# the sources of the two stages whose dispatches the counters measured
+KERNEL_SOURCES = tuple("paper_1507_05156_amd/csrc/" + f for f in
+                       ("pairs.hip", "pairs.hpp", "pairs_dev.hpp", "fft_reg.hpp", "fused_common.hpp"))
 
 
 def kernel_sources_digest() -> str:
@@ -64,12 +66,13 @@ def counter_traffic(workload: int):
 
 
 def symmetric_pair_ffts(n: int, nk: int, nb: int) -> int | None:
-    """Pairs whose FFTs the 32^3 split kernel runs when it uses the pair symmetry
-    (u as targets and sources, at least 3 k-points): each target runs the source
-    k-points k + d, d = 0 .. nk/2. None when the kernel runs every pair."""
-    if n != 32 or nk < 3 or os.environ.get("FOCKMI_SPLIT_SYM", "1") == "0":
+    """Pairs whose FFTs the two-stage form runs when it uses the pair symmetry (u as
+    targets and sources): target i runs the sources up to the end of its own tile of 8.
+    None where every pair runs."""
+    if n not in (24, 32) or os.environ.get("FOCKMI_SPLIT_SYM", "1") == "0":
         return None
-    return nk * nb * (nk // 2 + 1) * nb
+    nf = nk * nb
+    return sum(min(nf, 8 * (i // 8 + 1)) for i in range(nf))
 
 
 def flops_per_pair(nr: int) -> float:
@@ -386,10 +389,10 @@ def main():
     ap.add_argument("--steps", type=int, default=5)
     ap.add_argument("--warmup", type=int, default=1)
     ap.add_argument("--workload", type=int, default=2, help="2: 32^3/216k/16b (default); 1: 24^3/64k/16b")
-    ap.add_argument("--fp64-steps", type=int, default=1, help="timed plain FP64 applications (0 = skip)")
+    ap.add_argument("--fp64-steps", type=int, default=1, help="timed FP64 applications (0 = skip)")
     ap.add_argument("--fp64-form", choices=["plain", "fused"], default="plain",
-                    help="FP64 comparison path: the plain staged path (the reference of the speed-up), or the "
-                         "fused FP64 form (cubic 16^3-24^3 grids)")
+                    help="FP64 comparison path: the default FP64 precision (the reference of the speed-up), or the "
+                         "FP64 form of cubic 16^3-24^3 grids (fp64f)")
     ap.add_argument("--cpu-sources", type=int, default=96, help="source k-points in the oracle sample (0 = skip)")
     ap.add_argument("--cpu-workers", type=int, default=0,
                     help="oracle processes run at once (default: the host's CPU count, at most 16)")
@@ -462,7 +465,7 @@ def main():
           f"kernel {kern_avg_s * 1e3:.1f} ms", file=sys.stderr, flush=True)
     e32 = plan32.energy(ud)
 
-    # ---------------------------------------------------------- plain FP64 path
+    # ---------------------------------------------------------------- FP64 path
     fp64 = {}
     if args.fp64_steps > 0:
         plan64 = Plan(desc, prec="fp64" if args.fp64_form == "plain" else "fp64f")
@@ -520,12 +523,11 @@ def main():
                                f"a=10.26 bohr cubic, omega={omega} bohr^-1",
                    "pairs_per_step": pairs, "ffts_per_step": 2 * (sym_pairs or pairs),
                    "pairs_transformed_per_step": sym_pairs or pairs,
-                   "kernel": ("split FP32 pair kernel (each target on two CUs of one XCD"
-                              + ("; pair symmetry: each pair of k-points transformed once)" if sym_pairs else ")"))
-                   if n == 32 else "fused FP32 pair kernel"},
+                   "kernel": "two-stage FP32 pair form"
+                             + (" (pair symmetry: each pair transformed once)" if sym_pairs else "")},
         "roofline": {"bound": "hbm", "achieved": achieved_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved_gbs / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "split32_kernel" if n == 32 else f"fused_apply_kernel<{n}>", "kernel_ms_avg": kern_avg_s * 1e3, "launches": launches,
+                     "kernel": f"pair_w_kernel<{n}> + wsum_kernel (one application)", "kernel_ms_avg": kern_avg_s * 1e3, "launches": launches,
                      "alg_bytes_per_pair": nr * 8, "alg_bytes_per_launch": alg_bytes, "pairs_per_launch": pairs,
                      "traffic_bytes_per_pair": traffic / pairs if traffic else None,
                      "traffic_GBs": traffic / kern_avg_s / 1e9 if traffic else None,

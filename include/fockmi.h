@@ -241,7 +241,8 @@ fock_status taylor_energy_vjp(fockmi_plan plan, int cell, const void* psi, const
 fock_status taylor_current(fockmi_plan plan, int cell, const void* psi, const double A_over_c[3], double j_out[3],
                            void* stream);
 
-/* Modified Gram-Schmidt in band order, per k-point, in FP64 with the cell
+/* Gram-Schmidt in band order, per k-point, in FP64 (through the Gram matrix where that is faster
+ * and the fields are well conditioned, modified Gram-Schmidt elsewhere) with the cell
  * inner product (Omega/N_r) sum conj(a) b (the normalisation that Eq. (15)
  * assumes for occupied orbitals). psi: device [nk][nb][N_r] complex128 in place. */
 fock_status fock_orthonormalize(fockmi_plan plan, int cell, void* psi, void* stream);

@@ -598,8 +598,8 @@ int fused_variants(int n) { return n == 32 ? 3 : ((n == 16 || n == 20) ? 2 : 1);
 
 bool fused_has_lockstep(int n) { return n == 32; }
 
-// without a tuned choice at 32^3: the two-stage pair form (216 k / 16 bands: 1,088 ms against
-// 1,732 for the split form with u as targets, 27 of its k-points as targets 247 against 285)
+// without a tuned choice at 32^3: the two-stage pair form (216 k / 16 bands: 1,074 ms against
+// 1,729 for the split form with u as targets, 27 of its k-points as targets 235 against 285)
 int fused_default_variant(int n) { return n == 32 ? 3 : 0; }
 
 hipError_t launch_fused_apply(int n, const FusedArgs& a, hipStream_t st, int variant, const LockstepCfg* ls) {

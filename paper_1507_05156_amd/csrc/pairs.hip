@@ -18,7 +18,7 @@
 // 1,270 ms in this form with plain W accesses, 1,142 ms with non-temporal ones, 1,088 ms with
 // the next pair's first operands loaded before the stores, 1,076 ms with every access of stage 1
 // 16 bytes wide (stage 1 at 24^3 in FP32: 50.8 -> 45.1 ns per pair). One of eight k-point shards
-// of it (one-sided sums): 284.6 -> 241 ms.
+// of it (one-sided sums): 284.6 -> 235 ms.
 #include "pairs_dev.hpp"
 
 namespace fockmi {
@@ -64,7 +64,8 @@ __device__ __forceinline__ void ld_tab(rsrc_t r, unsigned t, int g, double* k) {
 }
 
 // elements whose loads are in flight together: operands of the pair product, kernel values
-// (24^3 FP64: groups of 4 took 120 ns per pair, of 12 115 ns; 24 kernel values at once spill)
+// (24^3 FP64, with transposes in two rounds: groups of 4 took 120 ns per pair, of 12 115 ns; 24
+// kernel values at once spill)
 template <int N, typename T>
 constexpr int pw_grp_px() { return 12; }
 // elements of the next pair's operands loaded before the current pair's W is stored (at 32^3

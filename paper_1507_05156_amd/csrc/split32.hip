@@ -1,4 +1,6 @@
-// Fused FP32 pair kernel for 32^3 cells with each target split over two CUs.
+// Fused FP32 pair kernel for 32^3 cells with each target split over two CUs: run where a wait limit
+// is set at plan creation or a tuning file names it (216 k / 16 bands: 1,729 ms, the two-stage form of
+// pairs.hip 1,074 ms).
 //
 // A 32^3 complex64 field (256 KiB) fills half of a CU's register file, so one
 // workgroup cannot keep a target's FP32 band sum (another 256 KiB) and the
