@@ -108,7 +108,8 @@ fock_status fock_plan_destroy(fockmi_plan plan);
  * conjugate term to the other row: the plan
  * then holds a batch of pair fields (8 GiB, less when the device or the plan's workspace
  * cap cannot hold it) and mirror sums of 24 bytes per grid point and 64 targets of a row
- * of blocks. The result is bitwise repeatable and agrees with the form that runs every
+ * of blocks. Few targets apart from u_occ run through the same batch, without the
+ * conjugate terms. The result is bitwise repeatable and agrees with the form that runs every
  * pair to rounding; that form runs instead when 64 fields' pairs exceed the plan's
  * workspace cap, or with FOCKMI_SPLIT_SYM=0 at plan creation. A plan created with
  * FOCKMI_SPLIT_WAIT_TICKS set runs 32^3 cells in the split form (each target on two CUs),
