@@ -20,30 +20,20 @@
 // 12 k / 6 bands 7.5 -> 2.1 ms. Loading the pair product's operands in groups of 4 instead of
 // 8, workgroups of 4 waves, two to a CU, and a plain last store were no faster.
 #include "pairs_dev.hpp"
+#include "plane_lds.hpp"
 
 namespace fockmi {
 
 namespace {
 
-constexpr int kPlaneWaves = 8;
-
-template <int N2, int N3, typename T>
-struct PlaneShape {
-  static constexpr int L = N2 > N3 ? N2 : N3;  // lanes of one plane
-  static constexpr int PL = 64 / L;            // planes of one wave
-  static constexpr int ROW = N3 + 1;           // padded row of the transpose
-  static constexpr int WORDS = PL * N2 * ROW;  // T values of one wave's transpose buffer (one component at a time)
-};
-
 // u[m3] of lane l2 <- v[l2] of lane m3, within each plane of the wave; the buffer is the
 // wave's own, LDS runs a wave's accesses in order, and one component at a time halves it
 template <int N2, int N3, typename T, bool FWD, int NA, int NB>
 __device__ __forceinline__ void plane_transpose(T* buf, int pl, int idx, cx<T> (&a)[NA], cx<T> (&b)[NB]) {
-  using S = PlaneShape<N2, N3, T>;
+  using S = PlaneShape<N2, N3>;
   // forward: a = lines along l2 held by lane m3, b = lines along m3 held by lane l2; inverse: the reverse
-  T* base = buf + pl * N2 * S::ROW;
-  T* col = base + (idx < N3 ? idx : 0);            // lane m3: element l2 at l2 * ROW
-  T* row = base + (idx < N2 ? idx : 0) * S::ROW;   // lane l2: element m3 at m3
+  T* col = buf + S::col(pl, idx);  // lane m3: element l2 at l2 * ROW
+  T* row = buf + S::row(pl, idx);  // lane l2: element m3 at m3
   const bool wr = pl < S::PL && idx < (FWD ? N3 : N2);
   static_for<2>([&](auto comp) {
     constexpr bool RE = decltype(comp)::value == 0;
@@ -84,7 +74,7 @@ __device__ __forceinline__ void line_pass(cx<T>* w, const double* __restrict__ K
 template <int N2, int N3, typename T>
 __global__ void __launch_bounds__(64 * kPlaneWaves) __attribute__((amdgpu_waves_per_eu(2)))
 pair_planes_kernel(PlaneArgs<T> a) {
-  using S = PlaneShape<N2, N3, T>;
+  using S = PlaneShape<N2, N3>;
   __shared__ T lds[kPlaneWaves * S::WORDS];
   static_assert(sizeof(lds) <= 160 * 1024, "LDS of the plane passes");
   constexpr int NP = N2 * N3;
@@ -152,7 +142,7 @@ pair_planes_kernel(PlaneArgs<T> a) {
 template <int N2, int N3, typename T>
 hipError_t launch_nn(const PlaneArgs<T>& a, int num_cus, hipStream_t st) {
   // workgroups of a CU: what the LDS holds, at most two (two waves per SIMD each)
-  using S = PlaneShape<N2, N3, T>;
+  using S = PlaneShape<N2, N3>;
   const long per = (a.b.npairs + 7) / 8;
   const long slots = (long)(num_cus / 8) * (kPlaneWaves * S::WORDS * sizeof(T) * 2 <= 160 * 1024 && sizeof(T) == 4 ? 2 : 1);
   const int g = (int)(per < slots ? per : slots);
