@@ -45,11 +45,20 @@ fock_status hip_fail(hipError_t e, const char* where) {
 
 bool valid_len(int n) { return n == 16 || n == 20 || n == 24 || n == 32; }
 
+thread_local bool g_capturing = false;
+
+void DevBuf::hold() {
+  if (ptr && g_capturing) held = true;
+}
+
 fock_status DevBuf::ensure(size_t need, size_t cap, const char* what) {
-  if (need <= bytes) return FOCK_OK;
+  if (need <= bytes) {
+    hold();
+    return FOCK_OK;
+  }
   if (cap && need > cap)
     return fail(FOCK_ERR_NOMEM, "%s: %zu bytes exceed the plan workspace cap of %zu bytes", what, need, cap);
-  release();
+  drop();
   hipError_t e = hipMalloc(&ptr, need);
   if (e != hipSuccess) {
     ptr = nullptr;
@@ -57,6 +66,7 @@ fock_status DevBuf::ensure(size_t need, size_t cap, const char* what) {
     return fail(FOCK_ERR_NOMEM, "%s: hipMalloc(%zu) failed: %s", what, need, hipGetErrorString(e));
   }
   bytes = need;
+  hold();
   return FOCK_OK;
 }
 
@@ -69,10 +79,19 @@ bool stream_captures(hipStream_t st) {
   return cs != hipStreamCaptureStatusNone;
 }
 
-void DevBuf::release() {
-  if (ptr) (void)hipFree(ptr);
+void DevBuf::drop() {
+  if (ptr && held) kept.push_back(ptr);
+  else if (ptr) (void)hipFree(ptr);
   ptr = nullptr;
   bytes = 0;
+  held = false;
+}
+
+void DevBuf::release() {
+  held = false;
+  drop();
+  for (void* p : kept) (void)hipFree(p);
+  kept.clear();
 }
 
 fock_status Plan::check_ready(int cell) const {
@@ -293,10 +312,10 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
             msum.ensure(nel * sizeof(c128), workspace_cap, "mirror FP64 sums") != FOCK_OK ||
             mcomp.ensure(nel * sizeof(c64), workspace_cap, "mirror compensation") != FOCK_OK ||
             mdone.ensure(split32_mirror_ctr_ints(nitems) * sizeof(int), workspace_cap, "mirror counters") != FOCK_OK) {
-          mpart.release();
-          msum.release();
-          mcomp.release();
-          mdone.release();
+          mpart.drop();
+          msum.drop();
+          mcomp.drop();
+          mdone.drop();
           sym = false;
           g_last_error.clear();  // the call goes on and succeeds: no failure to report
         }
@@ -318,6 +337,8 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
           sym_key[2] = ns;
           sym_key[3] = split_stagger_shift;
         }
+        sym_rank.hold();
+        sym_cnt.hold();
       }
       if (!fallbacks.ptr) {
         if ((st2 = fallbacks.ensure(sizeof(long long), workspace_cap, "fallback count")) != FOCK_OK) return st2;
@@ -720,6 +741,7 @@ fock_status fock_apply(fockmi_plan plan, int cell, const void* u_occ, const void
   const size_t bp = (size_t)c.nk * nphi * c.nr * sizeof(c128);
   if (overlap(vphi, bp, u_occ, bu) || overlap(vphi, bp, phi, bp))
     return fail(FOCK_ERR_ARG, "vphi overlaps an input array");
+  PlanCall use(p, (hipStream_t)stream);
   return p->apply_op(c, (const c128*)u_occ, (const c128*)phi, nphi, (c128*)vphi, (hipStream_t)stream);
 }
 
@@ -741,6 +763,7 @@ fock_status fock_apply_krange(fockmi_plan plan, int cell, const void* u_occ, int
   const size_t bp = (size_t)nk_out * nphi * c.nr * sizeof(c128);
   if (overlap(vphi, bp, u_occ, bu) || overlap(vphi, bp, phi, bp))
     return fail(FOCK_ERR_ARG, "vphi overlaps an input array");
+  PlanCall use(p, (hipStream_t)stream);
   return p->apply_krange(c, (const c128*)u_occ, k0, nk_out, (const c128*)phi, nphi, (c128*)vphi,
                          (hipStream_t)stream);
 }
@@ -755,6 +778,7 @@ fock_status fock_energy(fockmi_plan plan, int cell, const void* u_occ, double* e
   if (!u_occ) return fail(FOCK_ERR_ARG, "NULL device pointer");
   if (!aligned16(u_occ)) return fail(FOCK_ERR_ARG, "device pointers must be 16-byte aligned");
   hipStream_t st = (hipStream_t)stream;
+  PlanCall use(p, st);
   const size_t count = (size_t)c.nk * c.nb * c.nr;
   if ((s = p->vu.ensure(count * sizeof(c128), p->workspace_cap, "energy work array")) != FOCK_OK) return s;
   if ((s = p->apply_op(c, (const c128*)u_occ, (const c128*)u_occ, c.nb, (c128*)p->vu.ptr, st)) != FOCK_OK) return s;
@@ -779,6 +803,7 @@ fock_status fock_energy_vjp(fockmi_plan plan, int cell, const void* u_occ, doubl
   const size_t bu = (size_t)c.nk * c.nb * c.nr * sizeof(c128);
   if (overlap(g_u_occ, bu, u_occ, bu)) return fail(FOCK_ERR_ARG, "g_u_occ overlaps u_occ");
   hipStream_t st = (hipStream_t)stream;
+  PlanCall use(p, st);
   const c128* U = (const c128*)u_occ;
   c128* GU = (c128*)g_u_occ;
   // E_x = w sum conj(u) V_x[u] u, w = (g_s/2)(1/N_k)(Omega/N_r). u enters as the
@@ -824,6 +849,7 @@ fock_status fock_vjp(fockmi_plan plan, int cell, const void* u_occ, const void* 
                 (g_u_occ && overlap(g_phi, bp, g_u_occ, bu))))
     return fail(FOCK_ERR_ARG, "g_phi overlaps another array");
   hipStream_t st = (hipStream_t)stream;
+  PlanCall use(p, st);
   const double scale = -1.0 / c.nsrc;
   const c128* U = (const c128*)u_occ;
   const c128* F = (const c128*)phi;

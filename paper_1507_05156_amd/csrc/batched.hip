@@ -281,6 +281,9 @@ fock_status Plan::run_batched(const void* const* u, const void* const* phi, cons
   };
 
   if (!use_graph) {
+    for (DevBuf* b : {&B.accs, &B.queue, &B.counters}) b->hold();
+    for (int ci = 0; ci < nc; ++ci)
+      for (DevBuf* b : {&B.shadow_u[ci], &B.shadow_x[ci], &B.comp[ci]}) b->hold();
     if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
     if ((s = enqueue(st)) != FOCK_OK) return s;
     if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");
@@ -332,6 +335,7 @@ extern "C" fock_status fock_apply_batched(fockmi_plan plan, const void* const* u
     if (overlap(vphi[ci], bp, u_occ[ci], bu) || overlap(vphi[ci], bp, phi[ci], bp))
       return fail(FOCK_ERR_ARG, "cell %d: vphi overlaps an input array", ci);
   }
+  PlanCall use(p, (hipStream_t)stream);
   int nmax = 0;
   bool any_ds = false;
   for (const Cell& c : p->cells) {

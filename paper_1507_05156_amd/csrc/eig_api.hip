@@ -242,6 +242,7 @@ fock_status fock_eigensolve(fockmi_plan plan, int cell, const void* u_occ, const
     return fail(FOCK_ERR_ARG, "alpha and A/c must be finite");
   const size_t bytes = (size_t)c.nk * c.nb * c.nr * sizeof(c128);
   if (overlap(u_occ, bytes, phi, bytes)) return fail(FOCK_ERR_ARG, "phi must not alias u_occ");
+  PlanCall use(p, (hipStream_t)stream);
   return p->eigensolve(c, (const c128*)u_occ, (c128*)phi, vloc, A_over_c, alpha, tol, maxit, eig_host, res_host,
                        iters_host, (hipStream_t)stream);
 }
@@ -253,6 +254,7 @@ fock_status fock_excited_density(fockmi_plan plan, int cell, const void* phi, co
   if (s != FOCK_OK) return s;
   if (!phi || !psi || !nex_host) return fail(FOCK_ERR_ARG, "NULL argument");
   if (!aligned16(phi) || !aligned16(psi)) return fail(FOCK_ERR_ARG, "misaligned pointer");
+  PlanCall use(p, (hipStream_t)stream);
   return p->excited_density(p->cells[cell], (const c128*)phi, (const c128*)psi, (hipStream_t)stream, nex_host);
 }
 

@@ -20,12 +20,18 @@ fock_status fail(fock_status st, const char* fmt, ...);
 fock_status noalloc_setup(int device);
 fock_status hip_fail(hipError_t e, const char* where);
 
-// device allocation owned by the plan, grown on demand
+// Device allocation owned by the plan, grown on demand. A graph captured from a call refers to the
+// allocations that the call used: these are held, so that growth replaces them and keeps them until
+// the plan is destroyed.
 struct DevBuf {
   void* ptr = nullptr;
   size_t bytes = 0;
+  bool held = false;
+  std::vector<void*> kept;  // held allocations that a larger one has replaced
   fock_status ensure(size_t need, size_t cap, const char* what);
-  void release();
+  void hold();     // the call in progress uses the buffer as it is (ensure does this by itself)
+  void drop();     // without an allocation from here on
+  void release();  // frees everything
 };
 
 // whether the stream is being captured into a graph
@@ -272,6 +278,17 @@ struct Plan {
                           hipStream_t st);
   std::string key_for(const Cell& c, const PairSet& ps, int nx, const char* what) const;
   void save_tune();
+};
+
+// The time of one call of the ABI on a plan. While its stream is being captured, the buffers it
+// uses are held for the graph.
+extern thread_local bool g_capturing;
+class PlanCall {
+ public:
+  PlanCall(Plan*, hipStream_t st) { g_capturing = stream_captures(st); }
+  ~PlanCall() { g_capturing = false; }
+  PlanCall(const PlanCall&) = delete;
+  PlanCall& operator=(const PlanCall&) = delete;
 };
 
 }  // namespace fockmi

@@ -155,6 +155,7 @@ fock_status taylor_step(fockmi_plan plan, int cell, void* psi, const double* vlo
   if ((s = check_step_args(c, dt, order, A_over_c)) != FOCK_OK) return s;
   if (!std::isfinite(alpha)) return fail(FOCK_ERR_ARG, "alpha is not finite");
   hipStream_t st = (hipStream_t)stream;
+  PlanCall use(p, st);
   if ((s = p->field_bufs(c, {&p->psi0}, c.nb)) != FOCK_OK) return s;
   const size_t bytes = (size_t)c.nk * c.nb * c.nr * sizeof(c128);
   c128* P = (c128*)psi;
@@ -182,6 +183,7 @@ fock_status taylor_step_pc(fockmi_plan plan, int cell, void* psi, const double* 
   if ((s = check_step_args(c, dt, order, A_mid)) != FOCK_OK) return s;
   if (!std::isfinite(alpha)) return fail(FOCK_ERR_ARG, "alpha is not finite");
   hipStream_t st = (hipStream_t)stream;
+  PlanCall use(p, st);
   if ((s = p->field_bufs(c, {&p->psi0, &p->predb}, c.nb)) != FOCK_OK) return s;
   const size_t bytes = (size_t)c.nk * c.nb * c.nr * sizeof(c128);
   c128* P = (c128*)psi;
@@ -217,6 +219,7 @@ fock_status taylor_step_vjp(fockmi_plan plan, int cell, const void* psi_n, const
   if (overlap(g_psi, bytes, psi_n, bytes) || overlap(g_psi, bytes, g_next, bytes))
     return fail(FOCK_ERR_ARG, "g_psi overlaps an input");
   hipStream_t st = (hipStream_t)stream;
+  PlanCall use(p, st);
   const long count = (long)c.nk * c.nb * c.nr;
   // forward recomputation: phi_0 .. phi_{M-1}
   if ((s = p->phis.ensure(bytes * order, p->workspace_cap, "stored Taylor terms")) != FOCK_OK) return s;
@@ -381,6 +384,7 @@ fock_status taylor_energy(fockmi_plan plan, int cell, const void* psi, const dou
   fock_status s = common_checks(plan, cell, &p);
   if (s != FOCK_OK) return s;
   if (!e_out) return fail(FOCK_ERR_ARG, "e_out is NULL");
+  PlanCall use(p, (hipStream_t)stream);
   hdd e{0.0, 0.0};
   s = energy_impl(p, p->cells[cell], psi, vloc, A_over_c, alpha, 1.0, &e, grad_psi, grad_a, (hipStream_t)stream);
   *e_out = e.hi + e.lo;
@@ -394,6 +398,7 @@ fock_status taylor_excitation_energy(fockmi_plan plan, int cell, const void* psi
   fock_status s = common_checks(plan, cell, &p);
   if (s != FOCK_OK) return s;
   if (!e_ex) return fail(FOCK_ERR_ARG, "e_ex is NULL");
+  PlanCall use(p, (hipStream_t)stream);
   hdd et{0.0, 0.0}, e0{0.0, 0.0};
   if ((s = energy_impl(p, p->cells[cell], psi_t, vloc, A_t, alpha, 1.0, &et, nullptr, nullptr, (hipStream_t)stream)) !=
       FOCK_OK)
@@ -413,6 +418,7 @@ fock_status taylor_energy_vjp(fockmi_plan plan, int cell, const void* psi, const
   if (s != FOCK_OK) return s;
   if (!std::isfinite(g_e)) return fail(FOCK_ERR_ARG, "g_e is not finite");
   if (!g_psi && !g_a) return fail(FOCK_ERR_ARG, "both outputs are NULL");
+  PlanCall use(p, (hipStream_t)stream);
   return energy_impl(p, p->cells[cell], psi, vloc, A_over_c, alpha, g_e, nullptr, g_psi, g_a, (hipStream_t)stream);
 }
 
@@ -423,6 +429,7 @@ fock_status taylor_current(fockmi_plan plan, int cell, const void* psi, const do
   if (s != FOCK_OK) return s;
   if (!j_out) return fail(FOCK_ERR_ARG, "j_out is NULL");
   Cell& c = p->cells[cell];
+  PlanCall use(p, (hipStream_t)stream);
   // J = -(1/Omega) dE/d(A/c); V_x does not depend on A in the velocity gauge, so
   // only the kinetic term enters (alpha = 0)
   double ga[3];
@@ -440,6 +447,7 @@ fock_status fock_orthonormalize(fockmi_plan plan, int cell, void* psi, void* str
   if (!psi) return fail(FOCK_ERR_ARG, "psi is NULL");
   if (!aligned16(psi)) return fail(FOCK_ERR_ARG, "misaligned pointer");
   hipStream_t st = (hipStream_t)stream;
+  PlanCall use(p, st);
   const size_t need = gram_work_bytes(c.nk, c.nr);
   // the Gram route works in plan memory, which a capture cannot allocate
   const bool gram = c.nb <= kGramBands && gram_pays(c.nk, c.nb, c.nr) &&
