@@ -8,6 +8,14 @@
  * nothing throws across the ABI; fock_last_error() gives a thread-local
  * message for the last failing call.
  *
+ * Threads and streams: calls on one plan may come from several threads; one waits for the other to
+ * return. They share the plan's buffers, so work that they put on different streams must not overlap,
+ * with these exceptions: fock_orthonormalize, and on FOCK_FP64_FUSED cells of 16^3 and 20^3 without a
+ * source sub-mesh fock_apply, fock_apply_krange, fock_vjp and fock_energy_vjp, may be put on any
+ * streams (the library orders their use of the buffers; graphs captured from them use none). Replays
+ * of graphs captured from other calls count as the call's work. The buffers that a captured call uses
+ * stay in place until fock_plan_destroy.
+ *
  * Operation (Sato, Taniguchi, Shinohara, Yabana, Sec. II C "Nonlocal
  * Fock-like term", Eqs. (14)-(16); HSE composition Eq. (8)):
  *

@@ -177,6 +177,8 @@ fock_status Plan::run_pairs(int nr, int np, int nt, int nj, int ns, const PairSt
   constexpr bool F32 = sizeof(TM) == 4;
   const size_t fb = (size_t)nr * sizeof(cx<TW>);
   const bool two = mr.dst != nullptr;
+  // sums of this precision at 16^3 and 20^3 may run on several streams at once
+  if (prec == FOCK_FP64_FUSED) PlanCall::order();
   size_t budget = workspace_cap ? std::min(workspace_cap, batch) : batch;
   fock_status s;
   int rows = 0;

@@ -236,6 +236,8 @@ void Plan::destroy() {
   eig.release();
   if (host_pinned) (void)hipHostFree(host_pinned);
   host_pinned = nullptr;
+  if (done) (void)hipEventDestroy(done);
+  done = nullptr;
   magic = 0;
 }
 

@@ -5,6 +5,7 @@
 
 #include <functional>
 #include <initializer_list>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -36,6 +37,8 @@ struct DevBuf {
 
 // whether the stream is being captured into a graph
 bool stream_captures(hipStream_t st);
+// whether that of this thread's call in progress is
+extern thread_local bool g_capturing;
 
 inline bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
@@ -195,6 +198,9 @@ struct Plan {
   BatchState bstate;
   EigState eig;
   int num_cus = 0;
+  std::mutex calls;                         // one call at a time (PlanCall)
+  hipEvent_t done = nullptr;                // recorded behind the last ordered call's work (PlanCall)
+  bool done_recorded = false;
 
   std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_events;
   double prof_ms = 0.0;
@@ -280,15 +286,23 @@ struct Plan {
   void save_tune();
 };
 
-// The time of one call of the ABI on a plan. While its stream is being captured, the buffers it
-// uses are held for the graph.
-extern thread_local bool g_capturing;
+// One call of the ABI on a plan: calls of other threads wait for it to return. Where it uses scratch
+// that calls on other streams may use at the same time (order()), its work waits for that of the last
+// such call, and an event is recorded at its end for the next. While the stream is being captured
+// nothing is ordered (the graph runs later), and the buffers that the call uses are held for it.
 class PlanCall {
  public:
-  PlanCall(Plan*, hipStream_t st) { g_capturing = stream_captures(st); }
-  ~PlanCall() { g_capturing = false; }
+  PlanCall(Plan* p, hipStream_t st);
+  ~PlanCall();
   PlanCall(const PlanCall&) = delete;
   PlanCall& operator=(const PlanCall&) = delete;
+  static void order();  // of this thread's call in progress
+
+ private:
+  Plan* p_;
+  hipStream_t st_;
+  std::lock_guard<std::mutex> lock_;
+  bool ordered_ = false;
 };
 
 }  // namespace fockmi

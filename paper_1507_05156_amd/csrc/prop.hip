@@ -490,7 +490,8 @@ size_t gram_work_bytes(int nk, int nr) {
 
 // The faster route by measured costs in us, 1 to 6 bands of 16^3 to 32^3 on 1 to 384 k-points.
 // Modified Gram-Schmidt keeps one CU per k-point busy (4 us and two passes per band, 5 passes per
-// pair of bands) until its traffic reaches 5 TB/s; the Gram matrix costs 4 launches and, per point,
+// pair of bands) until its traffic reaches 5 TB/s; the Gram matrix costs 4 launches, the
+// event that orders the use of its scratch (3 us) and, per point,
 // what 16 fields cost on the matrix cores plus the bands' passes. 20^3 / 20 k / 1 band: 12 us
 // against 24; 16^3 / 8 k: 2 bands 16 against 21, 4 bands 41 against 22; 32^3 / 384 k: 2 bands 507
 // against 817, 4 bands 1,624 against 1,139.
@@ -499,7 +500,7 @@ bool gram_pays(int nk, int nb, int nr) {
   const double alone = (nb * (4.0 + 16.0 * x) + pairs * 20.0 * x) * (1.0 + (nk < 256 ? nk / 256.0 : 1.0));
   const double bytes = (3.0 * nb + 5.0 * pairs) * 16.0 * points;
   const double mgs = alone > bytes / 5e6 ? alone : bytes / 5e6;
-  return 20.0 + points * (38.0 + 12.7 * nb) * 1e-6 < mgs;
+  return 23.0 + points * (38.0 + 12.7 * nb) * 1e-6 < mgs;
 }
 
 hipError_t launch_gram_schmidt(c128* psi, int nk, int nb, int nr, double w, void* work, hipStream_t st) {

@@ -449,11 +449,12 @@ fock_status fock_orthonormalize(fockmi_plan plan, int cell, void* psi, void* str
   hipStream_t st = (hipStream_t)stream;
   PlanCall use(p, st);
   const size_t need = gram_work_bytes(c.nk, c.nr);
-  // the Gram route works in plan memory, which a capture cannot allocate
-  const bool gram = c.nb <= kGramBands && gram_pays(c.nk, c.nb, c.nr) &&
-                    (p->gramb.bytes >= need || !stream_captures(st)) &&
+  // the Gram route works in plan memory; captured calls need none, so that graphs of one plan may
+  // replay on several streams at once
+  const bool gram = c.nb <= kGramBands && gram_pays(c.nk, c.nb, c.nr) && !g_capturing &&
                     p->gramb.ensure(need, p->workspace_cap, "Gram matrices") == FOCK_OK;
   g_last_error.clear();
+  if (gram) PlanCall::order();  // calls may run on several streams at once
   hipError_t e = gram ? launch_gram_schmidt((c128*)psi, c.nk, c.nb, c.nr, c.vol / c.nr, p->gramb.ptr, st)
                       : launch_mgs((c128*)psi, c.nk, c.nb, c.nr, c.vol / c.nr, st);
   if (e != hipSuccess) return hip_fail(e, "Gram-Schmidt");

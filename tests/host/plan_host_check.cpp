@@ -2,6 +2,7 @@
 // named on the command line; exits with 0 if it holds, else prints what does not.
 #include <cmath>
 #include <functional>
+#include <thread>
 
 #include "../../include/fockmi.h"
 #include "fake_hip.hpp"
@@ -74,7 +75,7 @@ struct Held {
   }
 };
 
-// A graph captured from a plan refers to the plan's buffers: they stay where they are while eager
+// A graph captured from a plan refers to the plan's buffers (here all that there are): they stay where they are while eager
 // calls of other kinds (an adjoint, more targets, a larger cell) make the plan grow them, and the
 // plan frees everything when it is destroyed.
 void captured_buffers_stay() {
@@ -84,7 +85,6 @@ void captured_buffers_stay() {
   };
   const std::vector<Form> forms = {{FOCK_FP32_COMP, {cube(24, 64, 16), cube(24, 64, 20)}},
                                    {FOCK_FP64_FUSED, {cube(24, 64, 16), cube(24, 64, 20)}},
-                                   {FOCK_FP64_FUSED, {cube(20, 27, 12), cube(20, 64, 16)}},
                                    {FOCK_FP64, {cube(16, 8, 4), cube(16, 64, 4)}},
                                    {FOCK_FP64, {cube(32, 8, 16), cube(32, 27, 16)}},
                                    {FOCK_FP32_COMP, {cube(32, 27, 16), cube(32, 64, 16)}}};
@@ -95,7 +95,6 @@ void captured_buffers_stay() {
       const hipStream_t q = fake::stream(0);
       void *u = p.fields(), *out = p.fields(), *psi = p.fields();
       OK(fock_apply(p.h, 0, u, u, p.cells[0].nb, out, q));
-      OK(fock_orthonormalize(p.h, 0, psi, q));
       fake::st().capturing.insert(q);
       OK(fock_apply(p.h, 0, u, u, p.cells[0].nb, out, q));
       OK(fock_orthonormalize(p.h, 0, psi, q));
@@ -132,7 +131,114 @@ void growth_frees() {
   CHECK(fake::st().live.size() <= n + 8);
 }
 
+// Calls that the header lets run on any streams, and the others that use the same scratch: of each two the
+// first records an event behind its last launch, and the second's stream waits for it before its first.
+void streams_in_order() {
+  for (int n : {16, 20}) {
+    TestPlan p(FOCK_FP64_FUSED, {cube(n, 8, 4)});
+    void *u = p.fields(), *out = p.fields(), *psi = p.fields(), *phi = p.fields(), *g = p.fields(), *gu = p.fields();
+    const double a[3] = {0.0, 0.0, 0.01};
+    double e = 0, ga[3];
+    using Call = std::function<void(hipStream_t)>;
+    const std::vector<Call> calls = {
+        [&](hipStream_t q) { OK(fock_apply(p.h, 0, u, u, 4, out, q)); },
+        [&](hipStream_t q) { OK(fock_apply(p.h, 0, u, phi, 4, out, q)); },
+        [&](hipStream_t q) { OK(fock_apply_krange(p.h, 0, u, 1, 2, phi, 4, out, q)); },
+        [&](hipStream_t q) { OK(fock_energy_vjp(p.h, 0, u, 1.0, gu, q)); },
+        [&](hipStream_t q) { OK(fock_vjp(p.h, 0, u, phi, 4, g, gu, out, q)); },
+        [&](hipStream_t q) { OK(fock_orthonormalize(p.h, 0, psi, q)); },
+        [&](hipStream_t q) { OK(fock_energy(p.h, 0, u, &e, nullptr, q)); },
+        [&](hipStream_t q) { OK(taylor_step(p.h, 0, psi, nullptr, a, 0.01, 0.25, 2, nullptr, q)); },
+        [&](hipStream_t q) { OK(taylor_step_vjp(p.h, 0, psi, nullptr, a, 0.01, 0.25, 2, g, gu, ga, q)); },
+        [&](hipStream_t q) { OK(taylor_energy(p.h, 0, psi, nullptr, a, 0.25, &e, gu, ga, q)); }};
+    // the calls' kernels that use the shared scratch
+    auto shared = [](const fake::Op& o) {
+      return o.kind == fake::Op::Launch && (o.name.find("pair_w") != std::string::npos ||
+                                            o.name.find("wsum") != std::string::npos ||
+                                            o.name.find("mirror_add") != std::string::npos ||
+                                            o.name.find("gram") != std::string::npos);
+    };
+    for (const Call& first : calls)
+      for (const Call& second : calls) {
+        std::vector<fake::Op>& ops = fake::st().ops;
+        ops.clear();
+        first(fake::stream(1));
+        const size_t cut = ops.size();
+        second(fake::stream(2));
+        size_t last = cut, next = ops.size(), recorded = 0, waited = ops.size();
+        void* ev = nullptr;
+        for (size_t i = 0; i < cut; ++i)
+          if (shared(ops[i])) last = i;
+        for (size_t i = last; i < cut; ++i)
+          if (ops[i].kind == fake::Op::Record && ops[i].stream == fake::stream(1)) recorded = i, ev = ops[i].event;
+        for (size_t i = ops.size(); i-- > cut;) {
+          if (shared(ops[i])) next = i;
+          if (ops[i].kind == fake::Op::Wait && ops[i].stream == fake::stream(2) && ops[i].event == ev) waited = i;
+        }
+        CHECK(last < cut && ev && recorded > last && waited < next && next < ops.size());
+      }
+  }
+}
+
+// Two threads on one plan: the work of one call is enqueued whole before another call's begins.
+void threads_one_at_a_time() {
+  TestPlan p(FOCK_FP64_FUSED, {cube(16, 8, 4)});
+  void* u = p.fields();
+  void* outs[2] = {p.fields(), p.fields()};
+  void* psis[2] = {p.fields(), p.fields()};
+  auto run = [&](int id) {
+    for (int i = 0; i < 200; ++i) {
+      OK(fock_apply(p.h, 0, u, u, 4, outs[id], fake::stream(id + 1)));
+      OK(fock_orthonormalize(p.h, 0, psis[id], fake::stream(id + 1)));
+    }
+  };
+  fake::st().ops.clear();
+  std::thread a(run, 0), b(run, 1);
+  a.join();
+  b.join();
+  // a call ends with its record: until then every operation is of one thread
+  long owner = 0;
+  size_t mixed = 0, records = 0;
+  for (const fake::Op& o : fake::st().ops) {
+    if (owner && o.thread != owner) ++mixed;
+    owner = o.kind == fake::Op::Record ? 0 : o.thread;
+    records += o.kind == fake::Op::Record;
+  }
+  CHECK(mixed == 0);
+  CHECK(records == 800);
+}
+
+// Captured calls that need no plan memory use none, also on a plan whose buffers are there: their graphs
+// may replay on several streams at once.
+void captures_without_plan_memory() {
+  for (int n : {16, 20}) {
+    TestPlan p(FOCK_FP64_FUSED, {cube(n, 8, 4)});
+    const hipStream_t q = fake::stream(0);
+    void *u = p.fields(), *out = p.fields(), *psi = p.fields(), *phi = p.fields(), *g = p.fields(), *gu = p.fields();
+    auto calls = [&] {
+      OK(fock_apply(p.h, 0, u, u, 4, out, q));
+      OK(fock_apply(p.h, 0, u, phi, 4, out, q));
+      OK(fock_apply_krange(p.h, 0, u, 1, 2, phi, 4, out, q));
+      OK(fock_vjp(p.h, 0, u, phi, 4, g, gu, out, q));
+      OK(fock_energy_vjp(p.h, 0, u, 1.0, gu, q));
+      OK(fock_orthonormalize(p.h, 0, psi, q));
+    };
+    calls();
+    CHECK(fake::launches("pair_w") > 0 && fake::launches("gram") > 0);
+    const size_t from = fake::st().ops.size();
+    fake::st().capturing.insert(q);
+    calls();
+    fake::st().capturing.clear();
+    CHECK(fake::launches("fused64", from) + fake::launches("mgs", from) == fake::launches("", from));
+    CHECK(fake::st().bad_mallocs == 0);
+    fake::st().ops.clear();
+  }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"streams_in_order", streams_in_order},
+    {"threads_one_at_a_time", threads_one_at_a_time},
+    {"captures_without_plan_memory", captures_without_plan_memory},
     {"captured_buffers_stay", captured_buffers_stay},
     {"growth_frees", growth_frees},
 };
