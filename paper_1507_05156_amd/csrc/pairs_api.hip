@@ -159,16 +159,27 @@ fock_status pairs_blocks(int nr, int np, int nt, int nj, int ns, const PairStage
   return FOCK_OK;
 }
 
+PairsLayout pairs_layout(int nr, int nt, int nj, int ns, size_t fb, size_t budget, bool sums32, bool two, bool tri) {
+  PairsLayout l;
+  pairs_block_shape(nt, nj, ns, nr, fb, budget, sums32 && !two, tri, &l.rows, &l.njmax);
+  const int group = pair_group(l.rows, nr);
+  l.groups = (l.rows + group - 1) / group;
+  auto piece = [&](size_t bytes) {
+    const size_t at = l.end;
+    l.end = (at + bytes + 255) & ~size_t(255);
+    l.largest = std::max(l.largest, bytes);
+    return at;
+  };
+  piece((size_t)l.rows * l.njmax * fb);
+  l.run = piece((size_t)l.rows * nr * (sums32 ? sizeof(c64) : sizeof(c128)));
+  if (two) l.mir = piece((size_t)l.groups * nj * nr * sizeof(c128));
+  if (two && sums32) l.mcomp = piece((size_t)l.groups * nj * nr * sizeof(c64));
+  return l;
+}
+
 bool Plan::pairs_sized(int nr, int nt, int nj, int ns, size_t fb, bool sums32, bool two, bool tri) const {
-  int rows = 0;
-  long njmax = 0;
-  pairs_block_shape(nt, nj, ns, nr, fb, workspace_cap ? std::min(workspace_cap, pair_batch) : pair_batch,
-                    sums32 && !two, tri, &rows, &njmax);
-  const size_t group = pair_group(rows, nr), groups = (rows + group - 1) / group;
-  return pbatch.bytes >= (size_t)rows * njmax * fb &&
-         prun.bytes >= (size_t)rows * nr * (sums32 ? sizeof(c64) : sizeof(c128)) &&
-         (!two || (pmir.bytes >= groups * nj * nr * sizeof(c128) &&
-                   (!sums32 || pmcomp.bytes >= groups * nj * nr * sizeof(c64))));
+  const size_t budget = workspace_cap ? std::min(workspace_cap, pair_batch) : pair_batch;
+  return pscratch.bytes >= pairs_layout(nr, nt, nj, ns, fb, budget, sums32, two, tri).end;
 }
 
 template <typename TW, typename TM>
@@ -181,27 +192,21 @@ fock_status Plan::run_pairs(int nr, int np, int nt, int nj, int ns, const PairSt
   if (prec == FOCK_FP64_FUSED) PlanCall::order();
   size_t budget = workspace_cap ? std::min(workspace_cap, batch) : batch;
   fock_status s;
-  int rows = 0;
-  long njmax = 0;
+  PairsLayout l;
   for (;;) {
-    pairs_block_shape(nt, nj, ns, nr, fb, budget, F32 && !two, mr.tri, &rows, &njmax);
-    s = pbatch.ensure((size_t)rows * njmax * fb, workspace_cap, "pair batch");
+    l = pairs_layout(nr, nt, nj, ns, fb, budget, F32, two, mr.tri);
+    if (workspace_cap && l.largest > workspace_cap)
+      return fail(FOCK_ERR_NOMEM, "pair scratch: %zu bytes exceed the plan workspace cap of %zu bytes", l.largest,
+                  workspace_cap);
+    s = pscratch.ensure(l.end, 0, "pair scratch");
     if (s == FOCK_OK) break;
     if (budget <= (size_t(64) << 20)) return s;
     budget /= 2;
   }
   g_last_error.clear();  // a smaller batch after a failed allocation is no failure
-  if ((s = prun.ensure((size_t)rows * nr * (F32 ? sizeof(c64) : sizeof(c128)), workspace_cap, "pair sums")) != FOCK_OK)
-    return s;
-  const int group = pair_group(rows, nr), groups = (rows + group - 1) / group;
-  if (two) {
-    if ((s = pmir.ensure((size_t)groups * nj * nr * sizeof(c128), workspace_cap, "mirror sums")) != FOCK_OK) return s;
-    if (F32 && (s = pmcomp.ensure((size_t)groups * nj * nr * sizeof(c64), workspace_cap, "mirror compensation")) !=
-                   FOCK_OK)
-      return s;
-  }
-  return pairs_blocks<TW, TM>(nr, np, nt, nj, ns, stage, M, mr, out, scale, accumulate, rows, njmax, (cx<TW>*)pbatch.ptr,
-                              prun.ptr, (c128*)pmir.ptr, (c64*)pmcomp.ptr, st);
+  char* base = (char*)pscratch.ptr;
+  return pairs_blocks<TW, TM>(nr, np, nt, nj, ns, stage, M, mr, out, scale, accumulate, l.rows, l.njmax, (cx<TW>*)base,
+                              base + l.run, (c128*)(base + l.mir), (c64*)(base + l.mcomp), st);
 }
 
 template <typename T>

@@ -125,6 +125,18 @@ struct Mirror {
 // (whole_partials: blocks of at least one FP32 partial sum of at most 16 bands).
 void pairs_block_shape(int nt, int nj, int ns, int nr, size_t fb, size_t budget, bool whole_partials, bool tri,
                        int* rows, long* njmax);
+// The scratch of such a sum, one allocation: the batch of W fields, then (256-byte aligned, at these
+// offsets) the sums kept between the blocks of a row and, when two-sided, the mirror sums of each
+// group of a row's targets and in FP32 their compensation. One instead of four: an allocation takes
+// longer than a small sum (first application on a new plan, 16^3 / 8 k / 4 bands in FP64: 531 us with
+// one per piece, 181 us, of which the sum is 42).
+struct PairsLayout {
+  int rows = 0, groups = 0;
+  long njmax = 0;
+  size_t run = 0, mir = 0, mcomp = 0, end = 0;
+  size_t largest = 0;  // bytes of its largest piece
+};
+PairsLayout pairs_layout(int nr, int nt, int nj, int ns, size_t fb, size_t budget, bool sums32, bool two, bool tri);
 // Stage 1 of a two-stage pair sum: W of a block's pairs into the batch.
 template <typename TW>
 using PairStage = std::function<hipError_t(const PairBlock&, cx<TW>*)>;
@@ -181,9 +193,7 @@ struct Plan {
   int sym_key[4] = {-1, -1, -1, -1};
   int split_stagger_shift = 1;              // the bands' order of the symmetric form (FOCKMI_SPLIT_STAGGER_SHIFT)
   int split_sym = 1;                        // 0: the split form runs every pair (FOCKMI_SPLIT_SYM=0)
-  // two-stage pair form (pairs_api.hip): the batch of W fields, the sums kept between the
-  // blocks of a row, the mirror sums and their compensation
-  DevBuf pbatch, prun, pmir, pmcomp;
+  DevBuf pscratch;                          // scratch of the two-stage pair form (PairsLayout)
   DevBuf gramb;                             // Gram matrices and their factors (fock_orthonormalize)
   size_t pair_batch = size_t(8) << 30;      // bytes of one batch
   int split_form = 0;                       // 1: a split-form variable is set, 32^3 runs the split form

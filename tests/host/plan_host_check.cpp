@@ -235,7 +235,29 @@ void captures_without_plan_memory() {
   }
 }
 
+// The first sum on a new plan allocates once for the pair form's scratch, in every precision and direction, and
+// the same sum again allocates nothing.
+void first_sum_allocates_once() {
+  struct Form {
+    fock_prec prec;
+    CellSpec cell;
+    size_t shadows;  // complex64 copies, each its own buffer
+  };
+  for (const Form& f : {Form{FOCK_FP64, cube(16, 8, 4), 0}, Form{FOCK_FP64_FUSED, cube(16, 8, 4), 0},
+                        Form{FOCK_FP64, cube(32, 8, 4), 0}, Form{FOCK_FP64, CellSpec{{16, 20, 24}, 12, 6}, 0},
+                        Form{FOCK_FP32_COMP, cube(16, 8, 4), 1}}) {
+    TestPlan p(f.prec, {f.cell});
+    void *u = p.fields(), *out = p.fields();
+    const size_t before = fake::st().mallocs;
+    OK(fock_apply(p.h, 0, u, u, f.cell.nb, out, fake::stream(0)));
+    CHECK(fake::st().mallocs == before + 1 + f.shadows);
+    OK(fock_apply(p.h, 0, u, u, f.cell.nb, out, fake::stream(0)));
+    CHECK(fake::st().mallocs == before + 1 + f.shadows);
+  }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"first_sum_allocates_once", first_sum_allocates_once},
     {"streams_in_order", streams_in_order},
     {"threads_one_at_a_time", threads_one_at_a_time},
     {"captures_without_plan_memory", captures_without_plan_memory},
