@@ -131,6 +131,21 @@ fock_status Plan::check_ready(int cell) const {
 }
 
 // ------------------------------------------------------------------ plumbing
+namespace {
+// the two events of a tuning measurement
+struct TuneEvents {
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  hipError_t create() {
+    hipError_t e = hipEventCreate(&e0);
+    return e == hipSuccess ? hipEventCreate(&e1) : e;
+  }
+  ~TuneEvents() {
+    if (e0) (void)hipEventDestroy(e0);
+    if (e1) (void)hipEventDestroy(e1);
+  }
+};
+}  // namespace
+
 fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, const c128* P, const c128* M, int ns,
                             c128* out, double scale, bool accumulate, hipStream_t st) {
   const int nr = c.nr, nt = ps.ntk * nx, nj = ps.nsk * ns;
@@ -142,7 +157,7 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
   // k-ranges give the full application's bits.
   Mirror<double> mr;
   if (!c.f32plain && !c.ds && X == P && P == M && nx == ns && ps.ntk == c.nk && ps.nsk == c.nk &&
-      ps.qidx == (const int*)c.qidx.ptr && nt > 3 * kPairTile && pairs_tri_fits(nt, nr, nr * sizeof(c128))) {
+      ps.qidx == (const int*)c.qidx.ptr && nt > 3 * kPairTile && pairs_tri_fits(nt, ns, nr, false)) {
     mr.F = X;
     mr.dst = out;
     mr.scale = scale;
@@ -177,27 +192,24 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
   if (tune.get(key, &te)) return run((size_t)te.fields["batch_mb"] << 20);
   if (!tuning || accumulate) return run(pair_batch);
   // measure the pair-batch size (each candidate writes the same result to rounding)
-  hipEvent_t e0, e1;
-  hipError_t e;
-  if ((e = hipEventCreate(&e0)) != hipSuccess) return hip_fail(e, "tuning event");
-  if ((e = hipEventCreate(&e1)) != hipSuccess) return hip_fail(e, "tuning event");
+  TuneEvents ev;
+  hipError_t e = ev.create();
+  if (e != hipSuccess) return hip_fail(e, "tuning event");
   double best = 1e300;
   int bmb = 16384;
   for (int mb : {1024, 4096, 16384}) {
-    (void)hipEventRecord(e0, st);
+    (void)hipEventRecord(ev.e0, st);
     fock_status s = run((size_t)mb << 20);
     if (s != FOCK_OK) return s;
-    (void)hipEventRecord(e1, st);
-    if ((e = hipEventSynchronize(e1)) != hipSuccess) return hip_fail(e, "tuning sync");
+    (void)hipEventRecord(ev.e1, st);
+    if ((e = hipEventSynchronize(ev.e1)) != hipSuccess) return hip_fail(e, "tuning sync");
     float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, e0, e1);
+    (void)hipEventElapsedTime(&ms, ev.e0, ev.e1);
     if (ms < best) {
       best = ms;
       bmb = mb;
     }
   }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
   te.fields["batch_mb"] = bmb;
   te.fields["ms"] = best;
   tune.put(key, te);
@@ -260,7 +272,7 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   // the two-stage pair form, with the pair symmetry when u is targets and sources over the whole mesh
   const bool pairs_tri = split_sym && !c.ds && ps.ntk == c.nk && ps.nsk == c.nk &&
                          ps.qidx == (const int*)c.qidx.ptr && X == P && P == M && nx == ns &&
-                         pairs_tri_fits(nitems, nr, nr * sizeof(c64));
+                         pairs_tri_fits(nitems, ns, nr, true);
   PairRule rule = pair_rule(c, ps, nx, ns, X == P && P == M, true);
   if (n == 32) rule.tri = pairs_tri;
   auto usable = [&](int v) {
@@ -439,9 +451,8 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   } else if (tuning && !accumulate) {
     // measure every candidate on this call's data (each writes the same result up
     // to the grouping of its FP64 additions); the XCD map matters only for the grid form
-    hipEvent_t e0, e1;
-    if ((e = hipEventCreate(&e0)) != hipSuccess) return hip_fail(e, "tuning event");
-    if ((e = hipEventCreate(&e1)) != hipSuccess) return hip_fail(e, "tuning event");
+    TuneEvents ev;
+    if ((e = ev.create()) != hipSuccess) return hip_fail(e, "tuning event");
     double best = 1e300;
     int bv = 0, bx = 1;
     for (int v = 0; v < 4; ++v) {
@@ -449,13 +460,19 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
       if ((s = prepare(v)) != FOCK_OK) return s;
       for (int x = 0; x < (v == 0 || (n != 32 && v < 3) ? 2 : 1); ++x) {
         a.xcd_map = v == 0 || (n != 32 && v < 3) ? x : 1;
-        (void)hipEventRecord(e0, st);
+        (void)hipEventRecord(ev.e0, st);
         if ((e = launch(v)) != hipSuccess) return hip_fail(e, "fused pair kernel");
+        if (pairs_status == FOCK_ERR_NOMEM) {
+          // no room for a batch (nothing has been launched): not a candidate
+          g_last_error.clear();
+          pairs_status = FOCK_OK;
+          break;
+        }
         if (pairs_status != FOCK_OK) return pairs_status;
-        (void)hipEventRecord(e1, st);
-        if ((e = hipEventSynchronize(e1)) != hipSuccess) return hip_fail(e, "tuning sync");
+        (void)hipEventRecord(ev.e1, st);
+        if ((e = hipEventSynchronize(ev.e1)) != hipSuccess) return hip_fail(e, "tuning sync");
         float ms = 0.f;
-        (void)hipEventElapsedTime(&ms, e0, e1);
+        (void)hipEventElapsedTime(&ms, ev.e0, ev.e1);
         if (ms < best) {
           best = ms;
           bv = v;
@@ -463,8 +480,6 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
         }
       }
     }
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     te.fields["variant"] = bv;
     te.fields["xcd_map"] = bx;
     te.fields["ms"] = best;

@@ -39,9 +39,18 @@ void pairs_block_shape(int nt, int nj, int ns, int nr, size_t fb, size_t budget,
   *njmax = tri ? std::max<long>(m, *rows) : m;
 }
 
-bool Plan::pairs_tri_fits(int nt, int nr, size_t field_bytes) const {
-  const size_t b = std::min<size_t>(nt, 64);
-  return !workspace_cap || (b * b * field_bytes <= workspace_cap && (size_t)nt * nr * sizeof(c128) <= workspace_cap);
+bool Plan::pairs_fit(int nr, int nt, int nj, int ns, size_t fb, size_t batch, bool sums32, bool two, bool tri,
+                     PairsLayout* l) const {
+  for (size_t budget = workspace_cap ? std::min(workspace_cap, batch) : batch;; budget /= 2) {
+    *l = pairs_layout(nr, nt, nj, ns, fb, budget, sums32, two, tri);
+    if (!workspace_cap || l->largest <= workspace_cap) return true;
+    if (budget < fb) return false;
+  }
+}
+
+bool Plan::pairs_tri_fits(int nt, int nb, int nr, bool f32) const {
+  PairsLayout l;
+  return pairs_fit(nr, nt, nt, nb, (size_t)nr * (f32 ? sizeof(c64) : sizeof(c128)), pair_batch, f32, true, true, &l);
 }
 
 // Measured costs of the forms on a 256-CU device, cubic grids (64 k-points of 16 bands, phi apart
@@ -77,7 +86,7 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
   // below 4 tiles the triangle is nearly the whole square, and the mirror sums cost a launch
   const bool tri_ok = same && ps.ntk == c.nk && ps.nsk == c.nk && ps.qidx == (const int*)c.qidx.ptr &&
                       nt > 3 * kPairTile &&
-                      pairs_tri_fits((int)nt, c.nr, (size_t)c.nr * (f32 ? sizeof(c64) : sizeof(c128)));
+                      pairs_tri_fits((int)nt, ns, c.nr, f32);
   if (f32) {
     const size_t need = noalloc_bytes(c, ps, nx, ns, same);
     r.shared = need <= kNoAllocBytes;
@@ -178,8 +187,8 @@ PairsLayout pairs_layout(int nr, int nt, int nj, int ns, size_t fb, size_t budge
 }
 
 bool Plan::pairs_sized(int nr, int nt, int nj, int ns, size_t fb, bool sums32, bool two, bool tri) const {
-  const size_t budget = workspace_cap ? std::min(workspace_cap, pair_batch) : pair_batch;
-  return pscratch.bytes >= pairs_layout(nr, nt, nj, ns, fb, budget, sums32, two, tri).end;
+  PairsLayout l;
+  return pairs_fit(nr, nt, nj, ns, fb, pair_batch, sums32, two, tri, &l) && pscratch.bytes >= l.end;
 }
 
 template <typename TW, typename TM>
@@ -190,18 +199,15 @@ fock_status Plan::run_pairs(int nr, int np, int nt, int nj, int ns, const PairSt
   const bool two = mr.dst != nullptr;
   // sums of this precision at 16^3 and 20^3 may run on several streams at once
   if (prec == FOCK_FP64_FUSED) PlanCall::order();
-  size_t budget = workspace_cap ? std::min(workspace_cap, batch) : batch;
   fock_status s;
   PairsLayout l;
-  for (;;) {
-    l = pairs_layout(nr, nt, nj, ns, fb, budget, F32, two, mr.tri);
-    if (workspace_cap && l.largest > workspace_cap)
+  for (;; batch /= 2) {
+    if (!pairs_fit(nr, nt, nj, ns, fb, batch, F32, two, mr.tri, &l))
       return fail(FOCK_ERR_NOMEM, "pair scratch: %zu bytes exceed the plan workspace cap of %zu bytes", l.largest,
                   workspace_cap);
     s = pscratch.ensure(l.end, 0, "pair scratch");
     if (s == FOCK_OK) break;
-    if (budget <= (size_t(64) << 20)) return s;
-    budget /= 2;
+    if (batch <= (size_t(64) << 20)) return s;
   }
   g_last_error.clear();  // a smaller batch after a failed allocation is no failure
   char* base = (char*)pscratch.ptr;

@@ -247,8 +247,12 @@ struct Plan {
   PairRule pair_rule(const Cell& c, const PairSet& ps, int nx, int ns, bool same, bool f32) const;
   // whether the buffers of such a sum are there already (under capture nothing can be allocated)
   bool pairs_sized(int nr, int nt, int nj, int ns, size_t field_bytes, bool sums32, bool two, bool tri) const;
-  // whether the batch and mirror sums of a symmetric sum over nt fields fit the workspace cap
-  bool pairs_tri_fits(int nt, int nr, size_t field_bytes) const;
+  // the scratch of a sum with a batch of at most `batch` bytes, less where a piece would exceed the
+  // workspace cap (a smaller batch has rows of fewer groups); false: none fits
+  bool pairs_fit(int nr, int nt, int nj, int ns, size_t fb, size_t batch, bool sums32, bool two, bool tri,
+                 PairsLayout* l) const;
+  // whether that of a symmetric sum over nt fields of nb per k-point fits
+  bool pairs_tri_fits(int nt, int nb, int nr, bool f32) const;
   // the orbitals of the source k-points, contiguous: `arr` itself without
   // down-sampling, else a copy of its S blocks ([nsrc][nper][nr]) in buf
   fock_status sources(Cell& c, const c128* arr, int nper, DevBuf& buf, hipStream_t st, const c128** out);

@@ -256,7 +256,40 @@ void first_sum_allocates_once() {
   }
 }
 
+// A plan with a tuning cache and no room for the pair form's scratch measures the other forms: 5,000 targets of
+// 32^3 under a cap of 4 GiB (mirror sums of 5,000 MiB with rows of 128 targets, 2,500 with rows of 64, which
+// then run), and a device whose memory is full but for what the forms that sum on the CU need.
+void tuned_call_without_room() {
+  const std::string path = std::string(getenv("TMPDIR") ? getenv("TMPDIR") : "/tmp") + "/fockmi_tune_check.json";
+  auto launched = [] { return fake::launches("pair_w") > 0; };
+  {
+    remove(path.c_str());
+    setenv("FOCKMI_WORKSPACE_CAP", std::to_string(size_t(4) << 30).c_str(), 1);
+    TestPlan p(FOCK_FP32_COMP, {cube(32, 250, 20)}, path.c_str());
+    unsetenv("FOCKMI_WORKSPACE_CAP");
+    const size_t events = fake::st().events.size();
+    void *u = p.fields(), *out = p.fields();
+    OK(fock_apply(p.h, 0, u, u, 20, out, fake::stream(0)));
+    CHECK(launched() && fake::launches("mirror_add") > 0);
+    CHECK(fake::st().events.size() == events);
+  }
+  fake::st().ops.clear();
+  {
+    remove(path.c_str());
+    TestPlan p(FOCK_FP32_COMP, {cube(32, 8, 16)}, path.c_str());
+    const size_t events = fake::st().events.size();
+    void *u = p.fields(), *phi = p.fields(0, 4), *out = p.fields(0, 4);
+    fake::st().limit = fake::st().used() + (size_t(240) << 20);  // what the three forms that sum on the CU take: 217
+    OK(fock_apply(p.h, 0, u, phi, 4, out, fake::stream(0)));
+    fake::st().limit = ~size_t(0);
+    CHECK(!launched() && fake::launches("split32") + fake::launches("fused") > 0);
+    CHECK(fake::st().events.size() == events);
+  }
+  remove(path.c_str());
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"tuned_call_without_room", tuned_call_without_room},
     {"first_sum_allocates_once", first_sum_allocates_once},
     {"streams_in_order", streams_in_order},
     {"threads_one_at_a_time", threads_one_at_a_time},
