@@ -111,17 +111,17 @@ fock_status fock_plan_destroy(fockmi_plan plan);
  * nphi >= 1: an empty target set is FOCK_ERR_ARG, as are a NULL or misaligned
  * pointer, a cell index out of range and an output that overlaps an input;
  * nothing is launched then.
- * With phi == u_occ and no down-sampling, the FP32 form at 32^3 and the fused forms at
- * 16^3 to 24^3 (where it is the faster way) transform each pair of fields once and add its
- * conjugate term to the other row: the plan
+ * With phi == u_occ and no down-sampling, FP64 on grids that are not cubic and at 32^3, FP32 at 32^3
+ * and every form at 16^3 to 24^3 (there where it is the faster way) transform each pair of fields once
+ * and add its conjugate term to the other row: the plan
  * then holds a batch of pair fields (8 GiB, less when the device or the plan's workspace
- * cap cannot hold it) and mirror sums of 24 bytes per grid point and 64 targets of a row
- * of blocks. Few targets apart from u_occ run through the same batch, without the
- * conjugate terms. The result is bitwise repeatable and agrees with the form that runs every
- * pair to rounding; that form runs instead when 64 fields' pairs exceed the plan's
- * workspace cap, or with FOCKMI_SPLIT_SYM=0 at plan creation. A plan created with
- * FOCKMI_SPLIT_WAIT_TICKS set runs 32^3 cells in the split form (each target on two CUs),
- * whose wait limit that variable is.
+ * cap cannot hold it) and mirror sums of 16 bytes (24 in FP32) per grid point of every field and per 64
+ * targets of a row of blocks (per 16 where a row has less than 2,048 waves' work). Few targets apart
+ * from u_occ run through the same batch, without the conjugate terms. The result is bitwise repeatable
+ * and agrees with the form that runs every pair to rounding; that form runs instead when 64 fields'
+ * pairs exceed the plan's workspace cap, and in a plan created with FOCKMI_SPLIT_SYM=0 in the
+ * environment. A plan created with FOCKMI_SPLIT_WAIT_TICKS set runs 32^3 cells in the split form (each
+ * target on two CUs), whose wait limit that variable is.
  * Stream-ordered; returns without synchronising. */
 fock_status fock_apply(fockmi_plan plan, int cell, const void* u_occ, const void* phi, int nphi,
                        void* vphi, void* stream);

@@ -156,7 +156,7 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
   // The pair symmetry, where u is targets and sources over the whole mesh; not in FP32, whose
   // k-ranges give the full application's bits.
   Mirror<double> mr;
-  if (!c.f32plain && !c.ds && X == P && P == M && nx == ns && ps.ntk == c.nk && ps.nsk == c.nk &&
+  if (split_sym && !c.f32plain && !c.ds && X == P && P == M && nx == ns && ps.ntk == c.nk && ps.nsk == c.nk &&
       ps.qidx == (const int*)c.qidx.ptr && nt > 3 * kPairTile && pairs_tri_fits(nt, ns, nr, false)) {
     mr.F = X;
     mr.dst = out;

@@ -84,7 +84,7 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
   const double fused = 1e3 * ((double)(per_cu / fc->per_cu) * fc->wg[fc->per_cu - 1] + (rest ? fc->wg[rest - 1] : 0.0));
   r.fused_ns = fused;
   // below 4 tiles the triangle is nearly the whole square, and the mirror sums cost a launch
-  const bool tri_ok = same && ps.ntk == c.nk && ps.nsk == c.nk && ps.qidx == (const int*)c.qidx.ptr &&
+  const bool tri_ok = split_sym && same && ps.ntk == c.nk && ps.nsk == c.nk && ps.qidx == (const int*)c.qidx.ptr &&
                       nt > 3 * kPairTile &&
                       pairs_tri_fits((int)nt, ns, c.nr, f32);
   if (f32) {

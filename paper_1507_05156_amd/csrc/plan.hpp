@@ -192,7 +192,7 @@ struct Plan {
   DevBuf mpart, msum, mcomp, mdone, sym_rank, sym_cnt;
   int sym_key[4] = {-1, -1, -1, -1};
   int split_stagger_shift = 1;              // the bands' order of the symmetric form (FOCKMI_SPLIT_STAGGER_SHIFT)
-  int split_sym = 1;                        // 0: the split form runs every pair (FOCKMI_SPLIT_SYM=0)
+  int split_sym = 1;                        // 0: every form runs every pair (FOCKMI_SPLIT_SYM=0)
   DevBuf pscratch;                          // scratch of the two-stage pair form (PairsLayout)
   DevBuf gramb;                             // Gram matrices and their factors (fock_orthonormalize)
   size_t pair_batch = size_t(8) << 30;      // bytes of one batch

@@ -288,7 +288,30 @@ void tuned_call_without_room() {
   remove(path.c_str());
 }
 
+// A plan created with FOCKMI_SPLIT_SYM=0 runs every pair, in every precision and on every grid; without it
+// the same calls use the pair symmetry.
+void symmetry_switch() {
+  struct Form {
+    fock_prec prec;
+    CellSpec cell;
+  };
+  for (const Form& f : {Form{FOCK_FP32_COMP, cube(24, 64, 16)}, Form{FOCK_FP32_COMP, cube(32, 8, 16)},
+                        Form{FOCK_FP64, cube(16, 8, 4)}, Form{FOCK_FP64, cube(32, 8, 16)},
+                        Form{FOCK_FP64, CellSpec{{16, 20, 24}, 12, 6}}, Form{FOCK_FP64_FUSED, cube(20, 27, 12)},
+                        Form{FOCK_FP64_FUSED, cube(24, 64, 16)}})
+    for (int sym : {0, 1}) {
+      if (!sym) setenv("FOCKMI_SPLIT_SYM", "0", 1);
+      TestPlan p(f.prec, {f.cell});
+      unsetenv("FOCKMI_SPLIT_SYM");
+      void *u = p.fields(), *out = p.fields();
+      fake::st().ops.clear();
+      OK(fock_apply(p.h, 0, u, u, f.cell.nb, out, fake::stream(0)));
+      CHECK((fake::launches("mirror_add") > 0) == (sym == 1));
+    }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"symmetry_switch", symmetry_switch},
     {"tuned_call_without_room", tuned_call_without_room},
     {"first_sum_allocates_once", first_sum_allocates_once},
     {"streams_in_order", streams_in_order},
