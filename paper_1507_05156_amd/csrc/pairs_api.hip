@@ -88,7 +88,9 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
                       nt > 3 * kPairTile &&
                       pairs_tri_fits((int)nt, ns, c.nr, f32);
   if (f32) {
-    const size_t need = noalloc_bytes(c, ps, nx, ns, same);
+    // what the allocation-free call needs where the targets could be u itself, also when they are not:
+    // a k-range of u, or a copy of it, goes the way of the application to u and gives its bits
+    const size_t need = noalloc_bytes(c, ps, nx, ns, nx == ns && !c.ds);
     r.shared = need <= kNoAllocBytes;
     if (r.shared) {
       // fock_apply_noalloc serves this sum with the same bits: one-sided in both (its sums do

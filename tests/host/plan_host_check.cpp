@@ -310,7 +310,31 @@ void symmetry_switch() {
     }
 }
 
+// FP32 at 16^3 to 24^3: where the application to u runs every pair, a k-range of u and a copy of u as targets
+// run the same kernel (their bits are the application's). Every count of fields up to 1,100.
+void same_kernel_for_a_k_range() {
+  for (int n : {16, 20, 24})
+    for (int nk : {1, 4, 10, 20})
+      for (int nb = 1; nb <= 1100 / nk; nb += nk == 1 ? 7 : 1) {
+        TestPlan p(FOCK_FP32_COMP, {cube(n, nk, nb)});
+        void *u = p.fields(), *v = p.fields(), *out = p.fields();
+        auto kernel = [&](const std::function<void()>& call) {
+          fake::st().ops.clear();
+          call();
+          return fake::launches("mirror_add") ? 2 : (fake::launches("pair_w") ? 1 : 0);
+        };
+        const int full = kernel([&] { OK(fock_apply(p.h, 0, u, u, nb, out, fake::stream(0))); });
+        const int copy = kernel([&] { OK(fock_apply(p.h, 0, u, v, nb, out, fake::stream(0))); });
+        const int part = nk == 1 ? copy : kernel([&] { OK(fock_apply_krange(p.h, 0, u, 1, nk - 1, v, nb, out, fake::stream(0))); });
+        if (copy != part || (full != 2 && full != copy)) {
+          std::printf("%d^3, %d x %d fields: u %d, copy %d, k-range %d\n", n, nk, nb, full, copy, part);
+          ++faults;
+        }
+      }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"same_kernel_for_a_k_range", same_kernel_for_a_k_range},
     {"symmetry_switch", symmetry_switch},
     {"tuned_call_without_room", tuned_call_without_room},
     {"first_sum_allocates_once", first_sum_allocates_once},
