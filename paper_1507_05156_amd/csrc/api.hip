@@ -150,14 +150,17 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
                             c128* out, double scale, bool accumulate, hipStream_t st) {
   const int nr = c.nr, nt = ps.ntk * nx, nj = ps.nsk * ns;
   const bool cube = c.Kp.ptr != nullptr;  // the field fits on a CU
-  // many targets: the fused FP64 kernel, which keeps each target's sum on its CU
-  if (cube && !pair_rule(c, ps, nx, ns, X == P && P == M, false).pairs)
+  // many targets: the fused FP64 kernel, which keeps each target's sum on its CU; under capture also where
+  // there is no scratch for the pair form
+  if (cube && !(pair_rule(c, ps, nx, ns, X == P && P == M, false).pairs &&
+                pairs_ready(nr, nt, nj, ns, nr * sizeof(c128), false, false, false)))
     return run_fused64(c, ps, X, nx, P, M, ns, out, scale, accumulate, st);
   // The pair symmetry, where u is targets and sources over the whole mesh; not in FP32, whose
   // k-ranges give the full application's bits.
   Mirror<double> mr;
   if (split_sym && !c.f32plain && !c.ds && X == P && P == M && nx == ns && ps.ntk == c.nk && ps.nsk == c.nk &&
-      ps.qidx == (const int*)c.qidx.ptr && nt > 3 * kPairTile && pairs_tri_fits(nt, ns, nr, false)) {
+      ps.qidx == (const int*)c.qidx.ptr && nt > 3 * kPairTile && pairs_tri_fits(nt, ns, nr, false) &&
+      pairs_ready(nr, nt, nj, ns, nr * sizeof(c128), false, true, true)) {
     mr.F = X;
     mr.dst = out;
     mr.scale = scale;
@@ -488,9 +491,9 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
     variant = bv;
     a.xcd_map = bx;
   }
-  // a first call under capture, where no batch can be allocated: a form that sums on the CU
-  if (variant == 3 && g_capturing &&
-      !pairs_sized(nr, nitems, ps.nsk * ns, ns, nr * sizeof(c64), true, rule.tri, rule.tri))
+  // under capture without scratch for the pair form: a form that sums on the CU
+  if (variant == 3 &&
+      !pairs_ready(nr, nitems, ps.nsk * ns, ns, nr * sizeof(c64), true, rule.tri, rule.tri))
     variant = n == 32 && has_ls ? 1 : 0;
   if ((s = prepare(variant)) != FOCK_OK) return s;
   if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
@@ -538,7 +541,7 @@ fock_status Plan::run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx,
   // if its buffers are there already.
   if (rule.pairs && g_capturing &&
       ((c.f64f && fused64_acc_scratch_elems(c.geom.n1, 1) == 0) ||
-       !pairs_sized(c.nr, nitems, ps.nsk * ns, ns, c.nr * sizeof(c128), false, rule.tri, rule.tri)))
+       !pairs_ready(c.nr, nitems, ps.nsk * ns, ns, c.nr * sizeof(c128), false, rule.tri, rule.tri)))
     rule.pairs = false;
   if (rule.pairs) {
     if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
@@ -608,7 +611,7 @@ fock_status Plan::two_sided(Cell& c, const c128* X, int nx, const c128* us, doub
   }
   // under capture as in run_fused64
   if (g_capturing && ((c.f64f && fused64_acc_scratch_elems(n, 1) == 0) ||
-                      !pairs_sized(nr, nt, nj, c.nb, (size_t)nr * (f32 ? sizeof(c64) : sizeof(c128)), f32 && !planes,
+                      !pairs_ready(nr, nt, nj, c.nb, (size_t)nr * (f32 ? sizeof(c64) : sizeof(c128)), f32 && !planes,
                                    true, false)))
     return FOCK_OK;
   fock_status s;

@@ -40,10 +40,10 @@ void pairs_block_shape(int nt, int nj, int ns, int nr, size_t fb, size_t budget,
 }
 
 bool Plan::pairs_fit(int nr, int nt, int nj, int ns, size_t fb, size_t batch, bool sums32, bool two, bool tri,
-                     PairsLayout* l) const {
+                     PairsLayout* l, size_t room) const {
   for (size_t budget = workspace_cap ? std::min(workspace_cap, batch) : batch;; budget /= 2) {
     *l = pairs_layout(nr, nt, nj, ns, fb, budget, sums32, two, tri);
-    if (!workspace_cap || l->largest <= workspace_cap) return true;
+    if ((!workspace_cap || l->largest <= workspace_cap) && l->end <= room) return true;
     if (budget < fb) return false;
   }
 }
@@ -188,9 +188,9 @@ PairsLayout pairs_layout(int nr, int nt, int nj, int ns, size_t fb, size_t budge
   return l;
 }
 
-bool Plan::pairs_sized(int nr, int nt, int nj, int ns, size_t fb, bool sums32, bool two, bool tri) const {
+bool Plan::pairs_ready(int nr, int nt, int nj, int ns, size_t fb, bool sums32, bool two, bool tri) const {
   PairsLayout l;
-  return pairs_fit(nr, nt, nj, ns, fb, pair_batch, sums32, two, tri, &l) && pscratch.bytes >= l.end;
+  return !g_capturing || pairs_fit(nr, nt, nj, ns, fb, pair_batch, sums32, two, tri, &l, pscratch.bytes);
 }
 
 template <typename TW, typename TM>
@@ -203,7 +203,10 @@ fock_status Plan::run_pairs(int nr, int np, int nt, int nj, int ns, const PairSt
   if (prec == FOCK_FP64_FUSED) PlanCall::order();
   fock_status s;
   PairsLayout l;
-  for (;; batch /= 2) {
+  // under capture in what is there, if that is possible
+  const bool there = g_capturing && pairs_fit(nr, nt, nj, ns, fb, batch, F32, two, mr.tri, &l, pscratch.bytes);
+  if (there) pscratch.hold();
+  for (; !there; batch /= 2) {
     if (!pairs_fit(nr, nt, nj, ns, fb, batch, F32, two, mr.tri, &l))
       return fail(FOCK_ERR_NOMEM, "pair scratch: %zu bytes exceed the plan workspace cap of %zu bytes", l.largest,
                   workspace_cap);

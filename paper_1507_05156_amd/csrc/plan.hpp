@@ -245,12 +245,13 @@ struct Plan {
     double fused_ns = 0.0, pairs_ns = 0.0;  // modelled cost of the one-sided sum per source (0: no fused form)
   };
   PairRule pair_rule(const Cell& c, const PairSet& ps, int nx, int ns, bool same, bool f32) const;
-  // whether the buffers of such a sum are there already (under capture nothing can be allocated)
-  bool pairs_sized(int nr, int nt, int nj, int ns, size_t field_bytes, bool sums32, bool two, bool tri) const;
+  // whether the scratch of such a sum can be had: under capture, where nothing can be allocated, what is
+  // there has to hold it, if in smaller blocks
+  bool pairs_ready(int nr, int nt, int nj, int ns, size_t field_bytes, bool sums32, bool two, bool tri) const;
   // the scratch of a sum with a batch of at most `batch` bytes, less where a piece would exceed the
-  // workspace cap (a smaller batch has rows of fewer groups); false: none fits
+  // workspace cap (a smaller batch has rows of fewer groups) or the whole `room`; false: none fits
   bool pairs_fit(int nr, int nt, int nj, int ns, size_t fb, size_t batch, bool sums32, bool two, bool tri,
-                 PairsLayout* l) const;
+                 PairsLayout* l, size_t room = ~size_t(0)) const;
   // whether that of a symmetric sum over nt fields of nb per k-point fits
   bool pairs_tri_fits(int nt, int nb, int nr, bool f32) const;
   // the orbitals of the source k-points, contiguous: `arr` itself without

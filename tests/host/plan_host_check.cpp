@@ -333,7 +333,29 @@ void same_kernel_for_a_k_range() {
       }
 }
 
+// A captured call whose kind of sum the plan has not run runs in the scratch that is there, or without any:
+// after a larger sum of another kind in FP64 (with separate targets on grids of every form; at 16^3 one that
+// runs the fused kernel), u as targets, few targets and the adjoint.
+void captures_use_what_is_there() {
+  for (const CellSpec& c : {cube(32, 8, 8), CellSpec{{16, 20, 24}, 12, 6}, cube(16, 64, 16), cube(24, 8, 16)})
+    for (int form : {0, 1}) {
+      TestPlan p(form ? FOCK_FP64_FUSED : FOCK_FP64, {c});
+      const hipStream_t q = fake::stream(0);
+      void *u = p.fields(), *out = p.fields(), *phi = p.fields(0, 40), *big = p.fields(0, 40);
+      void *g = p.fields(0, 2), *gp = p.fields(0, 2);
+      OK(fock_apply(p.h, 0, u, phi, 40, big, q));
+      fake::st().bad_mallocs = 0;
+      fake::st().capturing.insert(q);
+      OK(fock_apply(p.h, 0, u, u, c.nb, out, q));
+      OK(fock_apply(p.h, 0, u, phi, 2, big, q));
+      OK(fock_vjp(p.h, 0, u, phi, 2, g, out, gp, q));
+      fake::st().capturing.clear();
+      CHECK(fake::st().bad_mallocs == 0);
+    }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"captures_use_what_is_there", captures_use_what_is_there},
     {"same_kernel_for_a_k_range", same_kernel_for_a_k_range},
     {"symmetry_switch", symmetry_switch},
     {"tuned_call_without_room", tuned_call_without_room},
