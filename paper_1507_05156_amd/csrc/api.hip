@@ -153,8 +153,11 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
   // many targets: the fused FP64 kernel, which keeps each target's sum on its CU; under capture also where
   // there is no scratch for the pair form
   if (cube && !(pair_rule(c, ps, nx, ns, X == P && P == M, false).pairs &&
-                pairs_ready(nr, nt, nj, ns, nr * sizeof(c128), false, false, false)))
-    return run_fused64(c, ps, X, nx, P, M, ns, out, scale, accumulate, st);
+                pairs_ready(nr, nt, nj, ns, nr * sizeof(c128), false, false, false))) {
+    const fock_status s = run_fused64(c, ps, X, nx, P, M, ns, out, scale, accumulate, st);
+    if (s != FOCK_ERR_NOMEM) return s;
+    g_last_error.clear();  // no room for its sums (nothing has been launched): the pair form takes them in blocks
+  }
   // The pair symmetry, where u is targets and sources over the whole mesh; not in FP32, whose
   // k-ranges give the full application's bits.
   Mirror<double> mr;
@@ -185,6 +188,12 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
       // no room for the mirror sums: every pair (nothing has been launched)
       g_last_error.clear();
       s = sums(Mirror<double>{});
+    }
+    if (s == FOCK_ERR_NOMEM && cube) {
+      // no room for a batch (nothing has been launched): the fused kernel
+      prof_drop();
+      g_last_error.clear();
+      return run_fused64(c, ps, X, nx, P, M, ns, out, scale, accumulate, st);
     }
     if (s != FOCK_OK) return s;
     if ((e = prof_end(st)) != hipSuccess) return hip_fail(e, "profile event");

@@ -354,8 +354,20 @@ void captures_use_what_is_there() {
     }
 }
 
+// FP64 at 24^3 with a workspace cap below the fused kernel's sums (1,024 targets: 216 MiB): the sum runs in
+// blocks, as it did with a tuning file that asks for a batch of 64 MiB.
+void fused_sums_beyond_the_cap() {
+  setenv("FOCKMI_WORKSPACE_CAP", std::to_string(size_t(100) << 20).c_str(), 1);
+  TestPlan p(FOCK_FP64, {cube(24, 64, 16)});
+  unsetenv("FOCKMI_WORKSPACE_CAP");
+  void *u = p.fields(), *phi = p.fields(), *out = p.fields();
+  OK(fock_apply(p.h, 0, u, phi, 16, out, fake::stream(0)));
+  CHECK(fake::launches("pair_w") > 0 && fake::launches("fused64") == 0);
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
     {"captures_use_what_is_there", captures_use_what_is_there},
+    {"fused_sums_beyond_the_cap", fused_sums_beyond_the_cap},
     {"same_kernel_for_a_k_range", same_kernel_for_a_k_range},
     {"symmetry_switch", symmetry_switch},
     {"tuned_call_without_room", tuned_call_without_room},
