@@ -189,9 +189,9 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
       g_last_error.clear();
       s = sums(Mirror<double>{});
     }
+    if (s != FOCK_OK) prof_drop();
     if (s == FOCK_ERR_NOMEM && cube) {
       // no room for a batch (nothing has been launched): the fused kernel
-      prof_drop();
       g_last_error.clear();
       return run_fused64(c, ps, X, nx, P, M, ns, out, scale, accumulate, st);
     }
@@ -648,9 +648,9 @@ fock_status Plan::two_sided(Cell& c, const c128* X, int nx, const c128* us, doub
                  : cube_stage<double>(n, num_cus, ps, X, nx, us, c.nb, (const double*)c.Kp.ptr, st),
           us, out, scale, false, mr, pair_batch, st);
   }
+  if (s != FOCK_OK) prof_drop();
   if (s == FOCK_ERR_NOMEM) {
     // no room for the batch or the mirror sums (nothing has been launched): two separate sums
-    prof_drop();
     g_last_error.clear();
     return FOCK_OK;
   }

@@ -365,7 +365,23 @@ void fused_sums_beyond_the_cap() {
   CHECK(fake::launches("pair_w") > 0 && fake::launches("fused64") == 0);
 }
 
+// A sum that is refused for want of memory leaves the profile record readable, and is not in it.
+void refused_sum_is_not_profiled() {
+  setenv("FOCKMI_WORKSPACE_CAP", "1000", 1);
+  TestPlan p(FOCK_FP64, {CellSpec{{16, 20, 24}, 3, 2}});
+  unsetenv("FOCKMI_WORKSPACE_CAP");
+  void *u = p.fields(), *out = p.fields(), *g = p.fields(), *gp = p.fields();
+  OK(fock_profile_enable(p.h, 1));
+  CHECK(fock_apply(p.h, 0, u, u, 2, out, fake::stream(0)) == FOCK_ERR_NOMEM);
+  CHECK(fock_vjp(p.h, 0, u, u, 2, g, out, gp, fake::stream(0)) == FOCK_ERR_NOMEM);
+  double ms = -1;
+  long long n = -1;
+  OK(fock_profile_read(p.h, &ms, &n, 1));
+  CHECK(n == 0 && ms == 0.0);
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"refused_sum_is_not_profiled", refused_sum_is_not_profiled},
     {"captures_use_what_is_there", captures_use_what_is_there},
     {"fused_sums_beyond_the_cap", fused_sums_beyond_the_cap},
     {"same_kernel_for_a_k_range", same_kernel_for_a_k_range},
