@@ -298,7 +298,7 @@ fock_status fock_excited_density(fockmi_plan plan, int cell, const void* phi, co
  * over all cells or each cell's fused kernel on a stream of its own, forked
  * from the caller's stream (the default); a plan with a tuning cache measures
  * both on its first call. Other plans run their cells one after another, and so does a
- * plan without a tuning cache where the two-stage pair form is the faster way for a cell.
+ * plan without a tuning cache where that is faster, in the two-stage pair form.
  * Stream-ordered. */
 fock_status fock_apply_batched(fockmi_plan plan, const void* const* u_occ, const void* const* phi,
                                const int* nphi, void* const* vphi, void* stream);

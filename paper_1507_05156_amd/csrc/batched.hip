@@ -342,16 +342,11 @@ extern "C" fock_status fock_apply_batched(fockmi_plan plan, const void* const* u
     nmax = std::max(nmax, c.geom.n1);
     any_ds = any_ds || c.ds || c.f32plain;
   }
-  // Without a tuned choice, cells whose sums the two-stage pair form runs faster (u as many targets
-  // and sources, or few targets) go one after another through it: 16^3/27 k/8 b + 20^3/64 k/12 b +
-  // 24^3/125 k/16 b takes 153 ms so, 226 ms as a captured graph of the cells' fused kernels.
-  bool pairs = false;
-  if (p->prec == FOCK_FP32_COMP && !p->tuning && !any_ds)
-    for (int ci = 0; ci < nc; ++ci) {
-      Cell& c = p->cells[ci];
-      pairs = pairs || p->pair_rule(c, c.fwd(), nphi[ci], c.nb, phi[ci] == u_occ[ci], true).pairs;
-    }
-  if (p->prec != FOCK_FP32_COMP || nc > kMaxBatchCells || batched_threads(nmax) == 0 || any_ds || pairs) {
+  // without a tuned choice, the faster of the forked cells and the cells one after another through the
+  // pair form: 16^3/27 k/8 b + 20^3/64 k/12 b + 24^3/125 k/16 b takes 152 ms so, 226 ms forked
+  const bool fused = p->prec == FOCK_FP32_COMP && nc <= kMaxBatchCells && batched_threads(nmax) != 0 && !any_ds;
+  const bool pairs = fused && !p->tuning && p->batch_in_sequence(u_occ, phi, nphi);
+  if (!fused || pairs) {
     // FP64 plans, plans with a 32^3 cell, down-sampled cells and cells that are not
     // cubic run the cells one after another
     for (int ci = 0; ci < nc; ++ci) {

@@ -67,12 +67,16 @@ constexpr FormCost kCost64[] = {{16, 2, {4.8, 6.9}, 27.5, 17.0}, {20, 1, {10.7},
 constexpr FormCost kCost32[] = {
     {16, 4, {4.2, 4.8, 7.0, 8.9}, 13.6, 10.5}, {20, 2, {8.3, 13.4}, 33.0, 20.5}, {24, 1, {13.1}, 62.5, 35.5}};
 
+static const FormCost* form_cost(int n, bool f32) {
+  for (const FormCost& x : f32 ? kCost32 : kCost64)
+    if (x.n == n) return &x;
+  return nullptr;
+}
+
 Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns, bool same, bool f32) const {
   PairRule r;
   const long nt = (long)(ps.ntk_all ? ps.ntk_all : ps.ntk) * nx, nj = (long)ps.nsk * ns;
-  const FormCost* fc = nullptr;
-  for (const FormCost& x : f32 ? kCost32 : kCost64)
-    if (x.n == c.geom.n1) fc = &x;
+  const FormCost* fc = form_cost(c.geom.n1, f32);
   if (!fc) return r;
   same = same && nx == ns && !c.ds;
   // a cap without room for one FP32 partial sum's pairs (FP64: one pair) of one target
@@ -82,7 +86,7 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
   const long per_cu = (nt + num_cus - 1) / num_cus;  // targets of the busiest CU
   const int rest = (int)(per_cu % fc->per_cu);
   const double fused = 1e3 * ((double)(per_cu / fc->per_cu) * fc->wg[fc->per_cu - 1] + (rest ? fc->wg[rest - 1] : 0.0));
-  r.fused_ns = fused;
+  r.fused_ns = r.ns = fused;
   // below 4 tiles the triangle is nearly the whole square, and the mirror sums cost a launch
   const bool tri_ok = split_sym && same && ps.ntk == c.nk && ps.nsk == c.nk && ps.qidx == (const int*)c.qidx.ptr &&
                       nt > 3 * kPairTile &&
@@ -99,12 +103,57 @@ Plan::PairRule Plan::pair_rule(const Cell& c, const PairSet& ps, int nx, int ns,
       const size_t least = (size_t)std::min(ns, 16) * c.nr * sizeof(c64);
       r.pairs = nt * nj <= (fc->n == 24 ? 96 * 96 : 128 * 128) && r.pairs_ns < fused &&
                 need + least <= kNoAllocBytes;
+      if (r.pairs) r.ns = r.pairs_ns;
       return r;
     }
   }
-  if (tri_ok && nt * fc->sym * 256.0 / num_cus < fused) r.pairs = r.tri = true;
+  const double sym = nt * fc->sym * 256.0 / num_cus;
+  if (tri_ok && sym < fused) r.pairs = r.tri = true;
   else r.pairs = r.pairs_ns < fused;
+  if (r.pairs) r.ns = r.tri ? sym : r.pairs_ns;
   return r;
+}
+
+// The forked streams run four cells' kernels at a time (the device's hardware queues), whose workgroups
+// share CUs although others are idle: of four cells of 16^3 three to a CU, of 20^3 two. Both estimates
+// leave out some 13 us per cell for its launches; the forked one is within 16% of these sets' times
+// but for that. Measured, forked and in sequence (us): 8 cells of 16^3 / 8 k with
+// 16, 8 and 4 bands 1,821 and 2,019, 1,002 and 587, 512 and 233; 8 of 24^3 / 8 k / 12 b 4,496 and
+// 4,453, of 24^3 / 4 k / 8 b 889 and 640; 4 of 20^3 / 8 k / 8 b 913 and 604; 16^3 / 64 k / 16 b with
+// 16^3 / 8 k / 16 b 9,281 and 9,467; 24^3 / 125 k / 16 b with two smaller 225,600 and 152,100. The
+// sequence has to win by 15% in the estimate.
+bool Plan::batch_in_sequence(const void* const* u, const void* const* phi, const int* nphi) const {
+  constexpr int kQueues = 4;
+  struct One {
+    double fused, nj, nt;
+    const FormCost* fc;
+  };
+  std::vector<One> cs;
+  bool pairs = false;
+  double seq = 0.0, work = 0.0, forked = 0.0;
+  for (size_t i = 0; i < cells.size(); ++i) {
+    const Cell& c = cells[i];
+    const PairRule r = pair_rule(c, c.fwd(), nphi[i], c.nb, phi[i] == u[i], true);
+    const FormCost* fc = form_cost(c.geom.n1, true);
+    if (!fc || r.fused_ns == 0.0) return false;
+    const double nj = (double)c.nsrc * c.nb, nt = (double)c.nk * nphi[i];
+    pairs = pairs || r.pairs;
+    seq += nj * r.ns;
+    work += nj * nt * fc->wg[fc->per_cu - 1] * 1e3 / fc->per_cu / num_cus;
+    cs.push_back(One{nj * r.fused_ns, nj, nt, fc});
+  }
+  std::sort(cs.begin(), cs.end(), [](const One& a, const One& b) { return a.fused > b.fused; });
+  for (size_t i = 0; i < cs.size(); i += kQueues) {
+    const int beside = (int)std::min<size_t>(kQueues, cs.size() - i);
+    double most = 0.0;
+    for (int k = 0; k < beside; ++k) {
+      const One& o = cs[i + k];
+      const int stack = std::min(o.fc->per_cu, std::max(1, beside - 1));
+      most = std::max(most, o.nt > num_cus ? o.fused : o.nj * o.fc->wg[stack - 1] * 1e3);
+    }
+    forked += most;
+  }
+  return pairs && 1.15 * seq < std::max(forked, work);
 }
 
 template <typename TW, typename TM>

@@ -243,8 +243,12 @@ struct Plan {
     bool pairs = false, tri = false;
     bool shared = false;  // fock_apply_noalloc serves the same sum, by the same rule
     double fused_ns = 0.0, pairs_ns = 0.0;  // modelled cost of the one-sided sum per source (0: no fused form)
+    double ns = 0.0;                        // and of the form chosen
   };
   PairRule pair_rule(const Cell& c, const PairSet& ps, int nx, int ns, bool same, bool f32) const;
+  // FP32 cells of 16^3 to 24^3 with every k-point a source: whether they are faster one after another, in
+  // the pair form where that is the rule, than as the batched launch's forked streams
+  bool batch_in_sequence(const void* const* u, const void* const* phi, const int* nphi) const;
   // whether the scratch of such a sum can be had: under capture, where nothing can be allocated, what is
   // there has to hold it, if in smaller blocks
   bool pairs_ready(int nr, int nt, int nj, int ns, size_t field_bytes, bool sums32, bool two, bool tri) const;

@@ -380,7 +380,38 @@ void refused_sum_is_not_profiled() {
   CHECK(n == 0 && ms == 0.0);
 }
 
+// Without a tuned choice the batched call runs the faster of its forked cells (a captured graph) and the cells
+// in sequence through the pair form, by what both took on the device.
+void batched_route() {
+  struct Set {
+    std::vector<CellSpec> cells;
+    bool sequence;
+  };
+  auto many = [](int n, CellSpec c) { return std::vector<CellSpec>(n, c); };
+  for (const Set& s : {Set{many(8, cube(16, 8, 16)), false}, Set{many(8, cube(16, 8, 8)), true},
+                       Set{many(8, cube(16, 8, 4)), true}, Set{many(4, cube(20, 8, 8)), true},
+                       Set{many(8, cube(20, 8, 8)), true}, Set{many(8, cube(24, 4, 8)), true},
+                       Set{{cube(16, 64, 16), cube(16, 8, 16)}, false}, Set{{cube(24, 64, 16), cube(16, 1, 1)}, true},
+                       Set{{cube(24, 125, 16), cube(20, 64, 12), cube(16, 27, 8)}, true},
+                       Set{{cube(16, 8, 8), cube(20, 4, 8), cube(24, 2, 8)}, true},
+                       Set{many(8, cube(16, 1, 4)), true}, Set{many(2, cube(16, 216, 16)), false}}) {
+    TestPlan p(FOCK_FP32_COMP, s.cells);
+    std::vector<const void*> u;
+    std::vector<void*> out;
+    std::vector<int> np;
+    for (size_t i = 0; i < s.cells.size(); ++i) {
+      u.push_back(p.fields((int)i));
+      out.push_back(p.fields((int)i));
+      np.push_back(s.cells[i].nb);
+    }
+    fake::st().ops.clear();
+    OK(fock_apply_batched(p.h, u.data(), u.data(), np.data(), out.data(), fake::stream(0)));
+    CHECK((fake::launches("graph") == 0) == s.sequence);
+  }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"batched_route", batched_route},
     {"refused_sum_is_not_profiled", refused_sum_is_not_profiled},
     {"captures_use_what_is_there", captures_use_what_is_there},
     {"fused_sums_beyond_the_cap", fused_sums_beyond_the_cap},
