@@ -410,7 +410,23 @@ void batched_route() {
   }
 }
 
+// A plan created with the split form's wait limit set runs it at 32^3, with its mirror copies where u is the
+// targets.
+void wait_limit_runs_the_split_form() {
+  setenv("FOCKMI_SPLIT_WAIT_TICKS", "5000000", 1);
+  TestPlan p(FOCK_FP32_COMP, {cube(32, 8, 3)});
+  unsetenv("FOCKMI_SPLIT_WAIT_TICKS");
+  void *u = p.fields(), *phi = p.fields(), *out = p.fields();
+  fake::st().ops.clear();
+  OK(fock_apply(p.h, 0, u, u, 3, out, fake::stream(0)));
+  CHECK(fake::launches("split32_kernel") == 1 && fake::launches("sym_combine") == 1 && fake::launches("pair_w") == 0);
+  fake::st().ops.clear();
+  OK(fock_apply(p.h, 0, u, phi, 3, out, fake::stream(0)));
+  CHECK(fake::launches("split32_kernel") == 1 && fake::launches("sym_combine") == 0 && fake::launches("pair_w") == 0);
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"wait_limit_runs_the_split_form", wait_limit_runs_the_split_form},
     {"batched_route", batched_route},
     {"refused_sum_is_not_profiled", refused_sum_is_not_profiled},
     {"captures_use_what_is_there", captures_use_what_is_there},

@@ -13,7 +13,8 @@ LIBDIR = os.path.join(os.path.dirname(HERE), "paper_1507_05156_amd")
 SCENARIOS = ("captured_buffers_stay", "growth_frees", "streams_in_order", "threads_one_at_a_time",
              "captures_without_plan_memory", "first_sum_allocates_once", "tuned_call_without_room",
              "symmetry_switch", "same_kernel_for_a_k_range", "captures_use_what_is_there",
-             "fused_sums_beyond_the_cap", "refused_sum_is_not_profiled", "batched_route")
+             "fused_sums_beyond_the_cap", "refused_sum_is_not_profiled", "batched_route",
+             "wait_limit_runs_the_split_form")
 
 
 @pytest.fixture(scope="module")
