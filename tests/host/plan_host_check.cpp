@@ -425,7 +425,35 @@ void wait_limit_runs_the_split_form() {
   CHECK(fake::launches("split32_kernel") == 1 && fake::launches("sym_combine") == 0 && fake::launches("pair_w") == 0);
 }
 
+// What test_gpu_grid_forms.py runs: the fused kernels, by a tuning file in FP32 and by the rule for separate
+// targets in FP64, against symmetric pairs with u as targets.
+void grid_forms_of_the_device_tests() {
+  const std::string path = std::string(getenv("TMPDIR") ? getenv("TMPDIR") : "/tmp") + "/fockmi_grid_forms.json";
+  for (const CellSpec& c : {cube(16, 54, 19), cube(20, 28, 19), cube(24, 17, 19)}) {
+    FILE* f = fopen(path.c_str(), "w");
+    fprintf(f, "{\"gfx950/fp32/fused/n%dx%dx%d/nt%d/ns%d/nb%d/nx%d\": {\"variant\": 0, \"xcd_map\": 1}}\n", c.n[0], c.n[0],
+            c.n[0], c.nk, c.nk, c.nb, c.nb);
+    fclose(f);
+    TestPlan p(FOCK_FP32_COMP, {c}, path.c_str());
+    void *u = p.fields(), *out = p.fields();
+    fake::st().ops.clear();
+    OK(fock_apply(p.h, 0, u, u, c.nb, out, fake::stream(0)));
+    CHECK(fake::launches("fused_apply") == 1 && fake::launches("pair_w") == 0);
+  }
+  remove(path.c_str());
+  for (const CellSpec& c : {cube(16, 27, 19), cube(20, 14, 18), cube(24, 8, 32)}) {
+    TestPlan p(FOCK_FP64_FUSED, {c});
+    void *u = p.fields(), *v = p.fields(), *out = p.fields();
+    fake::st().ops.clear();
+    OK(fock_apply(p.h, 0, u, v, c.nb, out, fake::stream(0)));
+    CHECK(fake::launches("fused64") == 1 && fake::launches("pair_w") == 0);
+    OK(fock_apply(p.h, 0, u, u, c.nb, out, fake::stream(0)));
+    CHECK(fake::launches("mirror_add") == 1);
+  }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"grid_forms_of_the_device_tests", grid_forms_of_the_device_tests},
     {"wait_limit_runs_the_split_form", wait_limit_runs_the_split_form},
     {"batched_route", batched_route},
     {"refused_sum_is_not_profiled", refused_sum_is_not_profiled},
