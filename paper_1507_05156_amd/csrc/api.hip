@@ -202,7 +202,7 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
   const std::string key = key_for(c, ps, nx, "plain");
   TuneEntry te;
   if (tune.get(key, &te)) return run((size_t)te.fields["batch_mb"] << 20);
-  if (!tuning || accumulate) return run(pair_batch);
+  if (!tuning || accumulate || g_capturing) return run(pair_batch);
   // measure the pair-batch size (each candidate writes the same result to rounding)
   TuneEvents ev;
   hipError_t e = ev.create();
@@ -460,7 +460,7 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
   if (tune.get(key, &te)) {
     variant = fallback_variant((int)te.fields["variant"]);
     a.xcd_map = (int)te.fields["xcd_map"];
-  } else if (tuning && !accumulate) {
+  } else if (tuning && !accumulate && !g_capturing) {
     // measure every candidate on this call's data (each writes the same result up
     // to the grouping of its FP64 additions); the XCD map matters only for the grid form
     TuneEvents ev;
@@ -500,10 +500,14 @@ fock_status Plan::run_fused(Cell& c, const PairSet& ps, const c128* X, int nx, c
     variant = bv;
     a.xcd_map = bx;
   }
-  // under capture without scratch for the pair form: a form that sums on the CU
-  if (variant == 3 &&
-      !pairs_ready(nr, nitems, ps.nsk * ns, ns, nr * sizeof(c64), true, rule.tri, rule.tri))
-    variant = n == 32 && has_ls ? 1 : 0;
+  // Under capture without scratch for the mirror sums every pair, without any for the pair form a form that
+  // sums on the CU, and the pair form where only its scratch is there.
+  const size_t fb = nr * sizeof(c64);
+  const bool one_sided = pairs_ready(nr, nitems, ps.nsk * ns, ns, fb, true, false, false);
+  if (rule.tri && !pairs_ready(nr, nitems, ps.nsk * ns, ns, fb, true, true, true)) rule.tri = false;
+  if (variant == 3 && !rule.tri && !one_sided) variant = n == 32 && has_ls ? 1 : 0;
+  if (variant != 3 && g_capturing && one_sided && comp.bytes < (size_t)(variant == 1 ? ksplit : 1) * nitems * fb)
+    variant = 3;
   if ((s = prepare(variant)) != FOCK_OK) return s;
   if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
   if ((e = launch(variant)) != hipSuccess) return hip_fail(e, "fused pair kernel");
@@ -550,8 +554,9 @@ fock_status Plan::run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx,
   // if its buffers are there already.
   if (rule.pairs && g_capturing &&
       ((c.f64f && fused64_acc_scratch_elems(c.geom.n1, 1) == 0) ||
-       !pairs_ready(c.nr, nitems, ps.nsk * ns, ns, c.nr * sizeof(c128), false, rule.tri, rule.tri)))
+       !pairs_ready(c.nr, nitems, ps.nsk * ns, ns, c.nr * sizeof(c128), false, false, false)))
     rule.pairs = false;
+  if (rule.tri && !pairs_ready(c.nr, nitems, ps.nsk * ns, ns, c.nr * sizeof(c128), false, true, true)) rule.tri = false;
   if (rule.pairs) {
     if ((e = prof_begin(st)) != hipSuccess) return hip_fail(e, "profile event");
     auto sums = [&](bool tri) -> fock_status {

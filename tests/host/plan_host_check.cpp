@@ -463,7 +463,32 @@ void new_plan_holds_no_temporary_tables() {
   }
 }
 
+// The same in FP32, whose sums on the CU need buffers that the pair form leaves unsized: a k-range, the energy
+// gradient and separate targets captured after an eager adjoint (the choice of the form falls on the fused
+// kernel for the k-range), and in a plan with a tuning cache, which measures nothing inside a capture.
+void fp32_captures_use_what_is_there() {
+  const std::string path = std::string(getenv("TMPDIR") ? getenv("TMPDIR") : "/tmp") + "/fockmi_capture_check.json";
+  for (const CellSpec& c : {cube(20, 103, 2), cube(16, 40, 20), cube(32, 61, 1)})
+    for (int tuned : {0, 1}) {
+      remove(path.c_str());
+      TestPlan p(FOCK_FP32_COMP, {c}, tuned ? path.c_str() : nullptr);
+      const hipStream_t q = fake::stream(0);
+      void *u = p.fields(), *out = p.fields(), *phi = p.fields(), *g = p.fields(), *gu = p.fields(), *gp = p.fields();
+      OK(fock_vjp(p.h, 0, u, phi, c.nb, g, gu, gp, q));
+      fake::st().bad_mallocs = 0;
+      fake::st().ops.clear();
+      fake::st().capturing.insert(q);
+      OK(fock_energy_vjp(p.h, 0, u, 1.0, gu, q));
+      OK(fock_apply_krange(p.h, 0, u, 1, c.nk / 2, phi, c.nb, out, q));
+      OK(fock_apply(p.h, 0, u, phi, c.nb, out, q));
+      fake::st().capturing.clear();
+      CHECK(fake::st().bad_mallocs == 0);
+    }
+  remove(path.c_str());
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"fp32_captures_use_what_is_there", fp32_captures_use_what_is_there},
     {"new_plan_holds_no_temporary_tables", new_plan_holds_no_temporary_tables},
     {"grid_forms_of_the_device_tests", grid_forms_of_the_device_tests},
     {"wait_limit_runs_the_split_form", wait_limit_runs_the_split_form},

@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIBDIR = os.path.join(os.path.dirname(HERE), "paper_1507_05156_amd")
 SCENARIOS = ("captured_buffers_stay", "growth_frees", "streams_in_order", "threads_one_at_a_time",
              "captures_without_plan_memory", "first_sum_allocates_once", "tuned_call_without_room",
-             "symmetry_switch", "same_kernel_for_a_k_range", "captures_use_what_is_there",
+             "symmetry_switch", "same_kernel_for_a_k_range", "captures_use_what_is_there", "fp32_captures_use_what_is_there",
              "fused_sums_beyond_the_cap", "refused_sum_is_not_profiled", "batched_route",
              "wait_limit_runs_the_split_form", "grid_forms_of_the_device_tests",
              "new_plan_holds_no_temporary_tables")
