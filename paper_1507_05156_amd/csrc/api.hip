@@ -74,6 +74,14 @@ PlanCall::~PlanCall() {
   g_call = nullptr;
 }
 
+bool PlanCall::give_back(const DevBuf* asking) {
+  if (!g_call || g_capturing) return false;
+  DevBuf& b = g_call->p_->pscratch;
+  if (&b == asking || !b.ptr || b.held) return false;
+  b.drop();
+  return true;
+}
+
 void DevBuf::hold() {
   if (ptr && g_capturing) held = true;
 }
@@ -87,6 +95,10 @@ fock_status DevBuf::ensure(size_t need, size_t cap, const char* what) {
     return fail(FOCK_ERR_NOMEM, "%s: %zu bytes exceed the plan workspace cap of %zu bytes", what, need, cap);
   drop();
   hipError_t e = hipMalloc(&ptr, need);
+  if (e != hipSuccess && PlanCall::give_back(this)) {
+    (void)hipGetLastError();
+    e = hipMalloc(&ptr, need);
+  }
   if (e != hipSuccess) {
     ptr = nullptr;
     (void)hipGetLastError();
@@ -176,12 +188,12 @@ fock_status Plan::run_plain(Cell& c, const PairSet& ps, const c128* X, int nx, c
       if (c.f32plain)
         return run_pairs<float, double>(
             nr, 0, nt, nj, ns, plane_stage<float>(c.geom, num_cus, ps, X, nx, P, ns, (const double*)c.Kpl.ptr, st), M,
-            out, scale, accumulate, m, batch, st);
+            out, scale, accumulate, m, batch, st, cube || m.dst);
       return run_pairs<double, double>(
           nr, 0, nt, nj, ns,
           cube ? cube_stage<double>(c.geom.n1, num_cus, ps, X, nx, P, ns, (const double*)c.Kp.ptr, st)
                : plane_stage<double>(c.geom, num_cus, ps, X, nx, P, ns, (const double*)c.Kpl.ptr, st),
-          M, out, scale, accumulate, m, batch, st);
+          M, out, scale, accumulate, m, batch, st, cube || m.dst);
     };
     fock_status s = sums(mr);
     if (s == FOCK_ERR_NOMEM && mr.dst) {

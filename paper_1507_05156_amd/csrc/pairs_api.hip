@@ -231,7 +231,7 @@ PairsLayout pairs_layout(int nr, int nt, int nj, int ns, size_t fb, size_t budge
     return at;
   };
   piece((size_t)l.rows * l.njmax * fb);
-  l.run = piece((size_t)l.rows * nr * (sums32 ? sizeof(c64) : sizeof(c128)));
+  if (tri ? nt > l.rows : nj > l.njmax) l.run = piece((size_t)l.rows * nr * (sums32 ? sizeof(c64) : sizeof(c128)));
   if (two) l.mir = piece((size_t)l.groups * nj * nr * sizeof(c128));
   if (two && sums32) l.mcomp = piece((size_t)l.groups * nj * nr * sizeof(c64));
   return l;
@@ -244,7 +244,7 @@ bool Plan::pairs_ready(int nr, int nt, int nj, int ns, size_t fb, bool sums32, b
 
 template <typename TW, typename TM>
 fock_status Plan::run_pairs(int nr, int np, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M, c128* out,
-                            double scale, bool accumulate, const Mirror<TM>& mr, size_t batch, hipStream_t st) {
+                            double scale, bool accumulate, const Mirror<TM>& mr, size_t batch, hipStream_t st, bool others) {
   constexpr bool F32 = sizeof(TM) == 4;
   const size_t fb = (size_t)nr * sizeof(cx<TW>);
   const bool two = mr.dst != nullptr;
@@ -261,7 +261,8 @@ fock_status Plan::run_pairs(int nr, int np, int nt, int nj, int ns, const PairSt
                   workspace_cap);
     s = pscratch.ensure(l.end, 0, "pair scratch");
     if (s == FOCK_OK) break;
-    if (batch <= (size_t(64) << 20)) return s;
+    // other forms are faster than small batches, where there are any
+    if (batch <= (others ? size_t(64) << 20 : fb)) return s;
   }
   g_last_error.clear();  // a smaller batch after a failed allocation is no failure
   char* base = (char*)pscratch.ptr;
@@ -323,7 +324,7 @@ template fock_status pairs_blocks<float, float>(int, int, int, int, int, const P
                                                 c128*, c64*, hipStream_t);
 #define FOCKMI_RUN_PAIRS(TW, TM)                                                                                  \
   template fock_status Plan::run_pairs<TW, TM>(int, int, int, int, int, const PairStage<TW>&, const cx<TM>*, c128*,    \
-                                               double, bool, const Mirror<TM>&, size_t, hipStream_t);
+                                               double, bool, const Mirror<TM>&, size_t, hipStream_t, bool);
 FOCKMI_RUN_PAIRS(float, float)
 FOCKMI_RUN_PAIRS(double, double)
 FOCKMI_RUN_PAIRS(float, double)

@@ -126,7 +126,7 @@ struct Mirror {
 void pairs_block_shape(int nt, int nj, int ns, int nr, size_t fb, size_t budget, bool whole_partials, bool tri,
                        int* rows, long* njmax);
 // The scratch of such a sum, one allocation: the batch of W fields, then (256-byte aligned, at these
-// offsets) the sums kept between the blocks of a row and, when two-sided, the mirror sums of each
+// offsets) the sums kept between the blocks of a row if it has several and, when two-sided, the mirror sums of each
 // group of a row's targets and in FP32 their compensation. One instead of four: an allocation takes
 // longer than a small sum (first application on a new plan, 16^3 / 8 k / 4 bands in FP64: 531 us with
 // one per piece, 181 us, of which the sum is 42).
@@ -234,10 +234,10 @@ struct Plan {
                         c128* out, double scale, bool accumulate, hipStream_t st);
   fock_status run_fused64(Cell& c, const PairSet& ps, const c128* X, int nx, const c128* P, const c128* M,
                           int ns, c128* out, double scale, bool accumulate, hipStream_t st);
-  // a sum in the two-stage pair form, its batch at most `batch` bytes
+  // a sum in the two-stage pair form, its batch at most `batch` bytes; others: the caller has another form
   template <typename TW, typename TM>
   fock_status run_pairs(int nr, int np, int nt, int nj, int ns, const PairStage<TW>& stage, const cx<TM>* M, c128* out,
-                        double scale, bool accumulate, const Mirror<TM>& mr, size_t batch, hipStream_t st);
+                        double scale, bool accumulate, const Mirror<TM>& mr, size_t batch, hipStream_t st, bool others = true);
   // whether the sum runs in the two-stage pair form (cubic grids up to 24), and with the pair symmetry
   struct PairRule {
     bool pairs = false, tri = false;
@@ -316,6 +316,9 @@ class PlanCall {
   PlanCall(const PlanCall&) = delete;
   PlanCall& operator=(const PlanCall&) = delete;
   static void order();  // of this thread's call in progress
+  // frees the plan's pair scratch, which the next pair sum sizes anew, where another buffer finds no
+  // device memory; false: there is none to free
+  static bool give_back(const DevBuf* asking);
 
  private:
   Plan* p_;

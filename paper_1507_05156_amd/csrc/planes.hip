@@ -16,7 +16,7 @@
 // and writes: 2.5 MiB per pair of 32^3 in FP64), at 5.3 TB/s over the kernel; without pass A,
 // B or C (timing copies) it takes 56%, 67% or 70% of its time. 32^3 / 8 k / 16 bands in FP64:
 // 32.1 ms per application with one kernel and one pass over HBM per step (21 passes per pair),
-// 5.3 ms in this form (4.3 ms here, half of it the pair symmetry); adjoint of 16 x 20 x 24 /
+// 5.3 ms in this form (4.45 ms here, half of it the pair symmetry); adjoint of 16 x 20 x 24 /
 // 12 k / 6 bands 7.5 -> 2.1 ms. Loading the pair product's operands in groups of 4 instead of
 // 8, workgroups of 4 waves, two to a CU, and a plain last store were no faster.
 #include "pairs_dev.hpp"

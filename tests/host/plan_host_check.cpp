@@ -487,7 +487,38 @@ void fp32_captures_use_what_is_there() {
   remove(path.c_str());
 }
 
+// On a device with little memory left the pair scratch gives way to the buffers that other calls need, takes
+// no more than the batch of a sum in one block, and shrinks as far as it has to where there is no other form.
+void device_nearly_full() {
+  const hipStream_t q = fake::stream(0);
+  {
+    TestPlan p(FOCK_FP32_COMP, {cube(24, 64, 16)});
+    void *u = p.fields(), *out = p.fields(), *psi = p.fields();
+    const double a[3] = {0.0, 0.0, 0.01};
+    fake::st().limit = fake::st().used() + (size_t(2) << 30);
+    OK(fock_apply(p.h, 0, u, u, 16, out, q));
+    OK(taylor_step(p.h, 0, psi, nullptr, a, 0.01, 0.25, 4, nullptr, q));
+    OK(fock_apply(p.h, 0, u, u, 16, out, q));
+    fake::st().limit = ~size_t(0);
+  }
+  {
+    TestPlan p(FOCK_FP64, {CellSpec{{16, 20, 24}, 3, 5}});
+    void *u = p.fields(), *phi = p.fields(), *out = p.fields();
+    fake::st().limit = fake::st().used() + 15 * 15 * 7680 * 16;  // the batch of all pairs
+    OK(fock_apply(p.h, 0, u, phi, 5, out, q));
+    fake::st().limit = ~size_t(0);
+  }
+  {
+    TestPlan p(FOCK_FP64, {cube(32, 8, 16)});
+    void *u = p.fields(), *phi = p.fields(), *out = p.fields();
+    fake::st().limit = fake::st().used() + (size_t(20) << 20);
+    OK(fock_apply(p.h, 0, u, phi, 16, out, q));
+    fake::st().limit = ~size_t(0);
+  }
+}
+
 const std::map<std::string, std::function<void()>> scenarios = {
+    {"device_nearly_full", device_nearly_full},
     {"fp32_captures_use_what_is_there", fp32_captures_use_what_is_there},
     {"new_plan_holds_no_temporary_tables", new_plan_holds_no_temporary_tables},
     {"grid_forms_of_the_device_tests", grid_forms_of_the_device_tests},
