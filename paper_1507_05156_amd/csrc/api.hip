@@ -792,7 +792,6 @@ fock_status fock_plan_create(const fock_cell_desc* cells, int ncells, fock_prec 
     g_last_error = msg;
     return s;
   }
-  p->ktmp.release();  // every form has its copy
   *out = reinterpret_cast<fockmi_plan>(p);
   return FOCK_OK;
 }

@@ -179,7 +179,7 @@ struct Plan {
   std::vector<Cell> cells;
   size_t workspace_cap = 0;                 // 0 = no cap (FOCKMI_WORKSPACE_CAP overrides)
   int xcd_map = 1;
-  DevBuf ktmp;                              // one cell's tables in natural order, while the plan is created
+  DevBuf ktmp;                              // one cell's tables in natural order, read while its forms' copies are made
   DevBuf shadow_x, shadow_p, shadow_m, comp, accs, vu, partial, dotres, srcbuf, srcout;
   DevBuf psi0, phiA, phiB, predb, srcbuf2, kin, vxb, lam, lam2, gtmp, ftmp, phis, norms, red6, vloc_buf;
   DevBuf sync;                              // lockstep counters of the persistent fused form

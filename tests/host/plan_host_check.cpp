@@ -452,17 +452,6 @@ void grid_forms_of_the_device_tests() {
   }
 }
 
-// A new plan holds its tables in the forms' orders only: in FP64 one table of 8 bytes per point and momentum
-// beside the index and momentum lists.
-void new_plan_holds_no_temporary_tables() {
-  for (const CellSpec& c : {cube(16, 8, 4), cube(32, 8, 4), CellSpec{{16, 20, 24}, 8, 4}}) {
-    const size_t before = fake::st().used();
-    TestPlan p(FOCK_FP64, {c});
-    const size_t table = (size_t)15 * c.n[0] * c.n[1] * c.n[2] * 8;  // 8 k-points in a row: 15 differences
-    CHECK(fake::st().used() - before < table + table / 2);
-  }
-}
-
 // The same in FP32, whose sums on the CU need buffers that the pair form leaves unsized: a k-range, the energy
 // gradient and separate targets captured after an eager adjoint (the choice of the form falls on the fused
 // kernel for the k-range), and in a plan with a tuning cache, which measures nothing inside a capture.
@@ -520,7 +509,6 @@ void device_nearly_full() {
 const std::map<std::string, std::function<void()>> scenarios = {
     {"device_nearly_full", device_nearly_full},
     {"fp32_captures_use_what_is_there", fp32_captures_use_what_is_there},
-    {"new_plan_holds_no_temporary_tables", new_plan_holds_no_temporary_tables},
     {"grid_forms_of_the_device_tests", grid_forms_of_the_device_tests},
     {"wait_limit_runs_the_split_form", wait_limit_runs_the_split_form},
     {"batched_route", batched_route},

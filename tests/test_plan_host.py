@@ -15,7 +15,7 @@ SCENARIOS = ("captured_buffers_stay", "growth_frees", "streams_in_order", "threa
              "symmetry_switch", "same_kernel_for_a_k_range", "captures_use_what_is_there", "fp32_captures_use_what_is_there",
              "fused_sums_beyond_the_cap", "refused_sum_is_not_profiled", "batched_route",
              "wait_limit_runs_the_split_form", "grid_forms_of_the_device_tests",
-             "new_plan_holds_no_temporary_tables", "device_nearly_full")
+             "device_nearly_full")
 
 
 @pytest.fixture(scope="module")
